@@ -162,7 +162,7 @@ int perm_ryser(const bbfg_c128 *A, int32_t n_rows, const int32_t *row_mult, int3
  * memory (tight serving loops, code that must not call hipMalloc).  Same
  * arguments, plan, kernels and result bits as perm_bbfg; every device buffer
  * it uses (binomial table, metadata, Gray table, staged host A, gathered rows,
- * unit partials, results) lives in one file-scope device array of 2 MiB per
+ * unit partials, results) lives in one file-scope device array of 3 MiB per
  * device, which stays allocated until the process ends.  It calls no
  * hipMalloc/hipFree or other device-allocating routine (host planning uses
  * ordinary heap memory).  bbfg_init takes the array's address on the current

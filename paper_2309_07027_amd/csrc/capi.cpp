@@ -343,8 +343,8 @@ try {
             for (int32_t t = 0; t < col_mult[j]; ++t) cmap.push_back(j);
     }
     it.col_map = cmap.data();
-    if (single) BBFG_TRY(get_plan(*c, row_mult, n_rows, (int)n, 0, PLAN_SINGLE, &it.plan));
-    else BBFG_TRY(get_plan(*c, row_mult, n_rows, (int)n, kKindCols, PLAN_SINGLE, &it.plan, it.arena_cols));
+    if (single) BBFG_TRY(get_plan(*c, row_mult, n_rows, (int)n, 0, PLAN_SINGLE, &it.plan, 0, false, kPairMinAddendsCols));
+    else BBFG_TRY(get_plan(*c, row_mult, n_rows, (int)n, kKindCols, PLAN_SINGLE, &it.plan, it.arena_cols, false, kPairMinAddendsCols));
     double res[2], diag[2];
     RunResult rr;
     BBFG_TRY(run_perms(*c, items, 0, single, res, diag, &rr));

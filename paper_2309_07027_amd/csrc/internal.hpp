@@ -17,7 +17,9 @@ constexpr int kBinomDim = kMaxN + 1;
 //   HIGH : a per-segment digit;  Delta = (h / stride) % radix, h = block index.
 //   LOW  : a Gray-walked digit;  Delta = reflected decode of the position t
 //          inside the block (Sec. 2.2 reflected n-ary Gray code).
-enum RowKind : int32_t { ROW_FIXED = 0, ROW_LANE = 1, ROW_HIGH = 2, ROW_LOW = 3 };
+//   MID, INNER: digits of the pair walk (pair_core.hpp): a position of its
+//          uniform table, and one of the four binary digits of its blocks.
+enum RowKind : int32_t { ROW_FIXED = 0, ROW_LANE = 1, ROW_HIGH = 2, ROW_LOW = 3, ROW_MID = 4, ROW_INNER = 5 };
 
 // One kept row.  Column-sum coefficient = base - 2 * Delta  (Eq. Deltak), where
 // base = M'_k + (1 if the row is the pivot).  Weight factor (-1)^Delta C(mp, Delta).
@@ -99,6 +101,11 @@ inline uint32_t mag_every_for(uint64_t units_per_group)
     return e > 1 ? (uint32_t)e : 1u;
 }
 
+// Unit counters of a launch sequence: the walk's and the pair walk's, on cache
+// lines of their own.
+constexpr uint32_t kCounters = 2;
+constexpr uint32_t kCounterStride = 32;
+
 constexpr uint32_t kUnitChunkLog2 = 6;
 constexpr uint32_t kUnitChunk = 1u << kUnitChunkLog2;
 
@@ -121,6 +128,64 @@ struct PrepItem {
     int32_t n;
     int32_t r;
     int32_t f32;
+    int32_t rows_only;  // no +-2a rows
+};
+
+// ---------------------------------------------------------------------------
+// pair walk (pair_core.hpp)
+// ---------------------------------------------------------------------------
+constexpr int kPairBits = 4;                  // inner binary digits
+constexpr int kPairBlock = 1 << kPairBits;    // addends of a block
+constexpr int kPairSlots = 2 + kPairBits;     // complex values of a pair: two column sums, the differences
+constexpr int kPairConsts = kPairBits * (kPairBits - 1) / 2;  // constants of a pair
+constexpr int kPairWaves = 16;               // wavefronts of a work group
+constexpr int kPairMidMax = 512;              // most mid positions
+constexpr int kPairMids = 9;                  // most mid digits
+constexpr int kPairMax = (kMaxN + 1) / 2;     // most pairs of columns
+
+// The pair walk takes sums of more than this many addends (with column
+// multiplicities, more than the second number).  A unit's start costs about
+// 7 us, which shorter sums do not earn back in full; up to these sizes the walk
+// stays the one whose bits the CPU emulation of walk_core.hpp pins.
+constexpr uint64_t kPairMinAddends = uint64_t(1) << 19;
+constexpr uint64_t kPairMinAddendsCols = uint64_t(1) << 22;
+constexpr int kPairMinCols = 4;
+
+// Device descriptor of one permanent evaluated by the pair walk.  Its units are
+// (lane group, high position) in that order; a unit covers every mid position.
+struct PairDesc {
+    uint64_t a_off;        // element offset of the r x n kept rows (complex)
+    uint64_t mid_off;      // double offsets into the tables: mid x np x kPairSlots complex uniform parts,
+    uint64_t weight_off;   //   the mid positions' signed weights,
+    uint64_t const_off;    //   np x 6 complex constants
+    uint64_t part_base;    // first partial slot (one per unit)
+    uint32_t unit_base;    // first unit of the item in the launch
+    uint32_t units;        // groups * high
+    uint32_t rowinfo_off;  // entry offset of the r RowInfo records
+    uint32_t lane_product;
+    uint32_t mid;          // mid positions
+    uint32_t high;         // high positions
+    uint32_t col_pow;
+    int32_t n;             // columns
+    int32_t np;            // pairs of columns, (n + 1) / 2
+    int32_t r;             // kept rows
+    int32_t inner[kPairBits];  // kept rows of the inner digits
+    int32_t mids;              // mid digits and their kept rows
+    int32_t mid_row[kPairMids];
+};
+
+// Kernel arguments of the pair walk (passed by value).
+struct PairArgs {
+    const PairDesc* descs;
+    const RowInfo* rowinfo;
+    const double* a;
+    double* tables;
+    const double* binom;
+    double* partials;
+    uint32_t* unit_item;     // item of each unit (null: one item)
+    uint32_t* counter;
+    uint32_t total_units;
+    uint32_t np_max;
 };
 
 // Kernel arguments of the walk kernels (passed by value).

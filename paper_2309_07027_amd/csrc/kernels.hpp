@@ -32,6 +32,12 @@ const void* walk_minors_fn_b32();
 const void* walk_minors_fn_b48();
 hipError_t launch_walk_minors(int bucket, uint32_t grid, hipStream_t s, const WalkArgs& A);
 hipError_t launch_reset_counter(uint32_t* counter, hipStream_t s);
+// pair walk (walk_pairs.hip): tables of the items, then the walk; pow: items with
+// col_pow >= 2
+const void* pair_walk_fn(bool pow);
+size_t pair_lds_bytes(uint32_t np);
+hipError_t launch_pair_tables(uint32_t items, uint32_t blocks, hipStream_t s, const PairArgs& A);
+hipError_t launch_pair_walk(bool pow, uint32_t grid, hipStream_t s, const PairArgs& A);
 hipError_t launch_prep(uint32_t items, hipStream_t s, const PrepItem* it, const uint32_t* srcrow, const uint32_t* srccol,
                        double* a, double* a2, float* af, float* a2f);
 hipError_t launch_finalize(uint32_t results, hipStream_t s, const PermDesc* descs, const uint32_t* res_item,

@@ -11,7 +11,7 @@
 //
 // Layout of the array (256-byte aligned regions):
 //   binomial table | metadata | Gray table | staged A | rows and +-2a rows |
-//   unit partials | results and diagnostics
+//   unit partials | results and diagnostics | unit counters | pair-walk tables
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,7 +25,7 @@
 namespace bbfg {
 namespace {
 
-constexpr size_t kScratchBytes = size_t(2) << 20;
+constexpr size_t kScratchBytes = size_t(3) << 20;
 constexpr uint64_t kMaxUnits = 32768;  // unit partials the array holds
 constexpr int kMaxDevices = 64;
 
@@ -49,11 +49,17 @@ constexpr size_t kOffPartials = align256(kOffArena + kArenaBytes);
 constexpr size_t kPartialBytes = sizeof(double) * kPartialDoubles * kMaxUnits;
 constexpr size_t kOffResults = align256(kOffPartials + kPartialBytes);
 constexpr size_t kResultBytes = 256;
-static_assert(kOffResults + kResultBytes <= kScratchBytes, "scratch layout exceeds the array");
+constexpr size_t kOffCounters = align256(kOffResults + kResultBytes);
+constexpr size_t kCounterBytes = sizeof(uint32_t) * kCounters * kCounterStride;
+constexpr size_t kOffPairs = align256(kOffCounters + kCounterBytes);
+constexpr size_t kPairBytes = kScratchBytes - kOffPairs;
+static_assert(kOffPairs < kScratchBytes, "scratch layout exceeds the array");
 
 std::mutex g_mu;                        // serialises no-allocation calls (they share the array)
 char* g_ptr[kMaxDevices] = {};           // device address of `scratch`, per device
-int g_waves[kMaxDevices][kMaxN + 1] = {};  // resident walk wavefronts per CU, per device and n
+int g_waves[kMaxDevices][kMaxN + 1] = {};  // resident walk wavefronts, per device and n
+int g_pair_groups[kMaxDevices][kPairMax + 1] = {};  // work groups of the pair walk per CU, per device and pairs
+uint32_t g_ncu[kMaxDevices] = {};
 alignas(256) char g_host_meta[kMetaBytes + kTableBytes];  // host image of metadata + table
 
 // Once per device, with that device current: the array's device address and
@@ -140,7 +146,19 @@ try {
     std::string err;
     int rc = build_plan(row_mult, n_rows, n_cols, slots, pp, P, err);
     if (rc != BBFG_OK) return set_error(rc, "%s", err.c_str());
-    if (P.units > kMaxUnits) {
+    // the pair walk, when its partials and tables fit the array
+    const int np = (n_cols + 1) / 2;
+    if (!g_ncu[dev]) {
+        int ncu = 0;
+        BBFG_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+        g_ncu[dev] = (uint32_t)std::max(1, ncu);
+    }
+    if (!g_pair_groups[dev][np]) BBFG_TRY(pair_occupancy(np, false, &g_pair_groups[dev][np]));
+    if (auto pair = build_pair_plan(P, n_cols, g_ncu[dev])) {
+        const uint64_t doubles = pair->mid * np * 2 * kPairSlots + pair->mid + np * 2 * kPairConsts + 24;
+        if (pair->units <= kMaxUnits && sizeof(double) * doubles <= kPairBytes) P.pair = pair;
+    }
+    if (!P.pair && P.units > kMaxUnits) {
         // longer units, so that the partials fit the array (still whole rounds of slots)
         const uint64_t total = (uint64_t)P.groups * P.span;
         const uint64_t rounds = std::max<uint64_t>(1, kMaxUnits / slots);
@@ -162,6 +180,7 @@ try {
     const size_t o_prep = L.add(sizeof(PrepItem));
     const size_t o_src = L.add(sizeof(uint32_t) * (size_t)r);
     const size_t o_ritem = L.add(sizeof(uint32_t));
+    const size_t o_pair = L.add(sizeof(PairDesc));
     if (L.size > kMetaBytes) return set_error(BBFG_ERANGE, "metadata beyond the no-allocation maximum");
     char* H = g_host_meta;
     std::memset(H, 0, L.size);
@@ -185,7 +204,7 @@ try {
     d.a_off = 0;
     d.a2_off = (uint64_t)r * n;
     d.tab = tab;
-    d.units = P.units;
+    d.units = P.pair ? P.pair->units : P.units;
     d.units_per_group = P.units_per_group;
     d.span = P.span;
     d.n = n;
@@ -197,7 +216,7 @@ try {
     d.err_coeff = P.err_coeff * 0x1.0p-53;
     d.col_pow = 1;
     d.mag_every = 1;
-    std::memcpy(H + o_row, P.rows.data(), sizeof(RowInfo) * (size_t)r);
+    std::memcpy(H + o_row, (P.pair ? P.pair->rows : P.rows).data(), sizeof(RowInfo) * (size_t)r);
     PrepItem& q = *reinterpret_cast<PrepItem*>(H + o_prep);
     q.src = src;
     q.ld = (uint32_t)n_cols;
@@ -206,9 +225,14 @@ try {
     q.srccol_off = kIdentityCols;
     q.n = n;
     q.r = r;
+    q.rows_only = P.pair ? 1 : 0;
     uint32_t* hs = reinterpret_cast<uint32_t*>(H + o_src);
     for (int k = 0; k < r; ++k) hs[k] = (uint32_t)P.src_row[(size_t)k];
     std::memcpy(g_host_meta + kMetaBytes, P.table->data(), tab_bytes);
+
+    uint64_t pair_doubles = 0, pair_positions = 0;
+    if (P.pair)
+        pair_positions = fill_pair_desc(*reinterpret_cast<PairDesc*>(H + o_pair), d, P, 0, &pair_doubles);
 
     WalkArgs W;
     std::memset(&W, 0, sizeof W);
@@ -222,10 +246,28 @@ try {
     W.nitem = 1;
 
     BBFG_HIP(hipMemcpyAsync(D, H, L.size, hipMemcpyHostToDevice, s));
-    BBFG_HIP(hipMemcpyAsync(base + kOffTable, g_host_meta + kMetaBytes, tab_bytes, hipMemcpyHostToDevice, s));
+    if (!P.pair)
+        BBFG_HIP(hipMemcpyAsync(base + kOffTable, g_host_meta + kMetaBytes, tab_bytes, hipMemcpyHostToDevice, s));
     BBFG_HIP(launch_prep(1, s, reinterpret_cast<const PrepItem*>(D + o_prep), reinterpret_cast<const uint32_t*>(D + o_src),
                          nullptr, arena, arena, nullptr, nullptr));
-    BBFG_HIP(launch_walk_single(n, 0, (uint32_t)P.units, s, W, 0u));
+    if (P.pair) {
+        PairArgs PA;
+        std::memset(&PA, 0, sizeof PA);
+        PA.descs = reinterpret_cast<const PairDesc*>(D + o_pair);
+        PA.rowinfo = W.rowinfo;
+        PA.a = arena;
+        PA.tables = reinterpret_cast<double*>(base + kOffPairs);
+        PA.binom = W.binom;
+        PA.partials = partials;
+        PA.counter = reinterpret_cast<uint32_t*>(base + kOffCounters) + kCounterStride;
+        PA.total_units = (uint32_t)P.pair->units;
+        PA.np_max = (uint32_t)(n + 1) / 2;
+        BBFG_HIP(launch_reset_counter(reinterpret_cast<uint32_t*>(base + kOffCounters), s));
+        BBFG_HIP(launch_pair_tables(1, pair_table_blocks(1, pair_positions, PA.np_max), s, PA));
+        BBFG_HIP(launch_pair_walk(false, (uint32_t)std::min<uint64_t>((uint64_t)g_pair_groups[dev][PA.np_max] * g_ncu[dev], P.pair->units), s, PA));
+    } else {
+        BBFG_HIP(launch_walk_single(n, 0, (uint32_t)P.units, s, W, 0u));
+    }
     BBFG_HIP(launch_finalize(1, s, W.descs, reinterpret_cast<const uint32_t*>(D + o_ritem), partials, results,
                              results + 2));
     double host_res[4];
@@ -239,7 +281,7 @@ try {
         bool mult = false;
         for (int32_t i = 0; i < n_rows; ++i) mult = mult || row_mult[i] > 1;
         info->n_addends = P.n_addends;
-        info->n_units = P.units;
+        info->n_units = d.units;
         info->flops = (double)P.n_addends * walk_flops(n_cols, mult);
     }
     return BBFG_OK;

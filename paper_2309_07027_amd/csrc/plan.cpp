@@ -143,6 +143,118 @@ int TableCache::get(const std::vector<uint32_t>& radix, TablePtr* out, std::stri
     return BBFG_OK;
 }
 
+namespace {
+
+// Products of subsets of the digits' radices up to `cap`: mask[p] = positions in
+// `digits` of a subset with product p, or -1.
+std::vector<int64_t> subset_products(const std::vector<int>& digits, const std::vector<RowInfo>& rows, uint32_t cap)
+{
+    std::vector<int64_t> mask(cap + 1, -1);
+    mask[1] = 0;
+    for (size_t i = 0; i < digits.size() && i < 62; ++i) {
+        const uint32_t R = rows[(size_t)digits[i]].radix;
+        for (uint32_t p = cap / R; p >= 1; --p)
+            if (mask[p] >= 0 && !(mask[p] >> i & 1) && mask[p * R] < 0) mask[p * R] = mask[p] | ((int64_t)1 << i);
+    }
+    return mask;
+}
+
+}  // namespace
+
+std::shared_ptr<const PairPlan> build_pair_plan(const HostPlan& P, int n_cols, uint32_t work_groups,
+                                                uint64_t min_addends)
+{
+    // the Ryser sum of the same rows has about twice the addends (no pivot)
+    if (P.n_addends <= min_addends * (P.pivot < 0 ? 2 : 1) || n_cols < kPairMinCols) return nullptr;
+    std::vector<int> digits, twos;
+    for (int k = 0; k < P.r; ++k) {
+        const uint32_t R = P.rows[(size_t)k].radix;
+        if (R >= 2) digits.push_back(k);
+        if (R == 2) twos.push_back(k);
+    }
+    if ((int)twos.size() < kPairBits) return nullptr;
+    auto pp = std::make_shared<PairPlan>();
+    PairPlan& Q = *pp;
+    Q.rows = P.rows;
+    for (RowInfo& x : Q.rows) {
+        x.kind = ROW_FIXED;
+        x.stride = 1;
+    }
+    std::vector<char> used((size_t)P.r, 0);
+    for (int i = 0; i < kPairBits; ++i) {
+        Q.inner[i] = twos[twos.size() - (size_t)kPairBits + (size_t)i];
+        Q.rows[(size_t)Q.inner[i]].kind = ROW_INNER;
+        used[(size_t)Q.inner[i]] = 1;
+    }
+    auto unused = [&]() {
+        std::vector<int> v;
+        for (int k : digits)
+            if (!used[(size_t)k]) v.push_back(k);
+        return v;
+    };
+    const uint64_t rest = P.n_addends / kPairBlock;
+    for (int k : choose_lane_digits(unused(), P.rows, rest)) {
+        Q.rows[(size_t)k].kind = ROW_LANE;
+        Q.rows[(size_t)k].stride = Q.lane_product;
+        Q.lane_product *= P.rows[(size_t)k].radix;
+        used[(size_t)k] = 1;
+    }
+    Q.groups = (Q.lane_product + kWave - 1) / kWave;
+    // lanes left idle cost more than the walk gains
+    if (Q.lane_product * 10 < Q.groups * kWave * 9) return nullptr;
+
+    // Mid positions (blocks of 16 addends per lane that a unit shares out to its
+    // wavefronts).  A unit's start, the lane parts in LDS, costs about as much as
+    // 120 pairs' blocks (7 us); positions that the wavefronts do not share evenly
+    // leave some idle, and so do, in a launch of one sum, units that do not come
+    // in whole rounds of the resident work groups.  The subset of the digits
+    // left with the largest product of the three shares is taken.  In a batch
+    // many items fill the device; at least 8 units an item and at most 256
+    // positions keep its units even and its tables small (4096 items of 23-24
+    // photons: 29.6, 29.2, 29.3 ms with at most 128, 256, 512).
+    const uint64_t blocks = rest / Q.lane_product * Q.groups;
+    const uint64_t np = (uint64_t)(n_cols + 1) / 2;
+    uint64_t cap = (size_t(1) << 20) / (np * sizeof(double) * 2 * kPairSlots);
+    cap = std::min<uint64_t>(cap, work_groups ? kPairMidMax : kPairMidMax / 2);
+    if (!work_groups) cap = std::min<uint64_t>(cap, std::max<uint64_t>(kPairWaves, blocks / 8));
+    const std::vector<int> left = unused();
+    const std::vector<int64_t> mask = subset_products(left, P.rows, (uint32_t)cap);
+    uint32_t best = 1;
+    double best_score = 0.0;
+    for (uint32_t p = 1; p <= cap; ++p) {
+        if (mask[p] < 0) continue;
+        const double shared = (double)p / (kPairWaves * std::ceil((double)p / kPairWaves));
+        const double started = (double)p * (double)np / ((double)p * (double)np + 120.0);
+        const double units = (double)(blocks / p);
+        const double rounds = work_groups ? units / (work_groups * std::ceil(units / work_groups)) : 1.0;
+        const double score = shared * started * rounds;
+        if (score > best_score) {
+            best_score = score;
+            best = p;
+        }
+    }
+    for (size_t i = 0; i < left.size(); ++i)
+        if (i < 62 && (mask[best] >> i & 1)) {
+            const int k = left[i];
+            Q.rows[(size_t)k].kind = ROW_MID;
+            Q.rows[(size_t)k].stride = Q.mid;
+            Q.mid *= P.rows[(size_t)k].radix;
+            Q.mid_rows.push_back(k);
+            used[(size_t)k] = 1;
+        }
+    uint64_t high = 1;
+    for (int k : unused()) {
+        if (high > 0xFFFFFFFFull) return nullptr;
+        Q.rows[(size_t)k].kind = ROW_HIGH;
+        Q.rows[(size_t)k].stride = (uint32_t)high;
+        high *= P.rows[(size_t)k].radix;
+    }
+    Q.units = high * Q.groups;
+    if (high > 0xFFFFFFFFull || Q.units > 0xFFFFFFF0ull) return nullptr;
+    Q.high = (uint32_t)high;
+    return pp;
+}
+
 int build_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t slots, const PlanParams& pp, HostPlan& P,
                std::string& err, TableCache* cache)
 {

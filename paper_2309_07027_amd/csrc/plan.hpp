@@ -39,6 +39,19 @@ struct TableCache {
     int get(const std::vector<uint32_t>& radix, TablePtr* out, std::string& err);
 };
 
+// Split of one permanent's digits for the pair walk (pair_core.hpp): kinds and
+// strides of the kept rows, in the numbering of its HostPlan.
+struct PairPlan {
+    std::vector<RowInfo> rows;
+    int inner[kPairBits] = {};     // kept rows of the inner binary digits
+    uint32_t lane_product = 1;
+    uint32_t groups = 1;
+    std::vector<int> mid_rows;     // kept rows of the mid digits
+    uint32_t mid = 1;              // positions a work unit walks
+    uint32_t high = 1;
+    uint64_t units = 1;            // groups * high
+};
+
 // Decomposition of one permanent (see walk.hip for how the kernel uses it).
 // Kept rows are numbered low digits first (in low-digit order), then the other
 // rows in input order.
@@ -64,6 +77,7 @@ struct HostPlan {
     int scale_log2 = 0;            // the walk's sum times 2^scale_log2 is the permanent
     std::vector<uint32_t> low_radix;  // radices of the low digits (table key)
     TablePtr table;                // Q entries
+    std::shared_ptr<const PairPlan> pair;  // set when the pair walk evaluates this permanent
     // scratch of one evaluation (run_perms, under the context's lock): the
     // evaluation that last placed this plan's row records, their offset and the
     // device copy of its table, so items sharing the plan find them without a
@@ -79,6 +93,13 @@ struct HostPlan {
 // Tables come from `cache` when given, else are built for this plan.
 int build_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t slots, const PlanParams& pp, HostPlan& out,
                std::string& err, TableCache* cache = nullptr);
+
+// Splits P's digits for the pair walk over n_cols distinct columns, for a launch
+// of this permanent alone on so many resident work groups, or (0) a batched
+// launch, when it has more than min_addends addends.  Returns null where
+// the walk of P itself is the one to use.
+std::shared_ptr<const PairPlan> build_pair_plan(const HostPlan& P, int n_cols, uint32_t work_groups,
+                                                uint64_t min_addends = kPairMinAddends);
 
 // Reflected mixed-radix Gray code (digit 0 fastest): Delta_k at position t.
 void gray_digits(uint64_t t, const uint32_t* radix, int nd, uint32_t* delta);

@@ -213,6 +213,36 @@ int batch_waves(Context& c, int bucket, int kind, int* waves)
     return BBFG_OK;
 }
 
+int pair_occupancy(int np, bool pow, int* groups)
+{
+    const void* fn = pair_walk_fn(pow);
+    const size_t lds = pair_lds_bytes((uint32_t)np);
+    // the largest any launch needs: the attribute belongs to the function
+    BBFG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds_bytes(kPairMax)));
+    int blocks = 0;
+    BBFG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, kWave * kPairWaves, lds));
+    *groups = std::max(1, blocks);
+    return BBFG_OK;
+}
+
+uint32_t pair_table_blocks(uint64_t items, uint64_t positions, uint64_t np)
+{
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024 / items, positions * np / 256));
+}
+
+int pair_groups(Context& c, int np, bool pow, int* groups)
+{
+    const auto key = std::make_pair(np, pow ? 1 : 0);
+    auto it = c.occ_pair.find(key);
+    if (it == c.occ_pair.end()) {
+        int n = 1;
+        BBFG_TRY(pair_occupancy(np, pow, &n));
+        it = c.occ_pair.emplace(key, n).first;
+    }
+    *groups = it->second;
+    return BBFG_OK;
+}
+
 uint64_t batch_unit_length(Context& c, int n, int f32)
 {
     auto it = c.batch_L.find(std::make_pair(n, f32));
@@ -238,7 +268,7 @@ int load_autotune_file(Context& c, const char* path)
 }
 
 int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, int mode,
-             std::shared_ptr<const HostPlan>* out, int kernel_cols, bool ryser)
+             std::shared_ptr<const HostPlan>* out, int kernel_cols, bool ryser, uint64_t pair_min)
 {
     PlanParams pp = c.params;
     pp.ryser = ryser;
@@ -250,6 +280,7 @@ int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, i
     key.push_back(ryser ? 'R' : 'G');
     key.append(reinterpret_cast<const char*>(&pp.l_batch), sizeof pp.l_batch);
     key.append(reinterpret_cast<const char*>(&kernel_cols), sizeof kernel_cols);
+    key.append(reinterpret_cast<const char*>(&pair_min), sizeof pair_min);
     key.append(reinterpret_cast<const char*>(mult), sizeof(int32_t) * (size_t)n_rows);
     auto it = c.plans.find(key);
     if (it != c.plans.end()) {
@@ -281,6 +312,9 @@ int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, i
     std::string err;
     const int rc = build_plan(mult, n_rows, n_cols, slots, pp, *p, err, &c.tables);
     if (rc != BBFG_OK) return set_error(rc, "%s", err.c_str());
+    if (f32 == 0 || f32 == kKindCols)
+        p->pair = build_pair_plan(*p, kernel_cols > 0 ? kernel_cols : n_cols, mode == PLAN_SINGLE ? (uint32_t)c.n_cu : 0u,
+                                  pair_min);
     c.plans.emplace(key, p);
     *out = p;
     return BBFG_OK;
@@ -323,6 +357,37 @@ int flush_plans(Context& c)
 // ---------------------------------------------------------------------------
 // the permanent engine
 // ---------------------------------------------------------------------------
+uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles)
+{
+    const PairPlan& pp = *p.pair;
+    std::memset(&q, 0, sizeof q);
+    q.a_off = d.a_off;
+    q.part_base = d.part_base;
+    q.unit_base = (uint32_t)unit_base;
+    q.units = (uint32_t)pp.units;
+    q.rowinfo_off = d.rowinfo_off;
+    q.lane_product = pp.lane_product;
+    q.mid = pp.mid;
+    q.high = pp.high;
+    q.col_pow = d.col_pow;
+    q.n = d.n;
+    q.np = (d.n + 1) / 2;
+    q.r = d.r;
+    for (int k = 0; k < kPairBits; ++k) q.inner[k] = pp.inner[k];
+    q.mids = (int32_t)pp.mid_rows.size();
+    for (int i = 0; i < q.mids; ++i) q.mid_row[i] = pp.mid_rows[(size_t)i];
+    // 64-byte aligned tables
+    auto take = [table_doubles](uint64_t doubles) {
+        const uint64_t off = *table_doubles;
+        *table_doubles += (doubles + 7) / 8 * 8;
+        return off;
+    };
+    q.mid_off = take((uint64_t)q.mid * (uint64_t)q.np * 2 * kPairSlots);
+    q.weight_off = take(q.mid);
+    q.const_off = take((uint64_t)q.np * 2 * kPairConsts);
+    return q.mid;
+}
+
 int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, bool single, double* out_host,
               double* diag_host, RunResult* rr, bool sync, bool use_graph)
 {
@@ -365,8 +430,28 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     size_t upload_bytes = 0;
     uint64_t a_elems = 0;
     int nmax = 0;
+    // items of the pair walk (their plans hold its split; other launches' plans hold none)
+    auto by_pairs = [&](const PermItem& it) { return !f32 && !minors && it.plan->pair != nullptr; };
+    size_t npair = 0;
+    int np_max = 0;
     for (auto& it : items) {
         const HostPlan* p = it.plan.get();
+        if (by_pairs(it)) {
+            const int nc = cols_of(it);
+            if (p->slot_call != call) {
+                p->slot_call = call;
+                p->slot_rowinfo = n_rowinfo;
+                p->slot_table = nullptr;
+                distinct.push_back(p);
+                n_rowinfo += (size_t)p->r;
+            }
+            n_srcrow += (size_t)p->r;
+            if (it.col_map) n_srccol += (size_t)nc;
+            a_elems += (uint64_t)p->r * (uint64_t)nc;
+            np_max = std::max(np_max, (nc + 1) / 2);
+            ++npair;
+            continue;
+        }
         if (p->slot_call != call) {
             auto te = c.dev_tables.find(p->table.get());
             auto up = uploading.find(p->table.get());
@@ -403,28 +488,42 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         nmax = std::max(nmax, nc);
     }
 
-    // unit numbering: longest units first (items ordered by per-unit cost)
-    std::vector<size_t> order(nitem);
-    std::iota(order.begin(), order.end(), 0);
+    // unit numbering of each launch: longest units first (items ordered by
+    // per-unit cost)
+    const size_t nwalk = nitem - npair;
+    std::vector<size_t> order, order_pair;
+    order.reserve(nwalk);
+    order_pair.reserve(npair);
+    for (size_t i = 0; i < nitem; ++i) (by_pairs(items[i]) ? order_pair : order).push_back(i);
     if (!single) {
         std::vector<double> cost(nitem);
         for (size_t i = 0; i < nitem; ++i) {
             const HostPlan& p = *items[i].plan;
             const double nc = cols_of(items[i]);
-            cost[i] = (double)p.span / (double)p.units_per_group * (6.0 * nc - 2.0 + 12.0 * items[i].targets);
+            if (by_pairs(items[i])) cost[i] = (double)p.pair->mid * nc;
+            else cost[i] = (double)p.span / (double)p.units_per_group * (6.0 * nc - 2.0 + 12.0 * items[i].targets);
         }
-        std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return cost[x] > cost[y]; });
+        auto longer = [&](size_t x, size_t y) { return cost[x] > cost[y]; };
+        std::stable_sort(order.begin(), order.end(), longer);
+        std::stable_sort(order_pair.begin(), order_pair.end(), longer);
     }
+    auto units_of = [&](const PermItem& it) { return by_pairs(it) ? it.plan->pair->units : it.plan->units; };
     std::vector<uint64_t> unit_base(nitem), part_base(nitem);
-    uint64_t total_units = 0, total_parts = 0;
-    for (size_t oi = 0; oi < nitem; ++oi) {
-        const PermItem& it = items[order[oi]];
-        unit_base[order[oi]] = total_units;
-        part_base[order[oi]] = total_parts;
-        total_units += it.plan->units;
-        total_parts += it.plan->units * stride_of(it);
+    uint64_t total_units = 0, pair_units = 0, total_parts = 0;
+    for (size_t i : order) {
+        unit_base[i] = total_units;
+        part_base[i] = total_parts;
+        total_units += items[i].plan->units;
+        total_parts += items[i].plan->units * stride_of(items[i]);
     }
-    if (total_units > 0xFFFFFFF0ull) return set_error(BBFG_ERANGE, "too many work units (%llu)", (unsigned long long)total_units);
+    for (size_t i : order_pair) {
+        unit_base[i] = pair_units;
+        part_base[i] = total_parts;
+        pair_units += items[i].plan->pair->units;
+        total_parts += items[i].plan->pair->units;
+    }
+    if (total_units > 0xFFFFFFF0ull || pair_units > 0xFFFFFFF0ull)
+        return set_error(BBFG_ERANGE, "too many work units (%llu)", (unsigned long long)(total_units + pair_units));
     // results: one per plain item, `targets` per minor item (item order)
     std::vector<uint32_t> res_base(nitem);
     uint64_t nres = 0;
@@ -441,10 +540,12 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     const size_t off_prep = L.add(sizeof(PrepItem) * nitem);
     const size_t off_src = L.add(sizeof(uint32_t) * std::max<size_t>(1, n_srcrow));
     const size_t off_col = L.add(sizeof(uint32_t) * std::max<size_t>(1, n_srccol));
-    const size_t nchunk = single ? 0 : (size_t)((total_units + kUnitChunk - 1) / kUnitChunk);
-    const size_t off_ubase = single ? 0 : L.add(sizeof(uint32_t) * (nitem + 1));
-    const size_t off_uorder = single ? 0 : L.add(sizeof(uint32_t) * nitem);
-    const size_t off_uchunk = single ? 0 : L.add(sizeof(uint32_t) * (nchunk + 1));
+    const size_t nchunk = (size_t)((total_units + kUnitChunk - 1) / kUnitChunk);
+    const bool indexed = !single && nwalk > 0;
+    const size_t off_ubase = indexed ? L.add(sizeof(uint32_t) * (nwalk + 1)) : 0;
+    const size_t off_uorder = indexed ? L.add(sizeof(uint32_t) * nwalk) : 0;
+    const size_t off_uchunk = indexed ? L.add(sizeof(uint32_t) * (nchunk + 1)) : 0;
+    const size_t off_pair = npair ? L.add(sizeof(PairDesc) * npair) : 0;
     const size_t off_ritem = L.add(sizeof(uint32_t) * (size_t)nres);
     const size_t off_tabs = L.add(std::max<size_t>(1, upload_bytes));
     BBFG_TRY(w.hmeta.ensure(L.size));
@@ -456,7 +557,9 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     uint32_t* hs = reinterpret_cast<uint32_t*>(H + off_src);
     uint32_t* hc = reinterpret_cast<uint32_t*>(H + off_col);
     uint32_t* hri = reinterpret_cast<uint32_t*>(H + off_ritem);
-    for (const HostPlan* p : distinct) std::memcpy(hr + p->slot_rowinfo, p->rows.data(), sizeof(RowInfo) * (size_t)p->r);
+    for (const HostPlan* p : distinct)
+        std::memcpy(hr + p->slot_rowinfo, (p->pair && !f32 && !minors ? p->pair->rows : p->rows).data(),
+                    sizeof(RowInfo) * (size_t)p->r);
     for (const Upload& u : uploads) std::memcpy(H + off_tabs + u.off, u.plan->table->data(), u.bytes);
     uint64_t a_cursor = 0;
     size_t s_cursor = 0, c_cursor = 0;
@@ -466,11 +569,12 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         PermDesc& d = hd[i];
         std::memset(&d, 0, sizeof d);
         d.a_off = a_cursor;
+        const bool pair = by_pairs(items[i]);
         d.a2_off = a_cursor + (uint64_t)p.r * nc;
-        a_cursor += (uint64_t)p.r * nc * 3u;
+        a_cursor += (uint64_t)p.r * nc * (pair ? 1u : 3u);
         d.tab = p.slot_table;
         d.unit_base = unit_base[i];
-        d.units = p.units;
+        d.units = units_of(items[i]);
         d.units_per_group = p.units_per_group;
         d.span = p.span;
         d.rowinfo_off = (uint32_t)p.slot_rowinfo;
@@ -498,6 +602,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.n = nc;
         q.r = p.r;
         q.f32 = f32;
+        q.rows_only = pair ? 1 : 0;
         for (int k = 0; k < p.r; ++k) {
             const int ur = p.src_row[(size_t)k];
             hs[s_cursor++] = (uint32_t)(items[i].row_map ? items[i].row_map[ur] : ur);
@@ -509,19 +614,29 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
             q.srccol_off = kIdentityCols;
         }
     }
-    if (!single) {
+    if (indexed) {
         uint32_t* hb = reinterpret_cast<uint32_t*>(H + off_ubase);
         uint32_t* ho = reinterpret_cast<uint32_t*>(H + off_uorder);
         uint32_t* hk = reinterpret_cast<uint32_t*>(H + off_uchunk);
-        for (size_t oi = 0; oi < nitem; ++oi) {
+        for (size_t oi = 0; oi < nwalk; ++oi) {
             const size_t i = order[oi];
             const uint64_t b = unit_base[i], e = b + items[i].plan->units;
             hb[oi] = (uint32_t)b;
             ho[oi] = (uint32_t)i;
             for (uint64_t c = (b + kUnitChunk - 1) / kUnitChunk; c * kUnitChunk < e; ++c) hk[c] = (uint32_t)oi;
         }
-        hb[nitem] = (uint32_t)total_units;
-        hk[nchunk] = (uint32_t)(nitem - 1);
+        hb[nwalk] = (uint32_t)total_units;
+        hk[nchunk] = (uint32_t)(nwalk - 1);
+    }
+    uint64_t table_doubles = 0, unit_map = 0, mid_max = 0;
+    if (npair) {
+        PairDesc* hpd = reinterpret_cast<PairDesc*>(H + off_pair);
+        for (size_t oi = 0; oi < npair; ++oi)
+            mid_max = std::max(mid_max, fill_pair_desc(hpd[oi], hd[order_pair[oi]], *items[order_pair[oi]].plan,
+                                                       unit_base[order_pair[oi]], &table_doubles));
+        unit_map = table_doubles;  // the units' items follow the tables
+        if (npair > 1) table_doubles += (pair_units + 1) / 2;
+        BBFG_TRY(w.pair_tables.ensure(sizeof(double) * table_doubles));
     }
 
     // device buffers
@@ -542,16 +657,35 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     W.a2f = w.arena_f.as<float>();
     W.binom = c.binom;
     W.partials = w.partials.as<double>();
-    W.ubase = single ? nullptr : reinterpret_cast<const uint32_t*>(D + off_ubase);
-    W.uorder = single ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uorder);
-    W.uchunk = single ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uchunk);
+    W.ubase = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_ubase);
+    W.uorder = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uorder);
+    W.uchunk = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uchunk);
     W.nitem = (uint32_t)nitem;
     W.counter = w.counter.as<uint32_t>();
     W.total_units = (uint32_t)total_units;
 
+    PairArgs PA;
+    std::memset(&PA, 0, sizeof PA);
+    uint64_t pair_grid = 0;
+    if (npair) {
+        PA.descs = reinterpret_cast<const PairDesc*>(D + off_pair);
+        PA.rowinfo = W.rowinfo;
+        PA.a = W.a;
+        PA.tables = w.pair_tables.as<double>();
+        PA.binom = c.binom;
+        PA.partials = W.partials;
+        PA.unit_item = npair > 1 ? reinterpret_cast<uint32_t*>(PA.tables + unit_map) : nullptr;
+        PA.counter = W.counter + kCounterStride;
+        PA.total_units = (uint32_t)pair_units;
+        PA.np_max = (uint32_t)np_max;
+        int groups = 1;
+        BBFG_TRY(pair_groups(c, np_max, powcols, &groups));
+        pair_grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, pair_units);
+    }
+    const uint32_t table_blocks = npair ? pair_table_blocks(npair, mid_max, (uint64_t)np_max) : 0;
     int bucket = 0;
     uint64_t grid = total_units;
-    if (!single) {
+    if (!single && nwalk) {
         bucket = minors ? minors_bucket_max(nmax) : batch_bucket_max(nmax, f32);
         if (bucket < 0) return set_error(BBFG_ERANGE, "no batch kernel for n=%d", nmax);
         int waves = 1;
@@ -570,9 +704,12 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
                              reinterpret_cast<const uint32_t*>(D + off_src),
                              reinterpret_cast<const uint32_t*>(D + off_col), w.arena_d.as<double>(),
                              w.arena_d.as<double>(), w.arena_f.as<float>(), w.arena_f.as<float>()));
-        if (!single) BBFG_HIP(launch_reset_counter(W.counter, q));
+        if (!single || npair) BBFG_HIP(launch_reset_counter(W.counter, q));
+        if (npair) BBFG_HIP(launch_pair_tables((uint32_t)npair, table_blocks, q, PA));
         if (timed) BBFG_HIP(hipEventRecord(w.ev0, q));
-        if (single) BBFG_HIP(launch_walk_single(items[0].plan->n, f32, (uint32_t)total_units, q, W, 0u));
+        if (npair) BBFG_HIP(launch_pair_walk(powcols, (uint32_t)pair_grid, q, PA));
+        if (!nwalk) {
+        } else if (single) BBFG_HIP(launch_walk_single(items[0].plan->n, f32, (uint32_t)total_units, q, W, 0u));
         else if (minors) BBFG_HIP(launch_walk_minors(bucket, (uint32_t)grid, q, W));
         else if (powcols) BBFG_HIP(launch_walk_cols(bucket, (uint32_t)grid, q, W));
         else BBFG_HIP(launch_walk_batch(bucket, f32, (uint32_t)grid, q, W));
@@ -618,10 +755,12 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
             for (size_t i = 0; i < n; ++i) key = (key ^ b[i]) * 1099511628211ull;
         };
         mix(&W, sizeof W);
+        mix(&PA, sizeof PA);
         const uint64_t extra[] = {nitem, nres, (uint64_t)single, (uint64_t)minors, (uint64_t)powcols, (uint64_t)f32,
                                   (uint64_t)bucket,
-                                  grid, L.size, off_desc, off_row, off_prep, off_src, off_col, off_ubase, off_uorder,
-                                  off_uchunk, off_ritem, off_tabs,
+                                  grid, L.size, off_desc, off_row, off_prep, off_src, off_col, off_ubase, off_uorder, off_uchunk,
+                                  off_pair, off_ritem, off_tabs,
+                                  npair, pair_grid, (uint64_t)table_blocks,
                                   (uint64_t)(uintptr_t)H, (uint64_t)(uintptr_t)D, (uint64_t)(uintptr_t)R,
                                   (uint64_t)(uintptr_t)HR, (uint64_t)(uintptr_t)w.arena_d.p,
                                   (uint64_t)(uintptr_t)w.arena_f.p};
@@ -658,7 +797,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         }
     }
     if (!launched) BBFG_TRY(enqueue(s, true));
-    if (rr) rr->units = total_units;
+    if (rr) rr->units = total_units + pair_units;
     if (!sync) return BBFG_OK;
     BBFG_HIP(hipStreamSynchronize(s));
     if (out_host) std::memcpy(out_host, HR, sizeof(double) * 2 * nres);
@@ -667,7 +806,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         float ms = 0.f;
         BBFG_HIP(hipEventElapsedTime(&ms, w.ev0, w.ev1));
         rr->kernel_ms = ms;
-        rr->units = total_units;
+        rr->units = total_units + pair_units;
     }
     return BBFG_OK;
 }

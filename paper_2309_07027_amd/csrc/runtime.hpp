@@ -102,7 +102,7 @@ struct Layout {
 // workspace holds one evaluation at a time (the device context has one, the
 // sampling server two, so that it can prepare one step while another runs).
 struct Workspace {
-    DevBuf arena_d, arena_f, meta, partials, results, counter, cc_meta;
+    DevBuf arena_d, arena_f, meta, partials, results, counter, cc_meta, pair_tables;
     PinnedBuf hmeta, hres, cc_hmeta;
     hipEvent_t ev0 = nullptr, ev1 = nullptr, done = nullptr;
     Workspace() = default;
@@ -136,6 +136,7 @@ struct Context {
     Workspace ws;
     std::map<std::pair<int, int>, int> occ_single;  // (n, f32) -> waves per CU
     std::map<std::pair<int, int>, int> occ_batch;   // (bucket, kind) -> waves per CU
+    std::map<std::pair<int, int>, int> occ_pair;    // (pairs of columns, pow) -> work groups per CU
     std::unordered_map<std::string, std::shared_ptr<const HostPlan>> plans;
     // Gray tables shared between plans (host), and their device copies:
     // bump-allocated in chunks that are never moved while referenced
@@ -186,15 +187,22 @@ int walk_slots(Context& c, int n, int f32, uint64_t* slots);
 constexpr int kKindMinors = 2;
 constexpr int kKindCols = 3;  // uniform column multiplicities
 int batch_waves(Context& c, int bucket, int kind, int* waves);
+// Resident work groups per CU of the pair walk with np pairs of columns.
+int pair_groups(Context& c, int np, bool pow, int* groups);
+int pair_occupancy(int np, bool pow, int* groups);  // the same, asked of the device
+// Blocks over an item's pair-walk tables: many for a lone item, one for each of many.
+uint32_t pair_table_blocks(uint64_t items, uint64_t positions, uint64_t np);
 // kind = 0 (FP64), 1 (FP32) or BBFG_MINORS: selects the tuned unit length of
 // PLAN_BATCH plans (plans of different kinds are cached separately).
 // PLAN_SINGLE plans fill the resident wavefronts of the kernel that runs them:
 // the plain walk for n_cols columns, the minors kernel for n_cols + 1 columns
 // (kind kKindMinors), or the column-power kernel for kernel_cols distinct
 // columns (kind kKindCols).
+// pair_min: the pair walk evaluates sums of more than this many addends.
 // ryser: the plan of Eq. ryser with row multiplicities (no pivot, base 0).
 int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int kind, int mode,
-             std::shared_ptr<const HostPlan>* out, int kernel_cols = 0, bool ryser = false);
+             std::shared_ptr<const HostPlan>* out, int kernel_cols = 0, bool ryser = false,
+             uint64_t pair_min = kPairMinAddends);
 // Pool space for a device table of `bytes` bytes (resident until a flush).
 int table_reserve(Context& c, size_t bytes, TabEntry** out);
 // Caches are bounded (Context::plan_cap, Context::table_entry_cap): past these
@@ -238,6 +246,11 @@ struct RunResult {
     uint64_t units = 0;
     bool graph = false;      // evaluated by replaying a captured graph
 };
+
+// Fills q from its permanent's descriptor d (complete but for its walk fields)
+// and plan, and places its tables at the end of a buffer of *table_doubles
+// doubles.  Returns its mid positions.
+uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles);
 
 // Evaluates items (all n >= 1).  The (re, im) results stay in c.results (item
 // order; an item with targets = G has G consecutive results) and, when out_host

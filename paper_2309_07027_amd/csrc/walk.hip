@@ -75,6 +75,7 @@ __global__ void prep_rows_kernel(const PrepItem* __restrict__ items, const uint3
         } else {
             a[2 * da] = xr;
             a[2 * da + 1] = xi;
+            if (it.rows_only) continue;
             a2[2 * dp] = 2.0 * xr;
             a2[2 * dp + 1] = 2.0 * xi;
             a2[2 * dm] = -2.0 * xr;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kWave) void walk_single_kernel(WalkArgs A, uint32_t
 
 __global__ void reset_counter_kernel(uint32_t* counter)
 {
-    if (threadIdx.x == 0) *counter = 0u;
+    if (threadIdx.x < kCounters) counter[threadIdx.x * kCounterStride] = 0u;
 }
 
 // ---------------------------------------------------------------------------
