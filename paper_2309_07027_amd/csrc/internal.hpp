@@ -129,6 +129,7 @@ struct PrepItem {
     int32_t r;
     int32_t f32;
     int32_t rows_only;  // no +-2a rows
+    int32_t np;         // > 0: the layout of the leave-one-column-out walk over pairs, np pairs a wavefront
 };
 
 // ---------------------------------------------------------------------------
@@ -173,6 +174,30 @@ struct PairDesc {
     int32_t mids;              // mid digits and their kept rows
     int32_t mid_row[kPairMids];
 };
+
+// ---------------------------------------------------------------------------
+// leave-one-column-out walk over pairs (minor_pairs_core.hpp)
+// ---------------------------------------------------------------------------
+constexpr int kMinorWaves = 4;                // wavefronts that share a walk's columns
+constexpr int kMinorMinPairs = 2;             // pairs of a wavefront, at least
+constexpr int kMinorMinCols = 9;              // fewest columns it is used for
+// It takes sums of more addends than this in a sampler step (16 samples of 20
+// photons: 1.57, 1.59, 1.78, 2.02 ms with 2^6, 2^8, 2^10, 2^12; without it 2.9
+// ms) and in a lone call (where the walk of shorter sums stays the one whose
+// bits the CPU emulation of walk_core.hpp pins; 24 columns, 2^22 addends: 0.193
+// -> 0.089 ms).
+constexpr uint64_t kMinorMinAddendsBatch = uint64_t(1) << 6;
+constexpr uint64_t kMinorMinAddends = uint64_t(1) << 17;
+// An item of a sampler step is split into about so many units, down to units of
+// so many steps of two addends (30 photons: 11.4 ms with 128 units, 12.0 with
+// 32, 12.5 with 16; 24 jobs on the server: 52.5, 51.4, 51.1 ms).
+constexpr uint64_t kMinorItemUnits = 64;
+constexpr uint64_t kMinorMinUnit = 16;
+constexpr int minor_pairs_per_wave(int K)
+{
+    const int np = ((K + 1) / 2 + kMinorWaves - 1) / kMinorWaves;
+    return np > kMinorMinPairs ? np : kMinorMinPairs;
+}
 
 // Kernel arguments of the pair walk (passed by value).
 struct PairArgs {

@@ -32,6 +32,12 @@ const void* walk_minors_fn_b32();
 const void* walk_minors_fn_b48();
 hipError_t launch_walk_minors(int bucket, uint32_t grid, hipStream_t s, const WalkArgs& A);
 hipError_t launch_reset_counter(uint32_t* counter, hipStream_t s);
+// leave-one-column-out walk over pairs, np pairs of columns a wavefront at most
+const void* minor_pairs_fn(int np);
+const void* minor_pairs_fn_b3();
+const void* minor_pairs_fn_b4();
+const void* minor_pairs_fn_b6();
+hipError_t launch_minor_pairs(int np, uint32_t grid, hipStream_t s, const WalkArgs& A);
 // pair walk (walk_pairs.hip): tables of the items, then the walk; pow: items with
 // col_pow >= 2
 const void* pair_walk_fn(bool pow);

@@ -1,0 +1,208 @@
+// minor_pairs.hpp -- gfx950 kernel of the leave-one-column-out walk over pairs
+// of columns (minor_pairs_core.hpp), one translation unit per bucket.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "internal.hpp"
+#include "minor_pairs_core.hpp"
+#include "walk_device.hpp"
+
+namespace bbfg {
+
+constexpr int kMinorThreads = kWave * kMinorWaves;
+
+struct MinorShared {
+    cpx prod[2][kMinorWaves][2][kWave];    // the wavefronts' products, two steps deep
+    double mag[kMinorWaves][kWave];        // the wavefronts' moduli at a sampled position
+    double weight[kMinorWaves][kWave];     // the wavefronts' shares of the lane weights
+    int8_t coef[kMaxN][kWave];
+    uint32_t next_unit;
+};
+
+// Coefficients of the kept rows at (block h, position t) into S.coef, each
+// wavefront a share of the rows; returns the lane's weight over its lane and
+// high digits (zero for idle lanes).
+__device__ __forceinline__ double minor_coefs(const WalkArgs& A, const PermDesc& d, MinorShared& S, uint32_t lane,
+                                              uint32_t wave, uint32_t lane_idx, bool valid, uint64_t h, uint32_t t)
+{
+    kptr<RowInfo> ri = kconst(A.rowinfo + d.rowinfo_off);
+    double w = valid ? 1.0 : 0.0;
+    for (int k = (int)wave; k < d.r; k += kMinorWaves) {
+        RowInfo x;
+        x.base = ri[k].base;
+        x.kind = ri[k].kind;
+        x.radix = ri[k].radix;
+        x.stride = ri[k].stride;
+        x.mp = ri[k].mp;
+        uint32_t delta = 0;
+        if (x.kind == ROW_LANE) {
+            delta = (lane_idx / x.stride) % x.radix;
+        } else if (x.kind == ROW_HIGH) {
+            delta = digit_of(h, x.stride, x.radix);
+        } else if (x.kind == ROW_LOW) {
+            const uint32_t dg = (t / x.stride) % x.radix;
+            const uint32_t q = t / (x.stride * x.radix);
+            delta = (q & 1u) ? (x.radix - 1u - dg) : dg;
+        }
+        const int c = x.base - 2 * (int)delta;
+        S.coef[k][lane] = (int8_t)c;
+        w *= pair_row_weight(x, A.binom, c);
+    }
+    S.weight[wave][lane] = w;
+    __syncthreads();
+    w = S.weight[0][lane];
+#pragma unroll
+    for (int v = 1; v < kMinorWaves; ++v) w *= S.weight[v][lane];
+    return w;
+}
+
+// One unit: the sums of this wavefront's 2 NP targets over the unit's addends,
+// then, for sampled units, the estimate of their magnitude sums (the modulus of
+// the addend at the unit's last position, the inner digit at the lane's parity,
+// times the addends it stands for).
+template <int NP>
+__device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S)
+{
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = uniform_u32(threadIdx.x / kWave);
+    const uint32_t upg = (uint32_t)d.units_per_group;
+    const uint32_t g = u_local / upg;
+    const uint32_t part = u_local - g * upg;
+    const uint64_t base = d.span / upg;
+    const uint32_t rem = (uint32_t)(d.span - base * upg);
+    const uint64_t lin0 = (uint64_t)part * base + (part < rem ? part : rem);
+    const uint64_t lin1 = lin0 + base + (part < rem ? 1u : 0u);
+    uint32_t lane_idx = g * kWave + lane;
+    const bool valid = lane_idx < d.lane_product;
+    if (!valid) lane_idx = 0;
+
+    constexpr int kCols = 2 * NP;
+    const size_t ld = 4 * (size_t)NP * kMinorWaves;                 // doubles per kept row
+    const size_t step_ld = 6 * (size_t)NP * kMinorWaves;            // doubles per step row
+    kptr<double> a = kconst(A.a + 2 * d.a_off + wave * (4 * NP));
+    kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + wave * (6 * NP));
+    kptr<TabEntry> tab = kconst(d.tab);
+    const int cols = (int)d.n - (int)wave * kCols;                  // real columns of this wavefront (may be < 0)
+    const uint32_t Q = d.Q;
+    auto coef = [&](int k) { return (double)S.coef[k][lane]; };
+
+    MinorLane<NP> L;
+    L.clear();
+    uint32_t buf = 0;
+    for (uint64_t lin = lin0; lin < lin1;) {
+        const uint64_t h = lin / Q;
+        const uint32_t t0 = (uint32_t)(lin - h * Q);
+        const uint64_t bend = (h + 1) * (uint64_t)Q;
+        const uint32_t t1 = (uint32_t)(((lin1 < bend) ? lin1 : bend) - h * Q);
+        const double w = minor_coefs(A, d, S, lane, wave, lane_idx, valid, h, t0);
+        L.seed(a, ld, d.r, cols, coef);
+        double ws = w * tab[t0].s;
+        uint32_t next_row = t0 + 1 < t1 ? uniform_u32(tab[t0 + 1].row) : 0u;
+        for (uint32_t t = t0; t < t1; ++t) {
+            L.forward();
+            S.prod[buf][wave][0][lane] = L.half[0].all;
+            S.prod[buf][wave][1][lane] = L.half[1].all;
+            __syncthreads();
+            const cpx(*const o0)[2][kWave] = &S.prod[buf][(wave + 1) % kMinorWaves];
+            const cpx(*const o1)[2][kWave] = &S.prod[buf][(wave + 2) % kMinorWaves];
+            const cpx(*const o2)[2][kWave] = &S.prod[buf][(wave + 3) % kMinorWaves];
+            const cpx e0 = cmul_uniform(cmul(cmul((*o0)[0][lane], (*o1)[0][lane]), (*o2)[0][lane]), ws);
+            const cpx e1 = cmul_uniform(cmul(cmul((*o0)[1][lane], (*o1)[1][lane]), (*o2)[1][lane]), ws);
+            // the next step's changes are fetched under the rest of this step (not
+            // earlier: a wait for LDS data waits for scalar loads as well); after
+            // the last step they are row 0's, and go into sums that are seeded anew
+            BBFG_SCHED_BARRIER();
+            double s[6 * NP];
+            kptr<double> row = steps + (size_t)next_row * step_ld;
+#pragma unroll
+            for (int i = 0; i < 6 * NP; ++i) s[i] = row[i];
+            ws = w * tab[t + 1 < t1 ? t + 1 : t].s;
+            next_row = uniform_u32(tab[t + 2 < t1 ? t + 2 : t].row);
+            BBFG_SCHED_BARRIER();
+            L.backward(e0, e1);
+            L.advance(s);
+            buf ^= 1u;
+        }
+        lin += (uint64_t)(t1 - t0);
+        __syncthreads();  // the coefficients and weights may be overwritten
+    }
+    kptr<double> inner = a + (int64_t)((size_t)(d.r - 1) * ld);
+    const uint64_t slot = d.part_base + (uint64_t)u_local * d.targets + wave * kCols;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        cpx first, second;
+        L.result(p, inner, first, second);
+        if (2 * p < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p, first.r, first.i);
+        if (2 * p + 1 < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p + 1, second.r, second.i);
+    }
+    const uint32_t every = d.mag_every;
+    if (part % every != 0) {
+#pragma unroll
+        for (int j = 0; j < kCols; ++j)
+            if (j < cols) A.partials[(slot + j) * kPartialDoubles + 4] = 0.0;
+        return;
+    }
+    const uint32_t reps = (upg - part < every) ? upg - part : every;
+    const uint64_t hl = (lin1 - 1) / Q;
+    const uint32_t tl = (uint32_t)(lin1 - 1 - hl * Q);
+    const double w = minor_coefs(A, d, S, lane, wave, lane_idx, valid, hl, tl);
+    L.seed(a, ld, d.r, cols, coef);
+    // moduli of the column sums, and their product
+    double mod[kCols], own = 1.0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const double x = (lane & 1u) ? -2.0 : 0.0;
+        const cpx c1 = {fmar(x, inner[4 * p], L.b1[p].r), fmar(x, inner[4 * p + 1], L.b1[p].i)};
+        const cpx c2 = {fmar(x, inner[4 * p + 2], L.b2[p].r), fmar(x, inner[4 * p + 3], L.b2[p].i)};
+        mod[2 * p] = __builtin_sqrt(fmar(c1.r, c1.r, c1.i * c1.i));
+        mod[2 * p + 1] = __builtin_sqrt(fmar(c2.r, c2.r, c2.i * c2.i));
+        own *= mod[2 * p] * mod[2 * p + 1];
+    }
+    S.mag[wave][lane] = own;
+    __syncthreads();
+    double lead = 2.0 * (double)(lin1 - lin0) * (double)reps * __builtin_fabs(w * tab[tl].s);
+#pragma unroll
+    for (int v = 1; v < kMinorWaves; ++v) lead *= S.mag[(wave + v) % kMinorWaves][lane];
+    // leave-one-out products: no division, so zero moduli are harmless
+    double pre[kCols];
+    pre[0] = lead;
+#pragma unroll
+    for (int j = 1; j < kCols; ++j) pre[j] = pre[j - 1] * mod[j - 1];
+    double suffix = 1.0;
+#pragma unroll
+    for (int j = kCols - 1; j >= 0; --j) {
+        if (j < cols) store_partial_mag_all_lanes(A.partials, slot + j, pre[j] * suffix);
+        suffix *= mod[j];
+    }
+}
+
+template <int NPMIN, int NPMAX>
+__device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S)
+{
+    if constexpr (NPMIN <= NPMAX) {
+        if (minor_pairs_per_wave(d.n) == NPMIN) minor_pairs_unit<NPMIN>(A, d, u, S);
+        else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S);
+    }
+}
+
+// Persistent work groups of four wavefronts pull units from a counter.
+template <int NPMAX>
+__global__ __launch_bounds__(kMinorThreads) __attribute__((amdgpu_waves_per_eu(NPMAX <= 3 ? 3 : 2))) void minor_pairs_kernel(WalkArgs A)
+{
+    __shared__ MinorShared S;
+    for (;;) {
+        if (threadIdx.x == 0) S.next_unit = atomicAdd(A.counter, 1u);
+        __syncthreads();
+        const uint32_t u = uniform_u32(S.next_unit);
+        __syncthreads();
+        if (u >= A.total_units) break;
+        const uint32_t item = item_of_unit(A, u);
+        const PermDesc d = A.descs[item];
+        dispatch_minor_pairs<kMinorMinPairs, NPMAX>(A, d, u - (uint32_t)d.unit_base, S);
+    }
+}
+
+}  // namespace bbfg

@@ -1,0 +1,171 @@
+// minor_pairs_core.hpp -- per-lane core of the leave-one-column-out walk over
+// pairs of columns (the Laplace minors of the Clifford & Clifford step, Sec. 4,
+// with Eq. bbfgrepeated; arXiv:2309.07027).
+//
+// Four wavefronts share the addends; each owns NP pairs of columns.  With
+// Z_p = w prod_{p' != p} c_1 c_2 (pair p'), the minors without the columns of
+// pair p are sum Z_p c_2 and sum Z_p c_1.  Per addend a wavefront forms its
+// pairs' products, hands their product to the other three through LDS, and gets
+// the Z_p of its pairs from the other three products and its own.
+//
+// One binary digit x is taken two addends at a time.  A pair's product is
+// c_1 c_2 = y + x D with D linear in the sign counts of the other rows, so the
+// second addend's costs one complex addition, and with c_2 = b_2 + x d_2
+//   sum_x Z c_2 = b_2 sum_x Z + d_2 Z(1):
+// the multiply-accumulates with the column sums are shared by the two addends,
+// and the d terms are added once at a unit's end.
+//
+// Bound by FP64 issue: 23.6 FP64 instructions per pair and addend (189 a step
+// of two addends and four pairs, 11 other vector ones) and about 40 registers
+// per pair, so up to 40 columns fit two wavefronts per SIMD without spills or
+// accumulation registers (up to 24 columns three).  One wavefront for all
+// columns, walk_minors_unit, issues 38 a pair and addend at 30 columns and 54
+// at 36, where half are register moves.  Measured (kernel): 24 columns, 2^22
+// addends, 0.193 -> 0.089 ms; 30 columns, 2^28, 4.96 -> 3.51 ms; 35 columns, 34
+// photons at random, 12.5 -> 7.2 ms.
+//
+// Compiled by hipcc for the kernel and by a host compiler for the CPU emulation.
+#pragma once
+
+#include "pair_core.hpp"
+
+namespace bbfg {
+
+// acc + a b
+BBFG_FN void cmac(cpx& acc, cpx a, cpx b) { acc = cfma(a, b, acc); }
+BBFG_FN cpx cmul_uniform(cpx a, double s) { return {a.r * s, a.i * s}; }
+
+template <int NP>
+struct MinorLane {
+    cpx b1[NP], b2[NP], D[NP];         // column sums at x = 0, difference of the product
+    cpx y[NP];                         // product at x = 0
+    cpx acc1[NP], acc2[NP], G[NP];     // sums of Z c_2, Z c_1 and -Z(1)
+
+    // products over neighbouring pairs at one x
+    static constexpr int H = (NP + 1) / 2;
+    struct Half {
+        cpx m[H];                      // of pairs 2i, 2i + 1
+        cpx all;
+    } half[2];
+
+    BBFG_FN void clear()
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) acc1[p] = acc2[p] = G[p] = {0.0, 0.0};
+    }
+
+    // Column sums at one position: coef(k) is kept row k's coefficient, a points
+    // at this wavefront's columns of row 0 (rows `ld` doubles apart, columns past
+    // the matrix zero; `cols` of the wavefront's 2 NP columns are real).  The last
+    // kept row is the inner digit's, at coefficient +1.
+    template <typename Coef>
+    BBFG_FN void seed(kptr<double> a, size_t ld, int r, int cols, Coef coef)
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            b1[p] = {2 * p < cols ? 0.0 : 1.0, 0.0};
+            b2[p] = {2 * p + 1 < cols ? 0.0 : 1.0, 0.0};
+        }
+        kptr<double> row = a;
+        for (int k = 0; k < r; ++k) {
+            const double c = coef(k);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                b1[p] = {fmar(c, row[4 * p], b1[p].r), fmar(c, row[4 * p + 1], b1[p].i)};
+                b2[p] = {fmar(c, row[4 * p + 2], b2[p].r), fmar(c, row[4 * p + 3], b2[p].i)};
+            }
+            if (k + 1 < r) row = row + (int64_t)ld;
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const cpx d1 = {-2.0 * row[4 * p], -2.0 * row[4 * p + 1]};
+            const cpx d2 = {-2.0 * row[4 * p + 2], -2.0 * row[4 * p + 3]};
+            D[p] = cfma(d1, b2[p], cfma(d2, b1[p], cmul(d1, d2)));
+        }
+    }
+
+    // One step of the Gray walk: s holds per pair the change of b_1, b_2 and D.
+    BBFG_FN void advance(const double* s)
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            b1[p] = cadd(b1[p], s + 6 * p);
+            b2[p] = cadd(b2[p], s + 6 * p + 2);
+            D[p] = cadd(D[p], s + 6 * p + 4);
+        }
+    }
+
+    BBFG_FN cpx value(int p, int x) const { return x ? cadd(y[p], D[p]) : y[p]; }
+
+    // This wavefront's product at both x.
+    BBFG_FN void forward()
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) y[p] = cmul(b1[p], b2[p]);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+#pragma unroll
+            for (int i = 0; i < H; ++i)
+                half[x].m[i] = 2 * i + 1 < NP ? cmul(value(2 * i, x), value(2 * i + 1 < NP ? 2 * i + 1 : 0, x))
+                                              : value(2 * i, x);
+            half[x].all = half[x].m[0];
+#pragma unroll
+            for (int i = 1; i < H; ++i) half[x].all = cmul(half[x].all, half[x].m[i]);
+        }
+    }
+
+    // z[p] = e prod of the other pairs' products at x
+    BBFG_FN void others(int x, cpx e, cpx* z) const
+    {
+        const Half& h = half[x];
+        cpx eh[H];  // e times the products of the other neighbour pairs
+        if constexpr (H == 1) {
+            eh[0] = e;
+        } else if constexpr (H == 2) {
+            eh[0] = cmul(e, h.m[1]);
+            eh[1] = cmul(e, h.m[0]);
+        } else {
+            const cpx t = cmul(e, h.m[2]);
+            eh[0] = cmul(t, h.m[1]);
+            eh[1] = cmul(t, h.m[0]);
+            eh[2] = cmul(e, cmul(h.m[0], h.m[1]));
+        }
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            if (2 * i + 1 < NP) {
+                z[2 * i] = cmul(eh[i], value(2 * i + 1 < NP ? 2 * i + 1 : 0, x));
+                z[2 * i + 1 < NP ? 2 * i + 1 : 0] = cmul(eh[i], value(2 * i, x));
+            } else {
+                z[2 * i] = eh[i];
+            }
+        }
+    }
+
+    // Accumulates both addends; e0, e1: the weight times the other wavefronts'
+    // products (the digit x enters with sign (-1)^x).
+    BBFG_FN void backward(cpx e0, cpx e1)
+    {
+        cpx z0[NP], z1[NP];
+        others(0, e0, z0);
+        others(1, e1, z1);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const cpx s = {z0[p].r - z1[p].r, z0[p].i - z1[p].i};
+            G[p] = {G[p].r - z1[p].r, G[p].i - z1[p].i};
+            cmac(acc1[p], s, b2[p]);
+            cmac(acc2[p], s, b1[p]);
+        }
+    }
+
+    // The sums over the walked addends of the minors without columns 2p, 2p + 1;
+    // inner points at the inner digit's row.
+    BBFG_FN void result(int p, kptr<double> inner, cpx& first, cpx& second) const
+    {
+        const cpx d1 = {-2.0 * inner[4 * p], -2.0 * inner[4 * p + 1]};
+        const cpx d2 = {-2.0 * inner[4 * p + 2], -2.0 * inner[4 * p + 3]};
+        first = cfma(d2, G[p], acc1[p]);
+        second = cfma(d1, G[p], acc2[p]);
+    }
+};
+
+}  // namespace bbfg

@@ -43,7 +43,7 @@
 
 namespace bbfg {
 
-struct cpx {
+struct alignas(16) cpx {
     double r, i;
 };
 

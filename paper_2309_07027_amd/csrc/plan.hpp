@@ -77,6 +77,8 @@ struct HostPlan {
     int scale_log2 = 0;            // the walk's sum times 2^scale_log2 is the permanent
     std::vector<uint32_t> low_radix;  // radices of the low digits (table key)
     TablePtr table;                // Q entries
+    bool minor_pairs = false;  // leave-one-column-out walk over pairs: the last kept row is its inner binary
+                               // digit (kind FIXED), the other fields split the sum over the other digits
     std::shared_ptr<const PairPlan> pair;  // set when the pair walk evaluates this permanent
     // scratch of one evaluation (run_perms, under the context's lock): the
     // evaluation that last placed this plan's row records, their offset and the
@@ -93,6 +95,12 @@ struct HostPlan {
 // Tables come from `cache` when given, else are built for this plan.
 int build_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t slots, const PlanParams& pp, HostPlan& out,
                std::string& err, TableCache* cache = nullptr);
+
+// Plans the leave-one-column-out walk over pairs of the n_cols + 1 columns of
+// rows `mult` (sum n_cols), as build_plan does the other one (slots: resident
+// work groups).  Returns false, with err empty, where that one is to be used.
+bool build_minor_pair_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t slots, const PlanParams& pp,
+                           HostPlan& out, std::string& err, TableCache* cache = nullptr);
 
 // Splits P's digits for the pair walk over n_cols distinct columns, for a launch
 // of this permanent alone on so many resident work groups, or (0) a batched

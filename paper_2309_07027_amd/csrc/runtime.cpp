@@ -243,6 +243,19 @@ int pair_groups(Context& c, int np, bool pow, int* groups)
     return BBFG_OK;
 }
 
+int minor_groups(Context& c, int np, int* groups)
+{
+    const auto key = std::make_pair(-np, 0);
+    auto it = c.occ_pair.find(key);
+    if (it == c.occ_pair.end()) {
+        int blocks = 0;
+        BBFG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, minor_pairs_fn(np), kWave * kMinorWaves, 0));
+        it = c.occ_pair.emplace(key, std::max(1, blocks)).first;
+    }
+    *groups = it->second;
+    return BBFG_OK;
+}
+
 uint64_t batch_unit_length(Context& c, int n, int f32)
 {
     auto it = c.batch_L.find(std::make_pair(n, f32));
@@ -310,6 +323,20 @@ int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, i
     if (c.tables.entries > c.table_entry_cap || c.plans.size() >= c.plan_cap) BBFG_TRY(flush_plans(c));
     auto p = std::make_shared<HostPlan>();
     std::string err;
+    if (f32 == kKindMinors) {
+        uint64_t groups = 1;
+        if (mode == PLAN_SINGLE) {
+            int per_cu = 1;
+            BBFG_TRY(minor_groups(c, minor_pairs_per_wave(n_cols + 1), &per_cu));
+            groups = (uint64_t)per_cu * (uint64_t)c.n_cu;
+        }
+        if (build_minor_pair_plan(mult, n_rows, n_cols, groups, pp, *p, err, &c.tables)) {
+            c.plans.emplace(key, p);
+            *out = p;
+            return BBFG_OK;
+        }
+        if (!err.empty()) return set_error(BBFG_ERANGE, "%s", err.c_str());
+    }
     const int rc = build_plan(mult, n_rows, n_cols, slots, pp, *p, err, &c.tables);
     if (rc != BBFG_OK) return set_error(rc, "%s", err.c_str());
     if (f32 == 0 || f32 == kKindCols)
@@ -430,13 +457,26 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     size_t upload_bytes = 0;
     uint64_t a_elems = 0;
     int nmax = 0;
-    // items of the pair walk (their plans hold its split; other launches' plans hold none)
-    auto by_pairs = [&](const PermItem& it) { return !f32 && !minors && it.plan->pair != nullptr; };
+    // items that go over pairs of columns have a launch of their own: the pair
+    // walk (plans that hold its split) or the leave-one-column-out walk over pairs
+    auto by_pairs = [&](const PermItem& it) { return minors ? it.plan->minor_pairs : !f32 && it.plan->pair != nullptr; };
+    auto arena_of = [&](const PermItem& it, int nc) -> uint64_t {
+        const uint64_t rows = (uint64_t)it.plan->r;
+        if (!by_pairs(it)) return rows * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
+        if (!minors) return rows * (uint64_t)nc;
+        const uint64_t pairs = (uint64_t)minor_pairs_per_wave(nc) * kMinorWaves;
+        return rows * 2 * pairs + 2 * (rows - 1) * 3 * pairs;
+    };
     size_t npair = 0;
     int np_max = 0;
     for (auto& it : items) {
         const HostPlan* p = it.plan.get();
         if (by_pairs(it)) {
+            const int nc = cols_of(it);
+            ++npair;
+            np_max = std::max(np_max, minors ? minor_pairs_per_wave(nc) : (nc + 1) / 2);
+        }
+        if (by_pairs(it) && !minors) {
             const int nc = cols_of(it);
             if (p->slot_call != call) {
                 p->slot_call = call;
@@ -447,9 +487,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
             }
             n_srcrow += (size_t)p->r;
             if (it.col_map) n_srccol += (size_t)nc;
-            a_elems += (uint64_t)p->r * (uint64_t)nc;
-            np_max = std::max(np_max, (nc + 1) / 2);
-            ++npair;
+            a_elems += arena_of(it, nc);
             continue;
         }
         if (p->slot_call != call) {
@@ -484,8 +522,8 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         const int nc = cols_of(it);
         n_srcrow += (size_t)p->r;
         if (it.col_map) n_srccol += (size_t)nc;
-        a_elems += (uint64_t)p->r * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
-        nmax = std::max(nmax, nc);
+        a_elems += arena_of(it, nc);
+        if (!by_pairs(it)) nmax = std::max(nmax, nc);
     }
 
     // unit numbering of each launch: longest units first (items ordered by
@@ -500,14 +538,16 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         for (size_t i = 0; i < nitem; ++i) {
             const HostPlan& p = *items[i].plan;
             const double nc = cols_of(items[i]);
-            if (by_pairs(items[i])) cost[i] = (double)p.pair->mid * nc;
+            if (by_pairs(items[i]) && !minors) cost[i] = (double)p.pair->mid * nc;
             else cost[i] = (double)p.span / (double)p.units_per_group * (6.0 * nc - 2.0 + 12.0 * items[i].targets);
         }
         auto longer = [&](size_t x, size_t y) { return cost[x] > cost[y]; };
         std::stable_sort(order.begin(), order.end(), longer);
         std::stable_sort(order_pair.begin(), order_pair.end(), longer);
     }
-    auto units_of = [&](const PermItem& it) { return by_pairs(it) ? it.plan->pair->units : it.plan->units; };
+    auto units_of = [&](const PermItem& it) {
+        return by_pairs(it) && !minors ? it.plan->pair->units : it.plan->units;
+    };
     std::vector<uint64_t> unit_base(nitem), part_base(nitem);
     uint64_t total_units = 0, pair_units = 0, total_parts = 0;
     for (size_t i : order) {
@@ -519,8 +559,8 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     for (size_t i : order_pair) {
         unit_base[i] = pair_units;
         part_base[i] = total_parts;
-        pair_units += items[i].plan->pair->units;
-        total_parts += items[i].plan->pair->units;
+        pair_units += units_of(items[i]);
+        total_parts += units_of(items[i]) * stride_of(items[i]);
     }
     if (total_units > 0xFFFFFFF0ull || pair_units > 0xFFFFFFF0ull)
         return set_error(BBFG_ERANGE, "too many work units (%llu)", (unsigned long long)(total_units + pair_units));
@@ -540,12 +580,22 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     const size_t off_prep = L.add(sizeof(PrepItem) * nitem);
     const size_t off_src = L.add(sizeof(uint32_t) * std::max<size_t>(1, n_srcrow));
     const size_t off_col = L.add(sizeof(uint32_t) * std::max<size_t>(1, n_srccol));
-    const size_t nchunk = (size_t)((total_units + kUnitChunk - 1) / kUnitChunk);
-    const bool indexed = !single && nwalk > 0;
-    const size_t off_ubase = indexed ? L.add(sizeof(uint32_t) * (nwalk + 1)) : 0;
-    const size_t off_uorder = indexed ? L.add(sizeof(uint32_t) * nwalk) : 0;
-    const size_t off_uchunk = indexed ? L.add(sizeof(uint32_t) * (nchunk + 1)) : 0;
-    const size_t off_pair = npair ? L.add(sizeof(PairDesc) * npair) : 0;
+    // unit -> item index of a launch (a single walk needs none, the pair walk
+    // makes its own on the device)
+    struct UnitIndex {
+        bool on = false;
+        size_t nchunk = 0, base = 0, order = 0, chunk = 0;
+    } ix_walk, ix_pair;
+    auto place_index = [&L](UnitIndex& ix, size_t count, uint64_t units) {
+        ix.on = true;
+        ix.nchunk = (size_t)((units + kUnitChunk - 1) / kUnitChunk);
+        ix.base = L.add(sizeof(uint32_t) * (count + 1));
+        ix.order = L.add(sizeof(uint32_t) * count);
+        ix.chunk = L.add(sizeof(uint32_t) * (ix.nchunk + 1));
+    };
+    if (!single && nwalk) place_index(ix_walk, nwalk, total_units);
+    if (minors && npair) place_index(ix_pair, npair, pair_units);
+    const size_t off_pair = npair && !minors ? L.add(sizeof(PairDesc) * npair) : 0;
     const size_t off_ritem = L.add(sizeof(uint32_t) * (size_t)nres);
     const size_t off_tabs = L.add(std::max<size_t>(1, upload_bytes));
     BBFG_TRY(w.hmeta.ensure(L.size));
@@ -558,7 +608,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     uint32_t* hc = reinterpret_cast<uint32_t*>(H + off_col);
     uint32_t* hri = reinterpret_cast<uint32_t*>(H + off_ritem);
     for (const HostPlan* p : distinct)
-        std::memcpy(hr + p->slot_rowinfo, (p->pair && !f32 && !minors ? p->pair->rows : p->rows).data(),
+        std::memcpy(hr + p->slot_rowinfo, (p->pair && !f32 ? p->pair->rows : p->rows).data(),
                     sizeof(RowInfo) * (size_t)p->r);
     for (const Upload& u : uploads) std::memcpy(H + off_tabs + u.off, u.plan->table->data(), u.bytes);
     uint64_t a_cursor = 0;
@@ -570,8 +620,9 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         std::memset(&d, 0, sizeof d);
         d.a_off = a_cursor;
         const bool pair = by_pairs(items[i]);
-        d.a2_off = a_cursor + (uint64_t)p.r * nc;
-        a_cursor += (uint64_t)p.r * nc * (pair ? 1u : 3u);
+        const int np = pair && minors ? minor_pairs_per_wave(nc) : 0;
+        d.a2_off = a_cursor + (uint64_t)p.r * (np ? 2u * (uint64_t)np * kMinorWaves : (uint64_t)nc);
+        a_cursor += arena_of(items[i], nc);
         d.tab = p.slot_table;
         d.unit_base = unit_base[i];
         d.units = units_of(items[i]);
@@ -603,6 +654,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.r = p.r;
         q.f32 = f32;
         q.rows_only = pair ? 1 : 0;
+        q.np = np;
         for (int k = 0; k < p.r; ++k) {
             const int ur = p.src_row[(size_t)k];
             hs[s_cursor++] = (uint32_t)(items[i].row_map ? items[i].row_map[ur] : ur);
@@ -614,22 +666,25 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
             q.srccol_off = kIdentityCols;
         }
     }
-    if (indexed) {
-        uint32_t* hb = reinterpret_cast<uint32_t*>(H + off_ubase);
-        uint32_t* ho = reinterpret_cast<uint32_t*>(H + off_uorder);
-        uint32_t* hk = reinterpret_cast<uint32_t*>(H + off_uchunk);
-        for (size_t oi = 0; oi < nwalk; ++oi) {
-            const size_t i = order[oi];
-            const uint64_t b = unit_base[i], e = b + items[i].plan->units;
+    auto fill_index = [&](const UnitIndex& ix, const std::vector<size_t>& ord, uint64_t units) {
+        if (!ix.on) return;
+        uint32_t* hb = reinterpret_cast<uint32_t*>(H + ix.base);
+        uint32_t* ho = reinterpret_cast<uint32_t*>(H + ix.order);
+        uint32_t* hk = reinterpret_cast<uint32_t*>(H + ix.chunk);
+        for (size_t oi = 0; oi < ord.size(); ++oi) {
+            const size_t i = ord[oi];
+            const uint64_t b = unit_base[i], e = b + units_of(items[i]);
             hb[oi] = (uint32_t)b;
             ho[oi] = (uint32_t)i;
             for (uint64_t c = (b + kUnitChunk - 1) / kUnitChunk; c * kUnitChunk < e; ++c) hk[c] = (uint32_t)oi;
         }
-        hb[nwalk] = (uint32_t)total_units;
-        hk[nchunk] = (uint32_t)(nwalk - 1);
-    }
+        hb[ord.size()] = (uint32_t)units;
+        hk[ix.nchunk] = (uint32_t)(ord.size() - 1);
+    };
+    fill_index(ix_walk, order, total_units);
+    fill_index(ix_pair, order_pair, pair_units);
     uint64_t table_doubles = 0, unit_map = 0, mid_max = 0;
-    if (npair) {
+    if (npair && !minors) {
         PairDesc* hpd = reinterpret_cast<PairDesc*>(H + off_pair);
         for (size_t oi = 0; oi < npair; ++oi)
             mid_max = std::max(mid_max, fill_pair_desc(hpd[oi], hd[order_pair[oi]], *items[order_pair[oi]].plan,
@@ -657,17 +712,28 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     W.a2f = w.arena_f.as<float>();
     W.binom = c.binom;
     W.partials = w.partials.as<double>();
-    W.ubase = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_ubase);
-    W.uorder = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uorder);
-    W.uchunk = !indexed ? nullptr : reinterpret_cast<const uint32_t*>(D + off_uchunk);
+    auto set_index = [&](WalkArgs& w_, const UnitIndex& ix) {
+        w_.ubase = ix.on ? reinterpret_cast<const uint32_t*>(D + ix.base) : nullptr;
+        w_.uorder = ix.on ? reinterpret_cast<const uint32_t*>(D + ix.order) : nullptr;
+        w_.uchunk = ix.on ? reinterpret_cast<const uint32_t*>(D + ix.chunk) : nullptr;
+    };
+    set_index(W, ix_walk);
     W.nitem = (uint32_t)nitem;
     W.counter = w.counter.as<uint32_t>();
     W.total_units = (uint32_t)total_units;
 
     PairArgs PA;
     std::memset(&PA, 0, sizeof PA);
+    WalkArgs WP = W;  // the leave-one-column-out walk over pairs
     uint64_t pair_grid = 0;
-    if (npair) {
+    if (npair && minors) {
+        set_index(WP, ix_pair);
+        WP.counter = W.counter + kCounterStride;
+        WP.total_units = (uint32_t)pair_units;
+        int groups = 1;
+        BBFG_TRY(minor_groups(c, np_max, &groups));
+        pair_grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, pair_units);
+    } else if (npair) {
         PA.descs = reinterpret_cast<const PairDesc*>(D + off_pair);
         PA.rowinfo = W.rowinfo;
         PA.a = W.a;
@@ -682,7 +748,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         BBFG_TRY(pair_groups(c, np_max, powcols, &groups));
         pair_grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, pair_units);
     }
-    const uint32_t table_blocks = npair ? pair_table_blocks(npair, mid_max, (uint64_t)np_max) : 0;
+    const uint32_t table_blocks = npair && !minors ? pair_table_blocks(npair, mid_max, (uint64_t)np_max) : 0;
     int bucket = 0;
     uint64_t grid = total_units;
     if (!single && nwalk) {
@@ -705,9 +771,10 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
                              reinterpret_cast<const uint32_t*>(D + off_col), w.arena_d.as<double>(),
                              w.arena_d.as<double>(), w.arena_f.as<float>(), w.arena_f.as<float>()));
         if (!single || npair) BBFG_HIP(launch_reset_counter(W.counter, q));
-        if (npair) BBFG_HIP(launch_pair_tables((uint32_t)npair, table_blocks, q, PA));
+        if (npair && !minors) BBFG_HIP(launch_pair_tables((uint32_t)npair, table_blocks, q, PA));
         if (timed) BBFG_HIP(hipEventRecord(w.ev0, q));
-        if (npair) BBFG_HIP(launch_pair_walk(powcols, (uint32_t)pair_grid, q, PA));
+        if (npair && minors) BBFG_HIP(launch_minor_pairs(np_max, (uint32_t)pair_grid, q, WP));
+        else if (npair) BBFG_HIP(launch_pair_walk(powcols, (uint32_t)pair_grid, q, PA));
         if (!nwalk) {
         } else if (single) BBFG_HIP(launch_walk_single(items[0].plan->n, f32, (uint32_t)total_units, q, W, 0u));
         else if (minors) BBFG_HIP(launch_walk_minors(bucket, (uint32_t)grid, q, W));
@@ -756,10 +823,11 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         };
         mix(&W, sizeof W);
         mix(&PA, sizeof PA);
+        mix(&WP, sizeof WP);
         const uint64_t extra[] = {nitem, nres, (uint64_t)single, (uint64_t)minors, (uint64_t)powcols, (uint64_t)f32,
                                   (uint64_t)bucket,
-                                  grid, L.size, off_desc, off_row, off_prep, off_src, off_col, off_ubase, off_uorder, off_uchunk,
-                                  off_pair, off_ritem, off_tabs,
+                                  grid, L.size, off_desc, off_row, off_prep, off_src, off_col, ix_walk.base, ix_walk.order, ix_walk.chunk,
+                                  ix_pair.base, ix_pair.order, ix_pair.chunk, off_pair, off_ritem, off_tabs,
                                   npair, pair_grid, (uint64_t)table_blocks,
                                   (uint64_t)(uintptr_t)H, (uint64_t)(uintptr_t)D, (uint64_t)(uintptr_t)R,
                                   (uint64_t)(uintptr_t)HR, (uint64_t)(uintptr_t)w.arena_d.p,

@@ -136,7 +136,8 @@ struct Context {
     Workspace ws;
     std::map<std::pair<int, int>, int> occ_single;  // (n, f32) -> waves per CU
     std::map<std::pair<int, int>, int> occ_batch;   // (bucket, kind) -> waves per CU
-    std::map<std::pair<int, int>, int> occ_pair;    // (pairs of columns, pow) -> work groups per CU
+    std::map<std::pair<int, int>, int> occ_pair;    // (pairs of columns, pow), (-pairs a wavefront of a minors walk, 0) ->
+                                                    // work groups per CU
     std::unordered_map<std::string, std::shared_ptr<const HostPlan>> plans;
     // Gray tables shared between plans (host), and their device copies:
     // bump-allocated in chunks that are never moved while referenced
@@ -189,6 +190,8 @@ constexpr int kKindCols = 3;  // uniform column multiplicities
 int batch_waves(Context& c, int bucket, int kind, int* waves);
 // Resident work groups per CU of the pair walk with np pairs of columns.
 int pair_groups(Context& c, int np, bool pow, int* groups);
+// Resident work groups per CU of the leave-one-column-out walk over np pairs a wavefront.
+int minor_groups(Context& c, int np, int* groups);
 int pair_occupancy(int np, bool pow, int* groups);  // the same, asked of the device
 // Blocks over an item's pair-walk tables: many for a lone item, one for each of many.
 uint32_t pair_table_blocks(uint64_t items, uint64_t positions, uint64_t np);

@@ -248,6 +248,15 @@ void add_minor_items(const PermItem& proto, const int32_t* cols, std::deque<std:
                      std::vector<PermItem>& items, uint64_t res_first, uint32_t* slot)
 {
     const int K = proto.plan->n + 1;
+    if (proto.plan->minor_pairs) {  // one walk for every target
+        PermItem it = proto;
+        keep.emplace_back(cols, cols + K);
+        it.col_map = keep.back().data();
+        it.targets = K;
+        items.push_back(std::move(it));
+        for (int l = 0; l < K; ++l) slot[l] = (uint32_t)(res_first + (uint64_t)l);
+        return;
+    }
     const int G = minor_group(K);
     const int groups = (K + G - 1) / G;
     uint64_t res = res_first;

@@ -56,6 +56,45 @@ __global__ void prep_rows_kernel(const PrepItem* __restrict__ items, const uint3
     const PrepItem it = items[blockIdx.x];
     const int n = it.n, r = it.r;
     const double* A = it.src;
+    if (it.np > 0) {
+        // rows of all wavefronts' pairs (columns past the matrix zero), then per
+        // row but the last (the inner digit's) the two steps of its sign count:
+        // for each pair the changes of b_1, b_2 and D
+        const int pairs = it.np * kMinorWaves;
+        auto at = [&](int k, int j, double& xr, double& xi) {
+            xr = xi = 0.0;
+            if (j >= n) return;
+            const uint32_t col = it.srccol_off == kIdentityCols ? (uint32_t)j : srccol[it.srccol_off + j];
+            const uint64_t src = it.src_off + (uint64_t)srcrow[it.srcrow_off + k] * (uint64_t)it.ld + (uint64_t)col;
+            xr = A[2 * src];
+            xi = A[2 * src + 1];
+        };
+        for (int e = threadIdx.x; e < r * pairs; e += blockDim.x) {
+            const int k = e / pairs, p = e - k * pairs;
+            double ar, ai, br, bi;
+            at(k, 2 * p, ar, ai);
+            at(k, 2 * p + 1, br, bi);
+            double* row = a + 2 * it.a_off + 4 * (size_t)e;
+            row[0] = ar;
+            row[1] = ai;
+            row[2] = br;
+            row[3] = bi;
+            if (k + 1 == r) continue;
+            double cr, ci, dr, di;  // the inner row: D changes by 4 (c b + a d) when Delta_k grows
+            at(r - 1, 2 * p, cr, ci);
+            at(r - 1, 2 * p + 1, dr, di);
+            const double kr = 4.0 * (__builtin_fma(cr, br, -(ci * bi)) + __builtin_fma(ar, dr, -(ai * di)));
+            const double ki = 4.0 * (__builtin_fma(cr, bi, ci * br) + __builtin_fma(ar, di, ai * dr));
+            double* down = a2 + 2 * it.a2_off + 6 * ((size_t)(2 * k) * pairs + p);
+            double* up = down + 6 * (size_t)pairs;
+            const double v[6] = {2.0 * ar, 2.0 * ai, 2.0 * br, 2.0 * bi, -kr, -ki};
+            for (int q = 0; q < 6; ++q) {
+                down[q] = v[q];
+                up[q] = -v[q];
+            }
+        }
+        return;
+    }
     for (int e = threadIdx.x; e < r * n; e += blockDim.x) {
         const int k = e / n, j = e - k * n;
         const uint32_t col = it.srccol_off == kIdentityCols ? (uint32_t)j : srccol[it.srccol_off + j];
@@ -258,6 +297,14 @@ hipError_t launch_walk_minors(int bucket, uint32_t grid, hipStream_t s, const Wa
     if (!fn) return hipErrorInvalidValue;
     void* args[] = {const_cast<WalkArgs*>(&A)};
     return hipLaunchKernel(fn, dim3(grid), dim3(kWave), args, 0, s);
+}
+
+const void* minor_pairs_fn(int np) { return np <= 3 ? minor_pairs_fn_b3() : np <= 4 ? minor_pairs_fn_b4() : minor_pairs_fn_b6(); }
+
+hipError_t launch_minor_pairs(int np, uint32_t grid, hipStream_t s, const WalkArgs& A)
+{
+    void* args[] = {const_cast<WalkArgs*>(&A)};
+    return hipLaunchKernel(minor_pairs_fn(np), dim3(grid), dim3(kWave * kMinorWaves), args, 0, s);
 }
 
 hipError_t launch_walk_single(int n, int f32, uint32_t grid, hipStream_t s, const WalkArgs& A, uint32_t item)

@@ -1,0 +1,152 @@
+// minor_pairs_emu.cpp -- CPU emulation of the leave-one-column-out walk over
+// pairs of columns, for tests.
+//
+// Runs the per-lane code of the gfx950 kernel (minor_pairs_core.hpp, compiled
+// for the host with bounds-checked pointers) on the planner's split: the four
+// wavefronts of a work group in step, lane by lane.  Built with
+// AddressSanitizer/UBSan by the tests.
+//
+// stdin : n_rows K slots l_batch / n_rows multiplicities (sum K - 1) /
+//         n_rows*K complex entries (re im, hex floats), row-major
+// stdout: K lines "re im" (permanent without column l), or "general" when the
+//         planner leaves the case to the other walk
+#include <cmath>
+#include <cstdio>
+#include <vector>
+
+#include "minor_pairs_core.hpp"
+#include "plan.hpp"
+
+using namespace bbfg;
+
+namespace {
+
+template <int NP>
+void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<double>& out)
+{
+    const int r = P.r, pairs = NP * kMinorWaves;
+    // the prep kernel's layout
+    std::vector<double> rows(4 * (size_t)r * pairs, 0.0), steps(6 * (size_t)(2 * (r - 1)) * pairs);
+    for (int k = 0; k < r; ++k)
+        for (int j = 0; j < K; ++j)
+            for (int c = 0; c < 2; ++c)
+                rows[4 * (size_t)k * pairs + 2 * j + c] = A[2 * ((size_t)P.src_row[(size_t)k] * K + j) + c];
+    for (int k = 0; k + 1 < r; ++k)
+        for (int p = 0; p < pairs; ++p) {
+            const double* x = &rows[4 * ((size_t)k * pairs + p)];
+            const double* c = &rows[4 * ((size_t)(r - 1) * pairs + p)];
+            const double kr = 4.0 * (c[0] * x[2] - c[1] * x[3] + x[0] * c[2] - x[1] * c[3]);
+            const double ki = 4.0 * (c[0] * x[3] + c[1] * x[2] + x[0] * c[3] + x[1] * c[2]);
+            const double v[6] = {2 * x[0], 2 * x[1], 2 * x[2], 2 * x[3], -kr, -ki};
+            for (int q = 0; q < 6; ++q) {
+                steps[6 * ((size_t)(2 * k) * pairs + p) + q] = v[q];
+                steps[6 * ((size_t)(2 * k + 1) * pairs + p) + q] = -v[q];
+            }
+        }
+    emu_clear();
+    emu_register(rows.data(), sizeof(double) * rows.size());
+    emu_register(steps.data(), sizeof(double) * steps.size());
+    std::vector<double> binom((size_t)kBinomDim * kBinomDim, 0.0);
+    for (int m = 0; m < kBinomDim; ++m)
+        for (int k = 0; k <= m; ++k) binom[(size_t)m * kBinomDim + k] = (double)binom_u64(m, k);
+    const size_t ld = 4 * (size_t)pairs, step_ld = 6 * (size_t)pairs;
+    const uint32_t upg = (uint32_t)P.units_per_group;
+    for (uint64_t u = 0; u < P.units; ++u) {
+        const uint32_t g = (uint32_t)(u / upg), part = (uint32_t)(u % upg);
+        const uint64_t base = P.span / upg, rem = P.span - base * upg;
+        const uint64_t lin0 = part * base + (part < rem ? part : rem), lin1 = lin0 + base + (part < rem ? 1 : 0);
+        for (uint32_t lane = 0; lane < (uint32_t)kWave; ++lane) {
+            const uint32_t lane_idx = g * kWave + lane;
+            if (lane_idx >= P.lane_product) continue;
+            MinorLane<NP> L[kMinorWaves];
+            for (auto& l : L) l.clear();
+            for (uint64_t lin = lin0; lin < lin1;) {
+                const uint64_t h = lin / P.Q;
+                const uint32_t t0 = (uint32_t)(lin - h * P.Q);
+                const uint64_t bend = (h + 1) * (uint64_t)P.Q;
+                const uint32_t t1 = (uint32_t)((lin1 < bend ? lin1 : bend) - h * P.Q);
+                std::vector<int> coef((size_t)r);
+                double w = 1.0;
+                for (int k = 0; k < r; ++k) {
+                    const RowInfo& x = P.rows[(size_t)k];
+                    uint32_t delta = 0;
+                    if (x.kind == ROW_LANE) delta = (lane_idx / x.stride) % x.radix;
+                    else if (x.kind == ROW_HIGH) delta = digit_of(h, x.stride, x.radix);
+                    else if (x.kind == ROW_LOW) {
+                        const uint32_t dg = (t0 / x.stride) % x.radix, q = t0 / (x.stride * x.radix);
+                        delta = (q & 1u) ? (x.radix - 1u - dg) : dg;
+                    }
+                    coef[(size_t)k] = x.base - 2 * (int)delta;
+                    w *= pair_row_weight(x, binom.data(), coef[(size_t)k]);
+                }
+                for (int v = 0; v < kMinorWaves; ++v)
+                    L[v].seed(kconst(rows.data()) + v * 4 * NP, ld, r, K - v * 2 * NP,
+                              [&](int k) { return (double)coef[(size_t)k]; });
+                for (uint32_t t = t0; t < t1; ++t) {
+                    const TabEntry e = (*P.table)[t];
+                    if (t > t0)
+                        for (int v = 0; v < kMinorWaves; ++v)
+                            L[v].advance(&steps[(size_t)e.row * step_ld + (size_t)v * 6 * NP]);
+                    for (auto& l : L) l.forward();
+                    for (int v = 0; v < kMinorWaves; ++v) {
+                        cpx o[2];
+                        for (int x = 0; x < 2; ++x)
+                            o[x] = cmul_uniform(cmul(cmul(L[(v + 1) % kMinorWaves].half[x].all,
+                                                          L[(v + 2) % kMinorWaves].half[x].all),
+                                                     L[(v + 3) % kMinorWaves].half[x].all),
+                                                w * e.s);
+                        L[v].backward(o[0], o[1]);
+                    }
+                }
+                lin += t1 - t0;
+            }
+            for (int v = 0; v < kMinorWaves; ++v)
+                for (int p = 0; p < NP; ++p) {
+                    cpx c[2];
+                    L[v].result(p, kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + (size_t)v * 4 * NP), c[0], c[1]);
+                    for (int q = 0; q < 2; ++q) {
+                        const int j = v * 2 * NP + 2 * p + q;
+                        if (j >= K) continue;
+                        out[2 * (size_t)j] += c[q].r;
+                        out[2 * (size_t)j + 1] += c[q].i;
+                    }
+                }
+        }
+    }
+}
+
+}  // namespace
+
+int main()
+{
+    int n_rows = 0, K = 0;
+    long long slots = 0, l_batch = 0;
+    if (std::scanf("%d %d %lld %lld", &n_rows, &K, &slots, &l_batch) != 4) return 2;
+    std::vector<int32_t> M((size_t)n_rows);
+    for (int32_t& m : M)
+        if (std::scanf("%d", &m) != 1) return 2;
+    std::vector<double> A(2 * (size_t)n_rows * (size_t)K);
+    for (double& x : A)
+        if (std::scanf("%la", &x) != 1) return 2;
+    HostPlan P;
+    PlanParams pp;
+    pp.l_batch = (uint64_t)l_batch;
+    std::string err;
+    if (!build_minor_pair_plan(M.data(), n_rows, K - 1, (uint64_t)slots, pp, P, err)) {
+        if (!err.empty()) return 3;
+        std::printf("general\n");
+        return 0;
+    }
+    std::vector<double> out(2 * (size_t)K, 0.0);
+    switch (minor_pairs_per_wave(K)) {
+    case 2: run<2>(P, K, A, out); break;
+    case 3: run<3>(P, K, A, out); break;
+    case 4: run<4>(P, K, A, out); break;
+    case 5: run<5>(P, K, A, out); break;
+    case 6: run<6>(P, K, A, out); break;
+    default: return 4;
+    }
+    const double s = std::ldexp(1.0, P.scale_log2);
+    for (int l = 0; l < K; ++l) std::printf("%a %a\n", out[2 * (size_t)l] * s, out[2 * (size_t)l + 1] * s);
+    return 0;
+}
