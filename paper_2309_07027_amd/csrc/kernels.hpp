@@ -31,7 +31,6 @@ const void* walk_minors_fn_b30();
 const void* walk_minors_fn_b32();
 const void* walk_minors_fn_b48();
 hipError_t launch_walk_minors(int bucket, uint32_t grid, hipStream_t s, const WalkArgs& A);
-hipError_t launch_reset_counter(uint32_t* counter, hipStream_t s);
 // leave-one-column-out walk over pairs, np pairs of columns a wavefront at most
 const void* minor_pairs_fn(int np);
 const void* minor_pairs_fn_b3();
@@ -44,8 +43,11 @@ const void* pair_walk_fn(bool pow);
 size_t pair_lds_bytes(uint32_t np);
 hipError_t launch_pair_tables(uint32_t items, uint32_t blocks, hipStream_t s, const PairArgs& A);
 hipError_t launch_pair_walk(bool pow, uint32_t grid, hipStream_t s, const PairArgs& A);
+// counters: the unit counters, cleared.  image_bytes > 0: it, srcrow and srccol
+// point into the pinned host image, which is copied to image_copy.
 hipError_t launch_prep(uint32_t items, hipStream_t s, const PrepItem* it, const uint32_t* srcrow, const uint32_t* srccol,
-                       double* a, double* a2, float* af, float* a2f);
+                       double* a, double* a2, float* af, float* a2f, uint32_t* counters, const void* image = nullptr,
+                       void* image_copy = nullptr, size_t image_bytes = 0);
 hipError_t launch_finalize(uint32_t results, hipStream_t s, const PermDesc* descs, const uint32_t* res_item,
                            const double* partials, double* out, double* diag);
 hipError_t launch_init_binom(double* tab, hipStream_t s);

@@ -249,7 +249,7 @@ try {
     if (!P.pair)
         BBFG_HIP(hipMemcpyAsync(base + kOffTable, g_host_meta + kMetaBytes, tab_bytes, hipMemcpyHostToDevice, s));
     BBFG_HIP(launch_prep(1, s, reinterpret_cast<const PrepItem*>(D + o_prep), reinterpret_cast<const uint32_t*>(D + o_src),
-                         nullptr, arena, arena, nullptr, nullptr));
+                         nullptr, arena, arena, nullptr, nullptr, reinterpret_cast<uint32_t*>(base + kOffCounters)));
     if (P.pair) {
         PairArgs PA;
         std::memset(&PA, 0, sizeof PA);
@@ -262,7 +262,6 @@ try {
         PA.counter = reinterpret_cast<uint32_t*>(base + kOffCounters) + kCounterStride;
         PA.total_units = (uint32_t)P.pair->units;
         PA.np_max = (uint32_t)(n + 1) / 2;
-        BBFG_HIP(launch_reset_counter(reinterpret_cast<uint32_t*>(base + kOffCounters), s));
         BBFG_HIP(launch_pair_tables(1, pair_table_blocks(1, pair_positions, PA.np_max), s, PA));
         BBFG_HIP(launch_pair_walk(false, (uint32_t)std::min<uint64_t>((uint64_t)g_pair_groups[dev][PA.np_max] * g_ncu[dev], P.pair->units), s, PA));
     } else {

@@ -762,15 +762,20 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     double* HR = w.hres.as<double>();
 
     // Everything one evaluation puts on a stream (also what a graph captures):
-    // metadata upload, gather, walk, finalize and, when results go back to the
-    // host, their download.  No memset: the unit counter is cleared by a kernel.
+    // metadata upload, gather, walks and finalize, whose results go straight to
+    // pinned host memory when the host waits for them.  No memset: the unit
+    // counters are cleared by the gather kernel.  A short metadata image is read
+    // and copied by the gather kernel itself.
+    const bool short_image = off_tabs <= kShortImageBytes;
+    const char* M = short_image ? H : D;
+    double* out = sync ? HR : R;
     auto enqueue = [&](hipStream_t q, bool timed) -> int {
-        BBFG_HIP(hipMemcpyAsync(D, H, L.size, hipMemcpyHostToDevice, q));
-        BBFG_HIP(launch_prep((uint32_t)nitem, q, reinterpret_cast<const PrepItem*>(D + off_prep),
-                             reinterpret_cast<const uint32_t*>(D + off_src),
-                             reinterpret_cast<const uint32_t*>(D + off_col), w.arena_d.as<double>(),
-                             w.arena_d.as<double>(), w.arena_f.as<float>(), w.arena_f.as<float>()));
-        if (!single || npair) BBFG_HIP(launch_reset_counter(W.counter, q));
+        if (!short_image) BBFG_HIP(hipMemcpyAsync(D, H, off_tabs, hipMemcpyHostToDevice, q));
+        BBFG_HIP(launch_prep((uint32_t)nitem, q, reinterpret_cast<const PrepItem*>(M + off_prep),
+                             reinterpret_cast<const uint32_t*>(M + off_src),
+                             reinterpret_cast<const uint32_t*>(M + off_col), w.arena_d.as<double>(),
+                             w.arena_d.as<double>(), w.arena_f.as<float>(), w.arena_f.as<float>(), W.counter,
+                             H, D, short_image ? off_tabs : 0));
         if (npair && !minors) BBFG_HIP(launch_pair_tables((uint32_t)npair, table_blocks, q, PA));
         if (timed) BBFG_HIP(hipEventRecord(w.ev0, q));
         if (npair && minors) BBFG_HIP(launch_minor_pairs(np_max, (uint32_t)pair_grid, q, WP));
@@ -782,8 +787,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         else BBFG_HIP(launch_walk_batch(bucket, f32, (uint32_t)grid, q, W));
         if (timed) BBFG_HIP(hipEventRecord(w.ev1, q));
         BBFG_HIP(launch_finalize((uint32_t)nres, q, W.descs, reinterpret_cast<const uint32_t*>(D + off_ritem),
-                                 W.partials, R, R + 2 * nres));
-        if (sync) BBFG_HIP(hipMemcpyAsync(HR, R, sizeof(double) * 4 * nres, hipMemcpyDeviceToHost, q));
+                                 W.partials, out, out + 2 * nres));
         return BBFG_OK;
     };
 

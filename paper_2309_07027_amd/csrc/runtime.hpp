@@ -83,6 +83,10 @@ struct PinnedBuf {
     T* as() const { return static_cast<T*>(p); }
 };
 
+// A metadata image of at most this many bytes is read over the bus by the
+// kernel that needs it first; longer ones, with many items, are copied before.
+constexpr size_t kShortImageBytes = 64 << 10;
+
 // Byte layout helper for one upload of several arrays.
 struct Layout {
     size_t size = 0;

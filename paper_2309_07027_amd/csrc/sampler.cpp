@@ -355,7 +355,6 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
     const size_t o_pi = L.add(sizeof(int32_t) * pis.size());
     const size_t o_slot = L.add(sizeof(uint32_t) * std::max<size_t>(1, slots.size()));
     const size_t o_drawn = L.add(sizeof(int32_t) * steps.size());
-    const size_t o_wsum = L.add(sizeof(double) * steps.size());
     const size_t o_tv = L.add(sizeof(double) * steps.size());
     BBFG_TRY(w.cc_hmeta.ensure(L.size));
     BBFG_TRY(w.cc_meta.ensure(L.size));
@@ -364,14 +363,18 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
     std::memcpy(H + o_steps, steps.data(), sizeof(CCStep) * steps.size());
     std::memcpy(H + o_pi, pis.data(), sizeof(int32_t) * pis.size());
     if (!slots.empty()) std::memcpy(H + o_slot, slots.data(), sizeof(uint32_t) * slots.size());
-    BBFG_HIP(hipMemcpyAsync(D, H, o_drawn, hipMemcpyHostToDevice, s));
-    // the minors' diagnostics follow their nres results (run_perms)
-    BBFG_HIP(launch_cc_weights((uint32_t)steps.size(), reinterpret_cast<const CCStep*>(D + o_steps),
-                               reinterpret_cast<const int32_t*>(D + o_pi),
-                               reinterpret_cast<const uint32_t*>(D + o_slot), w.results.as<double>(),
-                               w.results.as<double>() + 2 * nres, reinterpret_cast<int32_t*>(D + o_drawn),
-                               reinterpret_cast<double*>(D + o_wsum), reinterpret_cast<double*>(D + o_tv), s));
-    BBFG_HIP(hipMemcpyAsync(H + o_drawn, D + o_drawn, L.size - o_drawn, hipMemcpyDeviceToHost, s));
+    // a short image is read from pinned host memory; the draws go back there.
+    // The minors' diagnostics follow their nres results (run_perms).
+    const char* M = H;
+    if (o_drawn > kShortImageBytes) {
+        BBFG_HIP(hipMemcpyAsync(D, H, o_drawn, hipMemcpyHostToDevice, s));
+        M = D;
+    }
+    BBFG_HIP(launch_cc_weights((uint32_t)steps.size(), reinterpret_cast<const CCStep*>(M + o_steps),
+                               reinterpret_cast<const int32_t*>(M + o_pi),
+                               reinterpret_cast<const uint32_t*>(M + o_slot), w.results.as<double>(),
+                               w.results.as<double>() + 2 * nres, reinterpret_cast<int32_t*>(H + o_drawn),
+                               reinterpret_cast<double*>(H + o_tv), s));
     BBFG_HIP(hipEventRecord(w.done, s));
     p.o_drawn = o_drawn;
     p.o_tv = o_tv;

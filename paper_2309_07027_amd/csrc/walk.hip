@@ -47,12 +47,26 @@ __global__ void init_binom_kernel(double* tab)
 }
 
 // ---------------------------------------------------------------------------
-// prep: gather the kept rows of each matrix, and build the +-2a rows
+// prep: gather the kept rows of each matrix, and build the +-2a rows; clear the
+// unit counters.  For a short launch sequence the metadata image is not copied
+// before: the first blocks read their items from the pinned host image, the
+// others copy it for the kernels that follow (one launch instead of three).
 // ---------------------------------------------------------------------------
-__global__ void prep_rows_kernel(const PrepItem* __restrict__ items, const uint32_t* __restrict__ srcrow,
-                                 const uint32_t* __restrict__ srccol, double* __restrict__ a, double* __restrict__ a2,
-                                 float* __restrict__ af, float* __restrict__ a2f)
+constexpr int kPrepThreads = 256;
+constexpr size_t kImageBlockBytes = kPrepThreads * sizeof(uint4);
+
+__global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
+    uint32_t nitem, const PrepItem* __restrict__ items, const uint32_t* __restrict__ srcrow,
+    const uint32_t* __restrict__ srccol, double* __restrict__ a, double* __restrict__ a2, float* __restrict__ af,
+    float* __restrict__ a2f, uint32_t* __restrict__ counters, const uint4* __restrict__ image,
+    uint4* __restrict__ image_copy, uint32_t image_vecs)
 {
+    if (blockIdx.x == 0 && counters && threadIdx.x < kCounters) counters[threadIdx.x * kCounterStride] = 0u;
+    if (blockIdx.x >= nitem) {
+        const uint32_t v = (blockIdx.x - nitem) * kPrepThreads + threadIdx.x;
+        if (v < image_vecs) image_copy[v] = image[v];
+        return;
+    }
     const PrepItem it = items[blockIdx.x];
     const int n = it.n, r = it.r;
     const double* A = it.src;
@@ -134,11 +148,6 @@ __global__ __launch_bounds__(kWave) void walk_single_kernel(WalkArgs A, uint32_t
     double r, i, a;
     walk_unit<N, Real>(A, d, u, threadIdx.x & (kWave - 1), r, i, a);
     store_partial(A.partials, d.part_base + u, r, i, a);
-}
-
-__global__ void reset_counter_kernel(uint32_t* counter)
-{
-    if (threadIdx.x < kCounters) counter[threadIdx.x * kCounterStride] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -323,17 +332,15 @@ hipError_t launch_walk_batch(int bucket, int f32, uint32_t grid, hipStream_t s, 
     return hipLaunchKernel(fn, dim3(grid), dim3(kWave), args, 0, s);
 }
 
-hipError_t launch_reset_counter(uint32_t* counter, hipStream_t s)
-{
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, s, counter);
-    return hipGetLastError();
-}
-
 hipError_t launch_prep(uint32_t items, hipStream_t s, const PrepItem* it, const uint32_t* srcrow, const uint32_t* srccol,
-                       double* a, double* a2, float* af, float* a2f)
+                       double* a, double* a2, float* af, float* a2f, uint32_t* counters, const void* image,
+                       void* image_copy, size_t image_bytes)
 {
     if (items == 0) return hipSuccess;
-    hipLaunchKernelGGL(prep_rows_kernel, dim3(items), dim3(256), 0, s, it, srcrow, srccol, a, a2, af, a2f);
+    const uint32_t vecs = (uint32_t)((image_bytes + sizeof(uint4) - 1) / sizeof(uint4));
+    const uint32_t blocks = items + (uint32_t)((image_bytes + kImageBlockBytes - 1) / kImageBlockBytes);
+    hipLaunchKernelGGL(prep_rows_kernel, dim3(blocks), dim3(kPrepThreads), 0, s, items, it, srcrow, srccol, a, a2, af,
+                       a2f, counters, static_cast<const uint4*>(image), static_cast<uint4*>(image_copy), vecs);
     return hipGetLastError();
 }
 
