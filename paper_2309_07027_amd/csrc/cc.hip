@@ -35,15 +35,82 @@ __global__ void build_job_matrix_kernel(const double* __restrict__ U, int m, con
     }
 }
 
-// One block per sample's step.  Bound by latency: the step's record, columns and
-// minors are gathered once into LDS, so that the loads of a candidate's sum are
-// independent of each other, and one thread adds the weights in row order,
-// keeping the running sums for a search by all threads.  (With the loads
-// chained through the slot map inside the sums, and a serial search, a step of
-// 20 photons on 60 modes took 10.5 us.)
 constexpr int kCCThreads = 256;
 constexpr int kCCRows = 256;    // most candidate rows (2 x 128 modes, or 256)
 
+// What the draw of one step works on: the first k permuted columns, their
+// minors (values, moduli, error estimates), the candidates' weights.
+struct CCShared {
+    double w[kCCRows], dw[kCCRows];
+    double mr[kMaxN], mi[kMaxN], ma[kMaxN], me[kMaxN];
+    double sums[2];
+    int32_t p[kMaxN];
+    int choice;
+};
+
+// Draws row r_k by inverse CDF from the minors in S (all threads of the block;
+// S.choice is the drawn row and the return value its error estimate afterwards,
+// for thread 0).  The loads of a candidate's sum are independent of each other,
+// and one thread adds the weights in row order, keeping the running sums for a
+// search by all threads.
+__device__ __forceinline__ double cc_draw(CCShared& S, const double* A, int rows, int n, int k, double u)
+{
+    if (threadIdx.x == 0) S.choice = rows;
+    for (int r = threadIdx.x; r < rows; r += kCCThreads) {
+        const double* arow = A + 2 * (size_t)r * n;
+        double sr = 0.0, si = 0.0, e = 0.0;
+        if (k == 1) {
+            sr = arow[2 * S.p[0]];
+            si = arow[2 * S.p[0] + 1];
+        } else {
+#pragma unroll 8
+            for (int l = 0; l < k; ++l) {
+                const double ar = arow[2 * S.p[l]], ai = arow[2 * S.p[l] + 1];
+                sr = __builtin_fma(ar, S.mr[l], sr);
+                sr = __builtin_fma(-ai, S.mi[l], sr);
+                si = __builtin_fma(ar, S.mi[l], si);
+                si = __builtin_fma(ai, S.mr[l], si);
+                e += __builtin_sqrt(ar * ar + ai * ai) * S.ma[l] * S.me[l];
+            }
+        }
+        S.w[r] = __builtin_fma(sr, sr, si * si);
+        S.dw[r] = e * (2.0 * __builtin_sqrt(S.w[r]) + e);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double total = 0.0, dtotal = 0.0;
+#pragma unroll 8
+        for (int r = 0; r < rows; ++r) {
+            total += S.w[r];
+            dtotal += S.dw[r];
+            S.dw[r] = total;  // the running sum of the weights
+        }
+        S.sums[0] = total;
+        S.sums[1] = dtotal;
+    }
+    __syncthreads();
+    const double total = S.sums[0], target = u * total;
+    for (int r = threadIdx.x; r < rows; r += kCCThreads)
+        if (S.dw[r] > target) atomicMin(&S.choice, r);
+    __syncthreads();
+    if (threadIdx.x == 0 && S.choice >= rows) {
+        // rounding left the draw past the total: the last row with a weight
+        int c = rows - 1;
+        for (int r = rows - 1; r >= 0; --r)
+            if (S.w[r] > 0.0) {
+                c = r;
+                break;
+            }
+        S.choice = c;
+    }
+    __syncthreads();
+    return total > 0.0 ? S.sums[1] / total : 0.0;
+}
+
+// One block per sample's step.  Bound by latency: the step's record, columns and
+// minors are gathered once into LDS.  (With the loads chained through the slot
+// map inside the sums, and a serial search, a step of 20 photons on 60 modes
+// took 10.5 us.)
 __global__ __launch_bounds__(kCCThreads) void cc_weights_kernel(const CCStep* __restrict__ steps,
                                                                 const int32_t* __restrict__ pi,
                                                                 const uint32_t* __restrict__ slot,
@@ -52,76 +119,173 @@ __global__ __launch_bounds__(kCCThreads) void cc_weights_kernel(const CCStep* __
                                                                 int32_t* __restrict__ drawn, double* __restrict__ tv_est)
 {
     const CCStep st = steps[blockIdx.x];
-    __shared__ double w[kCCRows];
-    __shared__ double dw[kCCRows];
-    __shared__ double mr[kMaxN], mi[kMaxN], ma[kMaxN], me[kMaxN];
-    __shared__ int32_t p[kMaxN];
-    __shared__ int choice;
-    __shared__ double sums[2];
+    __shared__ CCShared S;
     if ((int)threadIdx.x < st.k) {
         const int l = threadIdx.x;
-        p[l] = pi[st.pi_off + l];
+        S.p[l] = pi[st.pi_off + l];
         if (st.k > 1) {
             const size_t q = slot[st.minor_off + l];
             const double x = minors[2 * q], y = minors[2 * q + 1];
-            mr[l] = x;
-            mi[l] = y;
-            ma[l] = __builtin_sqrt(x * x + y * y);
-            me[l] = minor_err[2 * q];
+            S.mr[l] = x;
+            S.mi[l] = y;
+            S.ma[l] = __builtin_sqrt(x * x + y * y);
+            S.me[l] = minor_err[2 * q];
         }
     }
-    if (threadIdx.x == 0) choice = st.rows;
     __syncthreads();
-    for (int r = threadIdx.x; r < st.rows; r += kCCThreads) {
-        const double* arow = st.A + 2 * (size_t)r * st.n;
-        double sr = 0.0, si = 0.0, e = 0.0;
-        if (st.k == 1) {
-            sr = arow[2 * p[0]];
-            si = arow[2 * p[0] + 1];
-        } else {
-#pragma unroll 8
-            for (int l = 0; l < st.k; ++l) {
-                const double ar = arow[2 * p[l]], ai = arow[2 * p[l] + 1];
-                sr = __builtin_fma(ar, mr[l], sr);
-                sr = __builtin_fma(-ai, mi[l], sr);
-                si = __builtin_fma(ar, mi[l], si);
-                si = __builtin_fma(ai, mr[l], si);
-                e += __builtin_sqrt(ar * ar + ai * ai) * ma[l] * me[l];
+    const double tv = cc_draw(S, st.A, st.rows, st.n, st.k, st.u);
+    if (threadIdx.x == 0) {
+        drawn[blockIdx.x] = S.choice;
+        tv_est[blockIdx.x] = tv;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the first steps of a sample, all in one launch
+// ---------------------------------------------------------------------------
+// Step k's minors are sums of 2^{k-2} addends over the signs of the k - 1
+// prefix rows (the first at +1; a row drawn twice is two rows): too short to be
+// worth a round trip to the host each.  One block takes a sample through its
+// first kEarlySteps steps.  A thread holds one pattern of the first eight signs
+// and walks the others in Gray order; the threads' sums meet in LDS.  Bound by
+// the latency of a step's chain of gathers, sums and draw: about 7 us a step
+// against 60 us for a step of its own launches and round trip.  16 samples on 60
+// modes: 12 photons 736 -> 144 us, 20 photons 1.41 -> 0.73 ms.  At 14 columns a
+// thread walks 16 patterns; each further step would double that, and a step's
+// own launches fill the device better from there on.
+constexpr int kEarlySigns = 8;
+static_assert(kCCThreads == 1 << kEarlySigns, "a thread per sign pattern");
+
+struct EarlyShared {
+    CCShared draw;
+    double row[kEarlySteps][kEarlySteps][2];           // drawn rows at the sample's columns
+    double acc[3 * kEarlySteps][kCCThreads + 1];       // per target: re, im, |re| + |im| of every thread
+    double part[3 * kEarlySteps][4];
+};
+
+template <int K>
+__device__ __forceinline__ void early_minors(EarlyShared& S)
+{
+    constexpr int kSigns = K - 2;
+    constexpr int kHeld = kSigns < kEarlySigns ? kSigns : kEarlySigns;
+    const uint32_t t = threadIdx.x;
+    double accr[K], acci[K], acca[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) accr[j] = acci[j] = acca[j] = 0.0;
+    if (t < (1u << kHeld)) {
+        double re[K], im[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            re[j] = S.row[0][j][0];
+            im[j] = S.row[0][j][1];
+        }
+        double sign = 1.0;
+        for (int i = 0; i < kSigns; ++i) {
+            const double d = i < kHeld && (t >> i & 1u) ? -1.0 : 1.0;
+            sign *= d;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                re[j] = __builtin_fma(d, S.row[1 + i][j][0], re[j]);
+                im[j] = __builtin_fma(d, S.row[1 + i][j][1], im[j]);
             }
         }
-        w[r] = __builtin_fma(sr, sr, si * si);
-        dw[r] = e * (2.0 * __builtin_sqrt(w[r]) + e);
+        for (uint32_t g = 0;;) {
+            double pr[K], pm[K];
+            pr[0] = sign;
+            pm[0] = 0.0;
+#pragma unroll
+            for (int j = 1; j < K; ++j) {
+                pr[j] = __builtin_fma(pr[j - 1], re[j - 1], -(pm[j - 1] * im[j - 1]));
+                pm[j] = __builtin_fma(pr[j - 1], im[j - 1], pm[j - 1] * re[j - 1]);
+            }
+            double sr = 1.0, si = 0.0;
+#pragma unroll
+            for (int j = K - 1; j >= 0; --j) {
+                const double zr = __builtin_fma(pr[j], sr, -(pm[j] * si));
+                const double zi = __builtin_fma(pr[j], si, pm[j] * sr);
+                accr[j] += zr;
+                acci[j] += zi;
+                acca[j] += __builtin_fabs(zr) + __builtin_fabs(zi);
+                const double nr = __builtin_fma(sr, re[j], -(si * im[j]));
+                si = __builtin_fma(sr, im[j], si * re[j]);
+                sr = nr;
+            }
+            if (++g >= (1u << (kSigns - kHeld))) break;
+            const int b = __builtin_ctz(g);
+            const double d = ((g ^ (g >> 1)) >> b & 1u) ? -2.0 : 2.0;
+            sign = -sign;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                re[j] = __builtin_fma(d, S.row[1 + kHeld + b][j][0], re[j]);
+                im[j] = __builtin_fma(d, S.row[1 + kHeld + b][j][1], im[j]);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        S.acc[3 * j][t] = accr[j];
+        S.acc[3 * j + 1][t] = acci[j];
+        S.acc[3 * j + 2][t] = acca[j];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double total = 0.0, dtotal = 0.0;
+    if (t < 3 * K * 4) {
+        const double* a = S.acc[t >> 2];
+        const uint32_t first = (t & 3u) * (kCCThreads / 4);
+        double s = 0.0;
 #pragma unroll 8
-        for (int r = 0; r < st.rows; ++r) {
-            total += w[r];
-            dtotal += dw[r];
-            dw[r] = total;  // the running sum of the weights
-        }
-        sums[0] = total;
-        sums[1] = dtotal;
+        for (uint32_t i = 0; i < kCCThreads / 4; ++i) s += a[first + ((i + 16 * (t & 3u)) & (kCCThreads / 4 - 1))];
+        S.part[t >> 2][t & 3u] = s;
     }
     __syncthreads();
-    const double total = sums[0], target = st.u * total;
-    for (int r = threadIdx.x; r < st.rows; r += kCCThreads)
-        if (dw[r] > target) atomicMin(&choice, r);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int c = choice;
-        if (c >= st.rows) {  // rounding left the draw past the total: the last row with a weight
-            c = st.rows - 1;
-            for (int r = st.rows - 1; r >= 0; --r)
-                if (w[r] > 0.0) {
-                    c = r;
-                    break;
-                }
+    if (t < K) {
+        const double scale = 1.0 / (double)(1u << (K - 2));
+        double v[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double* q = S.part[3 * t + c];
+            v[c] = ((q[0] + q[1]) + (q[2] + q[3])) * scale;
         }
-        drawn[blockIdx.x] = c;
-        tv_est[blockIdx.x] = total > 0.0 ? sums[1] / total : 0.0;
+        S.draw.mr[t] = v[0];
+        S.draw.mi[t] = v[1];
+        S.draw.ma[t] = __builtin_sqrt(v[0] * v[0] + v[1] * v[1]);
+        // kappa u (n + sqrt(Q)) of the K - 1 columns, Q = 1
+        S.draw.me[t] = S.draw.ma[t] > 0.0 ? v[2] / S.draw.ma[t] * (double)K * 0x1.0p-53 : __builtin_inf();
     }
+    __syncthreads();
+}
+
+template <int K>
+__device__ __forceinline__ void early_minors_of(int k, EarlyShared& S)
+{
+    if constexpr (K <= kEarlySteps) {
+        if (k == K) early_minors<K>(S);
+        else early_minors_of<K + 1>(k, S);
+    }
+}
+
+__global__ __launch_bounds__(kCCThreads) void cc_early_kernel(const CCEarly* __restrict__ early,
+                                                              const int32_t* __restrict__ pi,
+                                                              const double* __restrict__ us,
+                                                              int32_t* __restrict__ drawn, double* __restrict__ tv_est)
+{
+    __shared__ EarlyShared S;
+    const CCEarly e = early[blockIdx.x];
+    if ((int)threadIdx.x < e.steps) S.draw.p[threadIdx.x] = pi[e.pi_off + threadIdx.x];
+    __syncthreads();
+    double tv = 0.0;
+    for (int k = 1; k <= e.steps; ++k) {
+        if (k > 1) early_minors_of<2>(k, S);
+        tv += cc_draw(S.draw, e.A, e.rows, e.n, k, us[e.out_off + k - 1]);
+        const int c = S.draw.choice;
+        if ((int)threadIdx.x < e.steps) {
+            const double* x = e.A + 2 * ((size_t)c * e.n + S.draw.p[threadIdx.x]);
+            S.row[k - 1][threadIdx.x][0] = x[0];
+            S.row[k - 1][threadIdx.x][1] = x[1];
+        }
+        if (threadIdx.x == 0) drawn[e.out_off + k - 1] = c;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) tv_est[blockIdx.x] = tv;
 }
 
 hipError_t launch_build_job_matrix(const double* U, int m, const int32_t* cols, int n, double se, double sl, int lossy,
@@ -132,6 +296,14 @@ hipError_t launch_build_job_matrix(const double* U, int m, const int32_t* cols, 
     if (total == 0) return hipSuccess;
     const int blocks = (total + 255) / 256;
     hipLaunchKernelGGL(build_job_matrix_kernel, dim3(blocks), dim3(256), 0, s, U, m, cols, n, se, sl, lossy, A);
+    return hipGetLastError();
+}
+
+hipError_t launch_cc_early(uint32_t samples, const CCEarly* early, const int32_t* pi, const double* us, int32_t* drawn,
+                           double* tv_est, hipStream_t s)
+{
+    if (samples == 0) return hipSuccess;
+    hipLaunchKernelGGL(cc_early_kernel, dim3(samples), dim3(kCCThreads), 0, s, early, pi, us, drawn, tv_est);
     return hipGetLastError();
 }
 

@@ -22,6 +22,22 @@ struct CCStep {
     double u;
 };
 
+// A sample's first `steps` (at most kEarlySteps) steps in one launch: columns
+// pi[pi_off .. pi_off+steps), uniforms us[out_off ..), rows drawn to
+// drawn[out_off ..), tv_est the sum of the steps' estimates (per sample).
+constexpr int kEarlySteps = 14;
+struct CCEarly {
+    const double* A;
+    int32_t rows;
+    int32_t n;
+    int32_t steps;
+    uint32_t pi_off;
+    uint32_t out_off;
+    uint32_t pad;
+};
+hipError_t launch_cc_early(uint32_t samples, const CCEarly* early, const int32_t* pi, const double* us, int32_t* drawn,
+                           double* tv_est, hipStream_t s);
+
 hipError_t launch_build_job_matrix(const double* U, int m, const int32_t* cols, int n, double se, double sl, int lossy,
                                    double* A, hipStream_t s);
 // minor_err[2 q] is the relative error estimate of minors[q] (the diagnostics

@@ -289,12 +289,33 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
     std::vector<int32_t> pis;
     std::vector<uint32_t> slots;            // result index of each minor
     std::vector<size_t>& act_of_step = p.act_of_step;
+    std::vector<CCEarly> early;             // samples at their start
+    std::vector<double> us;                 // the uniforms of their first steps
+    p.addends = addends;
     uint64_t nres = 0;
     for (size_t ai = 0; ai < act.size(); ++ai) {
         CCJob& J = *act[ai].job;
         CCSample& S = J.samples[(size_t)act[ai].s];
         if (J.n == 0 || S.k > S.steps) continue;
         const int k = S.k;
+        if (k == 1) {
+            CCEarly e;
+            std::memset(&e, 0, sizeof e);
+            e.A = J.A.as<double>();
+            e.rows = J.rows;
+            e.n = J.n;
+            e.steps = std::min(S.steps, kEarlySteps);
+            e.pi_off = (uint32_t)pis.size();
+            e.out_off = (uint32_t)us.size();
+            for (int l = 0; l < e.steps; ++l) {
+                pis.push_back(S.pi[(size_t)l]);
+                us.push_back((double)(splitmix64_draw(S.key, (uint64_t)(J.n - 1 + l)) >> 11) * 0x1.0p-53);
+            }
+            early.push_back(e);
+            p.act_of_early.push_back(ai);
+            p.early_steps.push_back(e.steps);
+            continue;
+        }
         CCStep st;
         std::memset(&st, 0, sizeof st);
         st.A = J.A.as<double>();
@@ -345,33 +366,49 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
         steps.push_back(st);
         act_of_step.push_back(ai);
     }
-    if (steps.empty()) return BBFG_OK;
-    RunResult rr;
-    if (!items.empty()) BBFG_TRY(run_perms(c, w, items, 0, false, nullptr, nullptr, &rr, false));
-    p.has_items = !items.empty();
+    if (steps.empty() && early.empty()) return BBFG_OK;
 
     Layout L;
     const size_t o_steps = L.add(sizeof(CCStep) * steps.size());
+    const size_t o_first = L.add(sizeof(CCEarly) * early.size());
     const size_t o_pi = L.add(sizeof(int32_t) * pis.size());
+    const size_t o_us = L.add(sizeof(double) * us.size());
     const size_t o_slot = L.add(sizeof(uint32_t) * std::max<size_t>(1, slots.size()));
     const size_t o_drawn = L.add(sizeof(int32_t) * steps.size());
     const size_t o_tv = L.add(sizeof(double) * steps.size());
+    p.o_early = L.add(sizeof(int32_t) * us.size());
+    p.o_early_tv = L.add(sizeof(double) * early.size());
     BBFG_TRY(w.cc_hmeta.ensure(L.size));
     BBFG_TRY(w.cc_meta.ensure(L.size));
     char* H = w.cc_hmeta.as<char>();
     char* D = w.cc_meta.as<char>();
-    std::memcpy(H + o_steps, steps.data(), sizeof(CCStep) * steps.size());
-    std::memcpy(H + o_pi, pis.data(), sizeof(int32_t) * pis.size());
-    if (!slots.empty()) std::memcpy(H + o_slot, slots.data(), sizeof(uint32_t) * slots.size());
-    // a short image is read from pinned host memory; the draws go back there.
-    // The minors' diagnostics follow their nres results (run_perms).
+    auto put = [H](size_t off, const void* src, size_t bytes) {
+        if (bytes) std::memcpy(H + off, src, bytes);
+    };
+    put(o_steps, steps.data(), sizeof(CCStep) * steps.size());
+    put(o_first, early.data(), sizeof(CCEarly) * early.size());
+    put(o_pi, pis.data(), sizeof(int32_t) * pis.size());
+    put(o_us, us.data(), sizeof(double) * us.size());
+    put(o_slot, slots.data(), sizeof(uint32_t) * slots.size());
+    // a short image is read from pinned host memory; the draws go back there
     const char* M = H;
     if (o_drawn > kShortImageBytes) {
         BBFG_HIP(hipMemcpyAsync(D, H, o_drawn, hipMemcpyHostToDevice, s));
         M = D;
     }
-    BBFG_HIP(launch_cc_weights((uint32_t)steps.size(), reinterpret_cast<const CCStep*>(M + o_steps),
-                               reinterpret_cast<const int32_t*>(M + o_pi),
+    const int32_t* pi_dev = reinterpret_cast<const int32_t*>(M + o_pi);
+    // the walks are timed; the early launch is where there are none
+    const bool time_early = items.empty() && !early.empty();
+    if (time_early) BBFG_HIP(hipEventRecord(w.ev0, s));
+    BBFG_HIP(launch_cc_early((uint32_t)early.size(), reinterpret_cast<const CCEarly*>(M + o_first), pi_dev,
+                             reinterpret_cast<const double*>(M + o_us), reinterpret_cast<int32_t*>(H + p.o_early),
+                             reinterpret_cast<double*>(H + p.o_early_tv), s));
+    if (time_early) BBFG_HIP(hipEventRecord(w.ev1, s));
+    RunResult rr;
+    if (!items.empty()) BBFG_TRY(run_perms(c, w, items, 0, false, nullptr, nullptr, &rr, false));
+    p.has_items = !items.empty() || time_early;
+    // the minors' diagnostics follow their nres results (run_perms)
+    BBFG_HIP(launch_cc_weights((uint32_t)steps.size(), reinterpret_cast<const CCStep*>(M + o_steps), pi_dev,
                                reinterpret_cast<const uint32_t*>(M + o_slot), w.results.as<double>(),
                                w.results.as<double>() + 2 * nres, reinterpret_cast<int32_t*>(H + o_drawn),
                                reinterpret_cast<double*>(H + o_tv), s));
@@ -382,6 +419,30 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
     return BBFG_OK;
 }
 
+namespace {
+
+// Addends and algorithmic flops of early steps 2 .. steps, counted as the walks
+// of the other steps are: over row multiplicities, prod (M'_k + 1) addends.
+void count_early(const CCJob& J, const int32_t* drawn, int steps, CCPending& p)
+{
+    std::vector<int> count((size_t)J.rows, 0);
+    double prod = 1.0;  // prod (M_k + 1)
+    int bunched = 0;  // rows of multiplicity above one
+    for (int k = 2; k <= steps; ++k) {
+        int& c = count[(size_t)drawn[k - 2]];
+        prod *= (c + 2.0) / (c + 1.0);
+        ++c;
+        if (c == 2) ++bunched;
+        int least = kMaxN;  // the pivot's multiplicity
+        for (int i = 0; i < k - 1; ++i) least = std::min(least, count[(size_t)drawn[i]]);
+        const double addends = std::nearbyint(prod / (least + 1.0) * least);
+        if (p.addends) *p.addends += (uint64_t)k * (uint64_t)addends;
+        p.flops += addends * minors_flops(k, bunched > 0);
+    }
+}
+
+}  // namespace
+
 int cc_step_end(Workspace& w, std::vector<ActiveSample>& act, CCPending& p, double* kernel_ms, double* flops)
 {
     if (!p.queued) return BBFG_OK;
@@ -391,6 +452,18 @@ int cc_step_end(Workspace& w, std::vector<ActiveSample>& act, CCPending& p, doub
         float ms = 0.f;
         BBFG_HIP(hipEventElapsedTime(&ms, w.ev0, w.ev1));
         *kernel_ms += ms;
+    }
+    const int32_t* first = reinterpret_cast<const int32_t*>(w.cc_hmeta.as<char>() + p.o_early);
+    const double* first_tv = reinterpret_cast<const double*>(w.cc_hmeta.as<char>() + p.o_early_tv);
+    for (size_t i = 0; i < p.act_of_early.size(); ++i) {
+        ActiveSample& a = act[p.act_of_early[i]];
+        CCSample& S = a.job->samples[(size_t)a.s];
+        count_early(*a.job, first, p.early_steps[i], p);
+        S.prefix.assign(first, first + p.early_steps[i]);
+        first += p.early_steps[i];
+        S.tv += first_tv[i];
+        S.k = 1 + p.early_steps[i];
+        if (S.k > S.steps) finish_sample(*a.job, a.s);
     }
     if (flops) *flops += p.flops;
     const int32_t* drawn = reinterpret_cast<const int32_t*>(w.cc_hmeta.as<char>() + p.o_drawn);
@@ -442,7 +515,9 @@ int run_job(Context& c, CCJob& job, int32_t* out_occupation, bbfg_info* info)
             if (st > 0) act.push_back({&job, s});  // an empty sample is finished at its start
             max_steps = std::max(max_steps, st);
         }
-        for (int k = 1; k <= max_steps; ++k) BBFG_TRY(cc_step(c, act, &kms, &adds, nullptr, nullptr, &fl));
+        // the first launch takes every sample through its early steps
+        for (int k = std::min(max_steps, kEarlySteps); k <= max_steps; ++k)
+            BBFG_TRY(cc_step(c, act, &kms, &adds, nullptr, nullptr, &fl));
     }
     std::memcpy(out_occupation, job.out.data(), sizeof(int32_t) * job.out.size());
     if (info) {

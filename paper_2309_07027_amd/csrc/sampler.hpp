@@ -102,14 +102,19 @@ void cc_start_sample(CCJob& job, int s);
 
 // One step of every listed sample, in two halves so that a caller can prepare
 // another step while this one runs:
-//   cc_step_begin queues (in workspace w, on the current stream) all the
-//     samples' minors in one batched leave-one-column-out launch, then one
+//   cc_step_begin queues (in workspace w, on the current stream) the first
+//     steps of samples at their start in one launch (cc_early_kernel), all the
+//     other samples' minors in one batched leave-one-column-out launch, then one
 //     weights-and-draw launch and the download of the draws;
 //   cc_step_end waits for them and applies the draws.  Finished samples are
 //     written to job.out and counted in job.finished.
 // Between the two calls w, the samples and their jobs must stay untouched.
 struct CCPending {
     std::vector<size_t> act_of_step;  // step i advances act[act_of_step[i]]
+    std::vector<size_t> act_of_early; // early sample i is act[act_of_early[i]], its steps ...
+    std::vector<int> early_steps;     // ... in one launch
+    size_t o_early = 0, o_early_tv = 0;  // offsets of their draws and estimates in w.cc_hmeta
+    uint64_t* addends = nullptr;      // accumulates the early steps' addends (nullable)
     size_t o_drawn = 0;               // offset of the draws in w.cc_hmeta
     size_t o_tv = 0;                  // offset of the steps' error estimates in w.cc_hmeta
     bool has_items = false;           // a minors launch was queued (timed by w.ev0/ev1)
