@@ -109,9 +109,12 @@ int single_perm(const bbfg_c128* A, int32_t n_rows, const int32_t* row_mult, int
     items[0].n = n_cols;
     items[0].mult = row_mult;
     BBFG_TRY(get_plan(*c, row_mult, n_rows, n_cols, 0, PLAN_SINGLE, &items[0].plan, 0, ryser));
-    double res[2], diag[2];
+    double res[4];
+    double* diag = res + 2;
     RunResult rr;
-    BBFG_TRY(run_perms(*c, items, 0, true, res, diag, &rr));
+    bool done = false;
+    BBFG_TRY(run_short(*c, c->ws, items[0], res, &rr, &done));
+    if (!done) BBFG_TRY(run_perms(*c, items, 0, true, res, diag, &rr));
     if (info) {
         bool mult = false;
         for (int32_t i = 0; i < n_rows; ++i) mult = mult || row_mult[i] > 1;

@@ -133,6 +133,27 @@ struct PrepItem {
 };
 
 // ---------------------------------------------------------------------------
+// short single permanents (walk_short.hip)
+// ---------------------------------------------------------------------------
+constexpr int kShortMaxN = 32;                // most columns, hence kept rows
+constexpr uint32_t kShortMaxUnits = 2048;
+constexpr uint32_t kShortCounters = 16;
+constexpr uint32_t kShortLdsBytes = 40 << 10;  // rows and +-2a rows of a wavefront
+
+// Everything one short permanent needs, passed by value with its launch.
+struct ShortArgs {
+    PermDesc d;               // its table resident, its offsets zero
+    RowInfo rows[kShortMaxN];
+    uint32_t src_row[kShortMaxN];  // kept row -> row of src
+    const double* src;        // rows of ld complex elements
+    const double* binom;
+    double* partials;
+    uint32_t* done;           // counters of finished work groups; zero between launches
+    double* out;              // value and diagnostics (pinned host memory)
+    uint32_t ld;
+};
+
+// ---------------------------------------------------------------------------
 // pair walk (pair_core.hpp)
 // ---------------------------------------------------------------------------
 constexpr int kPairBits = 4;                  // inner binary digits

@@ -31,6 +31,9 @@ const void* walk_minors_fn_b30();
 const void* walk_minors_fn_b32();
 const void* walk_minors_fn_b48();
 hipError_t launch_walk_minors(int bucket, uint32_t grid, hipStream_t s, const WalkArgs& A);
+// a short single permanent in one launch (walk_short.hip)
+uint32_t walk_short_lds(int n, int r);
+hipError_t launch_walk_short(hipStream_t s, const ShortArgs& A);
 // leave-one-column-out walk over pairs, np pairs of columns a wavefront at most
 const void* minor_pairs_fn(int np);
 const void* minor_pairs_fn_b3();

@@ -406,7 +406,8 @@ int build_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t slots, cons
     if (pp.l_batch > 0) {
         units = (total + pp.l_batch - 1) / pp.l_batch;
     } else if (total < S * pp.l_floor) {
-        units = (total + pp.l_floor - 1) / pp.l_floor;
+        const uint64_t len = std::min(pp.l_floor, std::max(pp.l_least, total / pp.u_short));
+        units = (total + len - 1) / len;
     } else {
         const double k = std::max(1.0, std::nearbyint((double)total / ((double)S * (double)pp.l_target)));
         units = S * (uint64_t)k;

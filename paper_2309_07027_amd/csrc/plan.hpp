@@ -15,7 +15,12 @@ struct PlanParams {
     uint32_t q_max = 4096;     // largest Gray block length (rows of multiplicity <= 3)
     uint32_t q_max_heavy = 512;  // largest Gray block length when some M'_k > 3
     // single launches: units fill every resident wavefront slot when the sum allows
-    uint64_t l_floor = 16;     // shortest unit (positions per lane) of a single launch
+    // shorter ones: units between l_least and l_floor positions, about u_short of
+    // them in between (a unit's start costs as much as several positions: 20
+    // columns, 2^19 addends: 49.6, 46.7, 49.2 us a call with units of 16, 8, 4)
+    uint64_t l_least = 4;
+    uint64_t l_floor = 16;
+    uint64_t u_short = 1024;
     uint64_t l_target = 1024;  // unit length of sums larger than one round of slots
     // batched launches: units of a fixed length, so an item's split depends on its
     // own shape only (0 = use the single-launch rule)

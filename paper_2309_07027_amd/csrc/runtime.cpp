@@ -123,6 +123,13 @@ int Workspace::init()
     if (!ev1) BBFG_HIP(hipEventCreate(&ev1));
     if (!done) BBFG_HIP(hipEventCreateWithFlags(&done, hipEventDisableTiming));
     BBFG_TRY(counter.ensure(256));
+    if (!short_done.p) {
+        const size_t bytes = sizeof(uint32_t) * (1 + kShortCounters) * kCounterStride;
+        BBFG_TRY(short_done.ensure(bytes));
+        // zero here, and again after each launch that counts in it
+        BBFG_HIP(hipMemset(short_done.p, 0, bytes));
+        BBFG_HIP(hipDeviceSynchronize());
+    }
     return BBFG_OK;
 }
 
@@ -384,6 +391,26 @@ int flush_plans(Context& c)
 // ---------------------------------------------------------------------------
 // the permanent engine
 // ---------------------------------------------------------------------------
+namespace {
+
+// The fields of a descriptor that depend on its plan alone.
+void fill_walk_desc(PermDesc& d, const HostPlan& p, int n_cols, bool f32)
+{
+    d.units_per_group = p.units_per_group;
+    d.span = p.span;
+    d.n = n_cols;
+    d.r = p.r;
+    d.Q = p.Q;
+    d.lane_product = p.lane_product;
+    d.groups = p.groups;
+    d.scale = std::ldexp(1.0, p.scale_log2);
+    d.err_coeff = p.err_coeff * (f32 ? 0x1.0p-24 : 0x1.0p-53);
+    d.col_pow = 1;
+    d.mag_every = 1;
+}
+
+}  // namespace
+
 uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles)
 {
     const PairPlan& pp = *p.pair;
@@ -413,6 +440,50 @@ uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint6
     q.weight_off = take(q.mid);
     q.const_off = take((uint64_t)q.np * 2 * kPairConsts);
     return q.mid;
+}
+
+int run_short(Context& c, Workspace& w, const PermItem& item, double* out, RunResult* rr, bool* done)
+{
+    *done = false;
+    const HostPlan& p = *item.plan;
+    if (p.pair || p.n > kShortMaxN || p.units > kShortMaxUnits || walk_short_lds(p.n, p.r) > kShortLdsBytes ||
+        item.row_map || item.col_map || item.targets || item.col_pow)
+        return BBFG_OK;
+    hipStream_t s = current_stream();
+    auto te = c.dev_tables.find(p.table.get());
+    if (te == c.dev_tables.end()) return BBFG_OK;
+    if (te->second.ready && te->second.stream != s) {
+        if (hipEventQuery(te->second.ready.get()) != hipSuccess) return BBFG_OK;
+        te->second.ready.reset();
+    }
+    BBFG_TRY(w.partials.ensure(sizeof(double) * kPartialDoubles * (size_t)p.units));
+    BBFG_TRY(w.hres.ensure(sizeof(double) * 4));
+    ShortArgs A;
+    std::memset(&A, 0, sizeof A);
+    A.d.tab = te->second.dev;
+    fill_walk_desc(A.d, p, p.n, false);
+    A.d.units = p.units;
+    for (int k = 0; k < p.r; ++k) {
+        A.rows[k] = p.rows[(size_t)k];
+        A.src_row[k] = (uint32_t)p.src_row[(size_t)k];
+    }
+    A.src = item.src + 2 * item.src_off;
+    A.ld = item.ld;
+    A.binom = c.binom;
+    A.partials = w.partials.as<double>();
+    A.done = w.short_done.as<uint32_t>();
+    A.out = w.hres.as<double>();
+    BBFG_HIP(hipEventRecord(w.ev0, s));
+    BBFG_HIP(launch_walk_short(s, A));
+    BBFG_HIP(hipEventRecord(w.ev1, s));
+    BBFG_HIP(hipStreamSynchronize(s));
+    std::memcpy(out, w.hres.p, sizeof(double) * 4);
+    float ms = 0.f;
+    BBFG_HIP(hipEventElapsedTime(&ms, w.ev0, w.ev1));
+    rr->kernel_ms = ms;
+    rr->units = p.units;
+    *done = true;
+    return BBFG_OK;
 }
 
 int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, bool single, double* out_host,
@@ -626,16 +697,8 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         d.tab = p.slot_table;
         d.unit_base = unit_base[i];
         d.units = units_of(items[i]);
-        d.units_per_group = p.units_per_group;
-        d.span = p.span;
+        fill_walk_desc(d, p, nc, f32 != 0);
         d.rowinfo_off = (uint32_t)p.slot_rowinfo;
-        d.n = nc;
-        d.r = p.r;
-        d.Q = p.Q;
-        d.lane_product = p.lane_product;
-        d.groups = p.groups;
-        d.scale = std::ldexp(1.0, p.scale_log2);
-        d.err_coeff = p.err_coeff * (f32 ? 0x1.0p-24 : 0x1.0p-53);
         d.part_base = part_base[i];
         d.targets = (uint32_t)items[i].targets;
         d.res_base = res_base[i];

@@ -106,7 +106,7 @@ struct Layout {
 // workspace holds one evaluation at a time (the device context has one, the
 // sampling server two, so that it can prepare one step while another runs).
 struct Workspace {
-    DevBuf arena_d, arena_f, meta, partials, results, counter, cc_meta, pair_tables;
+    DevBuf arena_d, arena_f, meta, partials, results, counter, cc_meta, pair_tables, short_done;
     PinnedBuf hmeta, hres, cc_hmeta;
     hipEvent_t ev0 = nullptr, ev1 = nullptr, done = nullptr;
     Workspace() = default;
@@ -273,6 +273,10 @@ uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint6
 // w.results.
 int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, bool single, double* out_host,
               double* diag_host, RunResult* rr, bool sync = true, bool use_graph = false);
+// Evaluates one plain FP64 permanent (no maps, no column multiplicities) in one
+// launch when it is short and its Gray table is resident; *done tells whether it
+// did.  out: value and diagnostics (4 doubles).
+int run_short(Context& c, Workspace& w, const PermItem& item, double* out, RunResult* rr, bool* done);
 inline int run_perms(Context& c, std::vector<PermItem>& items, int f32, bool single, double* out_host,
                      double* diag_host, RunResult* rr, bool sync = true, bool use_graph = false)
 {

@@ -169,59 +169,112 @@ struct RowsOf<float> {
     static BBFG_FN const float* a2(const WalkArgs& A) { return A.a2f; }
 };
 
+// Sign count of a row that is the same for every lane (high and low digits; 0
+// for the others) at block h, position t.
+BBFG_FN uint32_t uniform_delta(const RowInfo& x, uint64_t h, uint32_t t)
+{
+    if (x.kind == ROW_HIGH) return digit_of(h, x.stride, x.radix);
+    if (x.kind != ROW_LOW) return 0;
+    const uint32_t dg = (t / x.stride) % x.radix;
+    const uint32_t q = t / (x.stride * x.radix);
+    return (q & 1u) ? (x.radix - 1u - dg) : dg;
+}
+
+// (-1)^Delta C(M', Delta), an exact integer.
+template <typename Table>
+BBFG_FN double signed_binom(Table binom, int32_t mp, uint32_t delta)
+{
+    const double b = binom[mp * kBinomDim + (int)delta];
+    return (delta & 1u) ? -b : b;
+}
+
+// coef times row k (N complex) added to the column sums.
+template <int N, typename Real, typename Rows>
+BBFG_FN void seed_row(Rows rows, int k, int coef, Real* re, Real* im)
+{
+    const Real c = (Real)coef;
+    Rows row = rows + 2 * (size_t)k * N;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        re[j] = fmar(c, (Real)row[2 * j], re[j]);
+        im[j] = fmar(c, (Real)row[2 * j + 1], im[j]);
+    }
+}
+
 // Column sums at block h, position t, for the lane with lane index lane_idx;
 // also the lane's weight for its LANE and HIGH digits:
-// w = prod (-1)^Delta C(M', Delta).
-template <int N, typename Real>
-BBFG_FN void seed(const WalkArgs& A, const PermDesc& d, uint32_t lane_idx, uint64_t h, uint32_t t, Real* re,
-                  Real* im, double& w)
+// w = prod (-1)^Delta C(M', Delta), an integer below 2^53, so exact in any order.
+// rows: the kept rows (r x N complex).
+// BY_LANES (device): lane k of the wavefront decodes row k, all rows at once, and
+// the loop over the rows broadcasts.  Where few wavefronts are resident that
+// takes the rows' records and divisions out of the chain; where many are, the
+// scalar loads are hidden anyway and the 4096-item batches ran 2 % slower.
+template <int N, typename Real, bool BY_LANES, typename Rows>
+BBFG_FN void seed_from(Rows rows, const WalkArgs& A, const PermDesc& d, uint32_t lane_idx, uint64_t h, uint32_t t,
+                       Real* re, Real* im, double& w)
 {
-    kptr<RowInfo> ri = kconst(A.rowinfo + d.rowinfo_off);
-    kptr<Real> rows = kconst(RowsOf<Real>::a(A) + 2 * d.a_off);
-    kptr<double> binom = kconst(A.binom);
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         re[j] = Real(0);
         im[j] = Real(0);
     }
     w = 1.0;
-    for (int k = 0; k < d.r; ++k) {
-        RowInfo x;
-        x.base = ri[k].base;
-        x.kind = ri[k].kind;
-        x.radix = ri[k].radix;
-        x.stride = ri[k].stride;
-        x.mp = ri[k].mp;
-        uint32_t delta = 0;
-        if (x.kind == ROW_LANE) {
-            delta = (lane_idx / x.stride) % x.radix;
-        } else if (x.kind == ROW_HIGH) {
-            delta = digit_of(h, x.stride, x.radix);
-        } else if (x.kind == ROW_LOW) {
-            const uint32_t dg = (t / x.stride) % x.radix;
-            const uint32_t q = t / (x.stride * x.radix);
-            delta = (q & 1u) ? (x.radix - 1u - dg) : dg;
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (BY_LANES) {
+        static_assert(kMaxN <= kWave, "a lane per row");
+        const uint32_t self = __lane_id();
+        RowInfo x = {0, ROW_FIXED, 1u, 1u, 0, 0};
+        if (self < (uint32_t)d.r) x = A.rowinfo[d.rowinfo_off + self];
+        const uint32_t du = uniform_delta(x, h, t);
+        const double wu = x.kind == ROW_HIGH ? signed_binom(A.binom, x.mp, du) : 1.0;
+        const int cu = x.base - 2 * (int)du;
+        for (int k = 0; k < d.r; ++k) {
+            const int kind = __builtin_amdgcn_readlane(x.kind, k);
+            int c = __builtin_amdgcn_readlane(cu, k);
+            if (kind == ROW_LANE) {
+                const uint32_t stride = (uint32_t)__builtin_amdgcn_readlane((int)x.stride, k);
+                const uint32_t radix = (uint32_t)__builtin_amdgcn_readlane((int)x.radix, k);
+                const int32_t mp = __builtin_amdgcn_readlane(x.mp, k);
+                const uint32_t delta = (lane_idx / stride) % radix;
+                if (mp <= 1) w = (delta & 1u) ? -w : w;  // C(1, Delta) = 1: no load
+                else w *= signed_binom(A.binom, mp, delta);
+                c -= 2 * (int)delta;
+            } else if (kind == ROW_HIGH) {
+                const uint64_t bits = __builtin_bit_cast(uint64_t, wu);
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, k);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), k);
+                w *= __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+            }
+            seed_row<N, Real>(rows, k, c, re, im);
         }
-        if (x.kind == ROW_LANE || x.kind == ROW_HIGH) {
-            const double b = binom[x.mp * kBinomDim + (int)delta];
-            w *= (delta & 1u) ? -b : b;
-        }
-        const Real coef = (Real)(x.base - 2 * (int)delta);
-        kptr<Real> row = rows + 2 * (size_t)k * N;
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            re[j] = fmar(coef, (Real)row[2 * j], re[j]);
-            im[j] = fmar(coef, (Real)row[2 * j + 1], im[j]);
-        }
+        return;
     }
+#endif
+    kptr<RowInfo> ri = kconst(A.rowinfo + d.rowinfo_off);
+    kptr<double> binom = kconst(A.binom);
+    for (int k = 0; k < d.r; ++k) {
+        const RowInfo x = {ri[k].base, ri[k].kind, ri[k].radix, ri[k].stride, ri[k].mp, 0};
+        const uint32_t delta = x.kind == ROW_LANE ? (lane_idx / x.stride) % x.radix : uniform_delta(x, h, t);
+        if (x.kind == ROW_LANE || x.kind == ROW_HIGH) w *= signed_binom(binom, x.mp, delta);
+        seed_row<N, Real>(rows, k, x.base - 2 * (int)delta, re, im);
+    }
+}
+
+template <int N, typename Real>
+BBFG_FN void seed(const WalkArgs& A, const PermDesc& d, uint32_t lane_idx, uint64_t h, uint32_t t, Real* re,
+                  Real* im, double& w)
+{
+    seed_from<N, Real, false>(kconst(RowsOf<Real>::a(A) + 2 * d.a_off), A, d, lane_idx, h, t, re, im, w);
 }
 
 // One work unit of permanent d, for one lane: the lane's sum of weighted
 // addends and the sum of their magnitudes (|re| + |im|).  POW: each of the N
 // columns has multiplicity d.col_pow, the product is (prod_j c_j)^col_pow.
-template <int N, typename Real, bool POW = false>
-BBFG_FN void walk_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, uint32_t lane, double& out_r,
-                       double& out_i, double& out_a)
+// a, a2: the kept rows and the +-2a rows; tab(t): the Gray table entry of
+// position t; BY_LANES: how the sums are seeded.
+template <int N, typename Real, bool POW, bool BY_LANES, typename Rows, typename Tab>
+BBFG_FN void walk_unit_from(Rows a, Rows a2, Tab tab, const WalkArgs& A, const PermDesc& d, uint32_t u_local,
+                            uint32_t lane, double& out_r, double& out_i, double& out_a)
 {
     const uint32_t upg = (uint32_t)d.units_per_group;
     const uint32_t g = u_local / upg;
@@ -234,8 +287,6 @@ BBFG_FN void walk_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, u
     const bool valid = lane_idx < d.lane_product;
     if (!valid) lane_idx = 0;
 
-    kptr<TabEntry> tab = kconst(d.tab);
-    kptr<Real> a2 = kconst(RowsOf<Real>::a2(A) + 2 * d.a2_off);
     const uint32_t cpow = POW ? uniform_u32(d.col_pow) : 1u;
     const uint32_t Q = d.Q;
 
@@ -247,22 +298,23 @@ BBFG_FN void walk_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, u
         const uint64_t bend = (h + 1) * (uint64_t)Q;
         const uint32_t t1 = (uint32_t)(((lin1 < bend) ? lin1 : bend) - h * Q);
         double w;
-        seed<N, Real>(A, d, lane_idx, h, t0, re, im, w);
+        seed_from<N, Real, BY_LANES>(a, A, d, lane_idx, h, t0, re, im, w);
         if (!valid) w = 0.0;
         double sr, si, sa;
         {
             Real pr, pi;
             cprod<N, Real>(re, im, pr, pi);
             if constexpr (POW) cpow_uint<Real>(pr, pi, cpow);
-            const double s = tab[t0].s;
+            const double s = tab(t0).s;
             sr = s * (double)pr;
             si = s * (double)pi;
             sa = __builtin_fabs(s) * (__builtin_fabs((double)pr) + __builtin_fabs((double)pi));
         }
         for (uint32_t t = t0 + 1; t < t1; ++t) {
-            const uint32_t rowi = uniform_u32(tab[t].row);
-            const double s = tab[t].s;
-            kptr<Real> row = a2 + 2 * (size_t)rowi * N;
+            const TabEntry e = tab(t);
+            const uint32_t rowi = uniform_u32(e.row);
+            const double s = e.s;
+            Rows row = a2 + 2 * (size_t)rowi * N;
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 re[j] += row[2 * j];
@@ -283,6 +335,16 @@ BBFG_FN void walk_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, u
     out_r = accr;
     out_i = acci;
     out_a = acca;
+}
+
+template <int N, typename Real, bool POW = false>
+BBFG_FN void walk_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, uint32_t lane, double& out_r,
+                       double& out_i, double& out_a)
+{
+    kptr<TabEntry> tab = kconst(d.tab);
+    walk_unit_from<N, Real, POW, false>(kconst(RowsOf<Real>::a(A) + 2 * d.a_off), kconst(RowsOf<Real>::a2(A) + 2 * d.a2_off),
+                                 [&](uint32_t t) { return TabEntry{tab[t].row, 0u, tab[t].s}; }, A, d, u_local, lane,
+                                 out_r, out_i, out_a);
 }
 
 // Leave-one-column-out products of one addend, accumulated: with c_j the K

@@ -27,11 +27,12 @@ __device__ __forceinline__ uint32_t item_of_unit(const WalkArgs& A, uint32_t u)
     return uniform_u32(kconst(A.uorder)[lo]);
 }
 
-// Wavefront sum of the per-lane results in double-double (the butterfly leaves
-// the same bits in every lane), then lane 0 stores the unit's partial record.
-__device__ __forceinline__ void store_partial(double* partials, uint64_t slot, double r, double i, double a)
+// Wavefront sums of the per-lane results, (r, i) in double-double; the butterfly
+// leaves the same bits in every lane.
+__device__ __forceinline__ void wave_sum(double r, double i, double& a, ddv& sr, ddv& si)
 {
-    ddv sr = {r, 0.0}, si = {i, 0.0};
+    sr = {r, 0.0};
+    si = {i, 0.0};
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         ddv orr = {__shfl_xor(sr.hi, off), __shfl_xor(sr.lo, off)};
@@ -41,6 +42,13 @@ __device__ __forceinline__ void store_partial(double* partials, uint64_t slot, d
         si = dd_add(si, oi);
         a = a + oa;
     }
+}
+
+// The wavefront's sums, stored by lane 0 as the unit's partial record.
+__device__ __forceinline__ void store_partial(double* partials, uint64_t slot, double r, double i, double a)
+{
+    ddv sr, si;
+    wave_sum(r, i, a, sr, si);
     if ((threadIdx.x & (kWave - 1)) == 0) {
         double* p = partials + slot * kPartialDoubles;
         p[0] = sr.hi;
