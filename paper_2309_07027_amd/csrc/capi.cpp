@@ -184,13 +184,16 @@ try {
         // same shapes and multiplicities as the last batch (and unchanged unit
         // lengths): its plans are reused
         Context::BatchMemo& memo = c->batch_memo;
-        std::vector<int32_t> flat;
-        for (int32_t b = 0; b < batch; ++b)
-            if (n_cols[b] > 0) flat.insert(flat.end(), row_mult_packed + row_mult_offset[b],
-                                           row_mult_packed + row_mult_offset[b] + n_rows[b]);
-        const bool hit = memo.epoch == c->plan_epoch && memo.f32 == precision && memo.n_rows.size() == (size_t)batch &&
-                         std::equal(memo.n_rows.begin(), memo.n_rows.end(), n_rows) &&
-                         std::equal(memo.n_cols.begin(), memo.n_cols.end(), n_cols) && memo.mult == flat;
+        bool hit = memo.epoch == c->plan_epoch && memo.f32 == precision && memo.n_rows.size() == (size_t)batch &&
+                   std::equal(memo.n_rows.begin(), memo.n_rows.end(), n_rows) &&
+                   std::equal(memo.n_cols.begin(), memo.n_cols.end(), n_cols);
+        size_t seen = 0;  // equal row counts: the multiplicities line up item by item
+        for (int32_t b = 0; hit && b < batch; ++b)
+            if (n_cols[b] > 0) {
+                const int32_t* m = row_mult_packed + row_mult_offset[b];
+                hit = std::equal(m, m + n_rows[b], memo.mult.begin() + (ptrdiff_t)seen);
+                seen += (size_t)n_rows[b];
+            }
         std::vector<PermItem> items;
         std::vector<int32_t> idx;
         items.reserve((size_t)batch);
@@ -213,7 +216,10 @@ try {
             memo.f32 = precision;
             memo.n_rows.assign(n_rows, n_rows + batch);
             memo.n_cols.assign(n_cols, n_cols + batch);
-            memo.mult.swap(flat);
+            memo.mult.clear();
+            for (int32_t b = 0; b < batch; ++b)
+                if (n_cols[b] > 0) memo.mult.insert(memo.mult.end(), row_mult_packed + row_mult_offset[b],
+                                                    row_mult_packed + row_mult_offset[b] + n_rows[b]);
             memo.plans.clear();
             for (auto& it : items) memo.plans.push_back(it.plan);
         }

@@ -287,26 +287,79 @@ int load_autotune_file(Context& c, const char* path)
     return count > 0 ? BBFG_OK : set_error(BBFG_EINVAL, "no entries in autotune cache %s", path);
 }
 
+uint64_t PlanIndex::hash(const char* p, size_t n)
+{
+    uint64_t h = 0x9E3779B97F4A7C15ull ^ n;
+    for (; n >= 8; p += 8, n -= 8) {
+        uint64_t x;
+        std::memcpy(&x, p, 8);
+        h = (h ^ x) * 0xBF58476D1CE4E5B9ull;
+        h ^= h >> 29;
+    }
+    uint64_t x = 0;
+    std::memcpy(&x, p, n);
+    h = (h ^ x) * 0x94D049BB133111EBull;
+    return h ^ (h >> 32);
+}
+
+const std::shared_ptr<const HostPlan>* PlanIndex::find(uint64_t h, const char* p, size_t n) const
+{
+    if (slots.empty()) return nullptr;
+    for (size_t i = h & (slots.size() - 1); slots[i].key; i = (i + 1) & (slots.size() - 1))
+        if (slots[i].hash == h && slots[i].key->size() == n && std::memcmp(slots[i].key->data(), p, n) == 0)
+            return slots[i].plan;
+    return nullptr;
+}
+
+void PlanIndex::add(uint64_t h, const std::string* key, const std::shared_ptr<const HostPlan>* plan)
+{
+    if (2 * (used + 1) > slots.size()) {
+        std::vector<Slot> old(std::max<size_t>(1024, 2 * slots.size()));
+        old.swap(slots);
+        used = 0;
+        for (const Slot& o : old)
+            if (o.key) add(o.hash, o.key, o.plan);
+    }
+    size_t i = h & (slots.size() - 1);
+    while (slots[i].key) i = (i + 1) & (slots.size() - 1);
+    slots[i].hash = h;
+    slots[i].key = key;
+    slots[i].plan = plan;
+    ++used;
+}
+
+void PlanIndex::clear()
+{
+    std::vector<Slot>().swap(slots);
+    used = 0;
+}
+
 int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, int mode,
              std::shared_ptr<const HostPlan>* out, int kernel_cols, bool ryser, uint64_t pair_min)
 {
     PlanParams pp = c.params;
     pp.ryser = ryser;
     if (mode == PLAN_BATCH) pp.l_batch = batch_unit_length(c, n_cols, f32);
-    std::string key;
-    key.reserve(32 + 4 * (size_t)n_rows);
-    key.append(reinterpret_cast<const char*>(&n_cols), sizeof n_cols);
-    key.push_back((char)f32);
-    key.push_back(ryser ? 'R' : 'G');
-    key.append(reinterpret_cast<const char*>(&pp.l_batch), sizeof pp.l_batch);
-    key.append(reinterpret_cast<const char*>(&kernel_cols), sizeof kernel_cols);
-    key.append(reinterpret_cast<const char*>(&pair_min), sizeof pair_min);
-    key.append(reinterpret_cast<const char*>(mult), sizeof(int32_t) * (size_t)n_rows);
-    auto it = c.plans.find(key);
-    if (it != c.plans.end()) {
-        *out = it->second;
+    // everything the plan depends on, as bytes
+    thread_local std::vector<char> key;
+    const struct {
+        int32_t n_cols, f32, ryser, kernel_cols;
+        uint64_t l_batch, pair_min;
+    } head = {n_cols, f32, ryser ? 1 : 0, kernel_cols, pp.l_batch, pair_min};
+    const size_t mult_bytes = sizeof(int32_t) * (size_t)n_rows;
+    key.resize(sizeof head + mult_bytes);
+    std::memcpy(key.data(), &head, sizeof head);
+    if (mult_bytes) std::memcpy(key.data() + sizeof head, mult, mult_bytes);
+    const uint64_t hash = PlanIndex::hash(key.data(), key.size());
+    if (const auto* found = c.plan_index.find(hash, key.data(), key.size())) {
+        *out = *found;
         return BBFG_OK;
     }
+    auto remember = [&](const std::shared_ptr<const HostPlan>& plan) {
+        const auto it = c.plans.emplace(std::string(key.data(), key.size()), plan).first;
+        c.plan_index.add(hash, &it->first, &it->second);
+        *out = plan;
+    };
     uint64_t slots = 1;
     if (f32 == kKindMinors && mode == PLAN_SINGLE) {
         // a lone leave-one-column-out walk fills the minors kernel's own
@@ -338,8 +391,7 @@ int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, i
             groups = (uint64_t)per_cu * (uint64_t)c.n_cu;
         }
         if (build_minor_pair_plan(mult, n_rows, n_cols, groups, pp, *p, err, &c.tables)) {
-            c.plans.emplace(key, p);
-            *out = p;
+            remember(p);
             return BBFG_OK;
         }
         if (!err.empty()) return set_error(BBFG_ERANGE, "%s", err.c_str());
@@ -349,8 +401,7 @@ int get_plan(Context& c, const int32_t* mult, int n_rows, int n_cols, int f32, i
     if (f32 == 0 || f32 == kKindCols)
         p->pair = build_pair_plan(*p, kernel_cols > 0 ? kernel_cols : n_cols, mode == PLAN_SINGLE ? (uint32_t)c.n_cu : 0u,
                                   pair_min);
-    c.plans.emplace(key, p);
-    *out = p;
+    remember(p);
     return BBFG_OK;
 }
 
@@ -384,6 +435,7 @@ int flush_plans(Context& c)
     c.tab_used = 0;
     c.tables.tables.clear();
     c.tables.entries = 0;
+    c.plan_index.clear();
     c.plans.clear();
     return BBFG_OK;
 }
@@ -392,6 +444,29 @@ int flush_plans(Context& c)
 // the permanent engine
 // ---------------------------------------------------------------------------
 namespace {
+
+// A positive cost as 16 ordered bits (its exponent and five bits of fraction):
+// what the order of units needs.
+uint16_t coarse_cost(double x)
+{
+    uint64_t bits;
+    std::memcpy(&bits, &x, sizeof bits);
+    return (uint16_t)(bits >> 47);
+}
+
+// Sorts item indices by falling cost, equal ones in their order (two counting
+// passes; comparing through the plans took 0.15 ms for 4096 items).
+void longest_first(const std::vector<uint16_t>& cost, std::vector<size_t>& order)
+{
+    std::vector<size_t> other(order.size());
+    for (int shift = 0; shift < 16; shift += 8) {
+        size_t first[257] = {};
+        for (size_t i : order) ++first[256 - (cost[i] >> shift & 255)];
+        for (int b = 1; b <= 256; ++b) first[b] += first[b - 1];
+        for (size_t i : order) other[first[255 - (cost[i] >> shift & 255)]++] = i;
+        order.swap(other);
+    }
+}
 
 // The fields of a descriptor that depend on its plan alone.
 void fill_walk_desc(PermDesc& d, const HostPlan& p, int n_cols, bool f32)
@@ -605,16 +680,17 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     order_pair.reserve(npair);
     for (size_t i = 0; i < nitem; ++i) (by_pairs(items[i]) ? order_pair : order).push_back(i);
     if (!single) {
-        std::vector<double> cost(nitem);
+        std::vector<uint16_t> cost(nitem);
         for (size_t i = 0; i < nitem; ++i) {
             const HostPlan& p = *items[i].plan;
             const double nc = cols_of(items[i]);
-            if (by_pairs(items[i]) && !minors) cost[i] = (double)p.pair->mid * nc;
-            else cost[i] = (double)p.span / (double)p.units_per_group * (6.0 * nc - 2.0 + 12.0 * items[i].targets);
+            if (by_pairs(items[i]) && !minors) cost[i] = coarse_cost((double)p.pair->mid * nc);
+            else
+                cost[i] = coarse_cost((double)p.span / (double)p.units_per_group *
+                                      (6.0 * nc - 2.0 + 12.0 * items[i].targets));
         }
-        auto longer = [&](size_t x, size_t y) { return cost[x] > cost[y]; };
-        std::stable_sort(order.begin(), order.end(), longer);
-        std::stable_sort(order_pair.begin(), order_pair.end(), longer);
+        longest_first(cost, order);
+        longest_first(cost, order_pair);
     }
     auto units_of = [&](const PermItem& it) {
         return by_pairs(it) && !minors ? it.plan->pair->units : it.plan->units;
@@ -825,13 +901,15 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     double* HR = w.hres.as<double>();
 
     // Everything one evaluation puts on a stream (also what a graph captures):
-    // metadata upload, gather, walks and finalize, whose results go straight to
-    // pinned host memory when the host waits for them.  No memset: the unit
-    // counters are cleared by the gather kernel.  A short metadata image is read
-    // and copied by the gather kernel itself.
+    // metadata upload, gather, walks and finalize.  No memset: the unit counters
+    // are cleared by the gather kernel.  A short metadata image is read and copied
+    // by the gather kernel itself, and a few results that the host waits for go
+    // straight to pinned host memory (many small writes over the bus take longer
+    // than a copy: 4096 results 0.05 ms).
     const bool short_image = off_tabs <= kShortImageBytes;
     const char* M = short_image ? H : D;
-    double* out = sync ? HR : R;
+    const bool direct = sync && nres <= kDirectResults;
+    double* out = direct ? HR : R;
     auto enqueue = [&](hipStream_t q, bool timed) -> int {
         if (!short_image) BBFG_HIP(hipMemcpyAsync(D, H, off_tabs, hipMemcpyHostToDevice, q));
         BBFG_HIP(launch_prep((uint32_t)nitem, q, reinterpret_cast<const PrepItem*>(M + off_prep),
@@ -851,6 +929,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         if (timed) BBFG_HIP(hipEventRecord(w.ev1, q));
         BBFG_HIP(launch_finalize((uint32_t)nres, q, W.descs, reinterpret_cast<const uint32_t*>(D + off_ritem),
                                  W.partials, out, out + 2 * nres));
+        if (sync && !direct) BBFG_HIP(hipMemcpyAsync(HR, R, sizeof(double) * 4 * nres, hipMemcpyDeviceToHost, q));
         return BBFG_OK;
     };
 

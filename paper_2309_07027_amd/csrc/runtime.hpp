@@ -87,6 +87,9 @@ struct PinnedBuf {
 // kernel that needs it first; longer ones, with many items, are copied before.
 constexpr size_t kShortImageBytes = 64 << 10;
 
+// At most so many results are written to pinned host memory by finalize itself.
+constexpr uint64_t kDirectResults = 256;
+
 // Byte layout helper for one upload of several arrays.
 struct Layout {
     size_t size = 0;
@@ -130,6 +133,22 @@ struct DevTable {
     hipStream_t stream = nullptr;
 };
 
+// Lookup of cached plans by the bytes of their key: open addressing over the
+// plans map's own keys and values (stable until the map is cleared).
+struct PlanIndex {
+    struct Slot {
+        uint64_t hash = 0;
+        const std::string* key = nullptr;
+        const std::shared_ptr<const HostPlan>* plan = nullptr;
+    };
+    std::vector<Slot> slots;
+    size_t used = 0;
+    static uint64_t hash(const char* p, size_t n);
+    const std::shared_ptr<const HostPlan>* find(uint64_t h, const char* p, size_t n) const;
+    void add(uint64_t h, const std::string* key, const std::shared_ptr<const HostPlan>* plan);
+    void clear();
+};
+
 // ---- per-device context -------------------------------------------------------
 struct Context {
     int device = -1;
@@ -143,6 +162,7 @@ struct Context {
     std::map<std::pair<int, int>, int> occ_pair;    // (pairs of columns, pow), (-pairs a wavefront of a minors walk, 0) ->
                                                     // work groups per CU
     std::unordered_map<std::string, std::shared_ptr<const HostPlan>> plans;
+    PlanIndex plan_index;
     // Gray tables shared between plans (host), and their device copies:
     // bump-allocated in chunks that are never moved while referenced
     TableCache tables;
