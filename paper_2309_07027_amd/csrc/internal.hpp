@@ -66,7 +66,8 @@ struct PermDesc {
                              //   leave out one of the last G columns (Laplace minors)
     uint32_t res_base;       // index of the first result
     uint32_t col_pow;        // every one of the n (distinct) columns has multiplicity col_pow
-                             //   (Eq. bbfgrepeated): the product is (prod_j c_j)^col_pow
+                             //   (Eq. bbfgrepeated): the product is (prod_j c_j)^col_pow; in a
+                             //   leave-one-column-out walk over pairs, its inner digits (1 or 2)
     uint32_t mag_every;      // leave-one-column-out walks: units whose index in their lane group is
                              //   a multiple of mag_every sample the magnitude estimate (>= 1)
 };
@@ -129,6 +130,7 @@ struct PrepItem {
     int32_t r;
     int32_t f32;
     int32_t rows_only;  // no +-2a rows
+    int32_t digits;     // inner digits of that walk
     int32_t np;         // > 0: the layout of the leave-one-column-out walk over pairs, np pairs a wavefront
 };
 
@@ -214,6 +216,14 @@ constexpr uint64_t kMinorMinAddends = uint64_t(1) << 17;
 // 32, 12.5 with 16; 24 jobs on the server: 52.5, 51.4, 51.1 ms).
 constexpr uint64_t kMinorItemUnits = 64;
 constexpr uint64_t kMinorMinUnit = 16;
+// Two inner digits instead of one: at four pairs a wavefront (25-32 columns),
+// where they fill the 256 registers of two wavefronts per SIMD, and for longer
+// sums.  30 photons: 10.1 -> 9.4 ms, 24 jobs on the server 47.9 -> 45.1 ms; at
+// three pairs one digit and three wavefronts per SIMD are faster, and short sums
+// want the more and shorter steps (24 photons with two throughout: 1.44 -> 1.54
+// ms).
+constexpr int kMinorTwoDigits = 4;
+constexpr uint64_t kMinorTwoAddends = uint64_t(1) << 18;
 constexpr int minor_pairs_per_wave(int K)
 {
     const int np = ((K + 1) / 2 + kMinorWaves - 1) / kMinorWaves;

@@ -61,9 +61,9 @@ __device__ __forceinline__ double minor_coefs(const WalkArgs& A, const PermDesc&
 
 // One unit: the sums of this wavefront's 2 NP targets over the unit's addends,
 // then, for sampled units, the estimate of their magnitude sums (the modulus of
-// the addend at the unit's last position, the inner digit at the lane's parity,
-// times the addends it stands for).
-template <int NP>
+// the addend at the unit's last position, the inner digits at the lane's lowest
+// bits, times the addends it stands for).
+template <int NP, int DIGITS>
 __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -81,17 +81,40 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
 
     constexpr int kCols = 2 * NP;
     const size_t ld = 4 * (size_t)NP * kMinorWaves;                 // doubles per kept row
-    const size_t step_ld = 6 * (size_t)NP * kMinorWaves;            // doubles per step row
+    constexpr int kStep = MinorLane<NP, DIGITS>::kStep;
+    const size_t step_ld = kStep * (size_t)NP * kMinorWaves;        // doubles per step row
     kptr<double> a = kconst(A.a + 2 * d.a_off + wave * (4 * NP));
-    kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + wave * (6 * NP));
+    kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + wave * (kStep * NP));
     kptr<TabEntry> tab = kconst(d.tab);
     const int cols = (int)d.n - (int)wave * kCols;                  // real columns of this wavefront (may be < 0)
     const uint32_t Q = d.Q;
     auto coef = [&](int k) { return (double)S.coef[k][lane]; };
 
-    MinorLane<NP> L;
+    MinorLane<NP, DIGITS> L;
     L.clear();
     uint32_t buf = 0;
+    // e of both x: the weight times the other wavefronts' products
+    auto exchange = [&](double ws, cpx& e0, cpx& e1) {
+        S.prod[buf][wave][0][lane] = L.half[0].all;
+        S.prod[buf][wave][1][lane] = L.half[1].all;
+        __syncthreads();
+        const cpx(*const o0)[2][kWave] = &S.prod[buf][(wave + 1) % kMinorWaves];
+        const cpx(*const o1)[2][kWave] = &S.prod[buf][(wave + 2) % kMinorWaves];
+        const cpx(*const o2)[2][kWave] = &S.prod[buf][(wave + 3) % kMinorWaves];
+        e0 = cmul_uniform(cmul(cmul((*o0)[0][lane], (*o1)[0][lane]), (*o2)[0][lane]), ws);
+        e1 = cmul_uniform(cmul(cmul((*o0)[1][lane], (*o1)[1][lane]), (*o2)[1][lane]), ws);
+        buf ^= 1u;
+    };
+    // K of the two inner digits: the change of D when x' grows
+    double K[DIGITS > 1 ? 2 * NP : 1];
+    if constexpr (DIGITS > 1) {
+        kptr<double> row = steps + (2 * (size_t)(d.r - 2) + 1) * step_ld;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            K[2 * p] = row[kStep * p + 4];
+            K[2 * p + 1] = row[kStep * p + 5];
+        }
+    }
     for (uint64_t lin = lin0; lin < lin1;) {
         const uint64_t h = lin / Q;
         const uint32_t t0 = (uint32_t)(lin - h * Q);
@@ -102,29 +125,27 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         double ws = w * tab[t0].s;
         uint32_t next_row = t0 + 1 < t1 ? uniform_u32(tab[t0 + 1].row) : 0u;
         for (uint32_t t = t0; t < t1; ++t) {
+            cpx e0, e1;
             L.forward();
-            S.prod[buf][wave][0][lane] = L.half[0].all;
-            S.prod[buf][wave][1][lane] = L.half[1].all;
-            __syncthreads();
-            const cpx(*const o0)[2][kWave] = &S.prod[buf][(wave + 1) % kMinorWaves];
-            const cpx(*const o1)[2][kWave] = &S.prod[buf][(wave + 2) % kMinorWaves];
-            const cpx(*const o2)[2][kWave] = &S.prod[buf][(wave + 3) % kMinorWaves];
-            const cpx e0 = cmul_uniform(cmul(cmul((*o0)[0][lane], (*o1)[0][lane]), (*o2)[0][lane]), ws);
-            const cpx e1 = cmul_uniform(cmul(cmul((*o0)[1][lane], (*o1)[1][lane]), (*o2)[1][lane]), ws);
+            exchange(ws, e0, e1);
+            if constexpr (DIGITS > 1) {
+                L.template backward<false>(e0, e1);
+                L.forward_second(K);
+                exchange(-ws, e0, e1);
+            }
             // the next step's changes are fetched under the rest of this step (not
             // earlier: a wait for LDS data waits for scalar loads as well); after
             // the last step they are row 0's, and go into sums that are seeded anew
             BBFG_SCHED_BARRIER();
-            double s[6 * NP];
+            double s[kStep * NP];
             kptr<double> row = steps + (size_t)next_row * step_ld;
 #pragma unroll
-            for (int i = 0; i < 6 * NP; ++i) s[i] = row[i];
+            for (int i = 0; i < kStep * NP; ++i) s[i] = row[i];
             ws = w * tab[t + 1 < t1 ? t + 1 : t].s;
             next_row = uniform_u32(tab[t + 2 < t1 ? t + 2 : t].row);
             BBFG_SCHED_BARRIER();
-            L.backward(e0, e1);
+            L.template backward<true>(e0, e1);
             L.advance(s);
-            buf ^= 1u;
         }
         lin += (uint64_t)(t1 - t0);
         __syncthreads();  // the coefficients and weights may be overwritten
@@ -134,7 +155,7 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         cpx first, second;
-        L.result(p, inner, first, second);
+        L.result(p, inner, ld, first, second);
         if (2 * p < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p, first.r, first.i);
         if (2 * p + 1 < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p + 1, second.r, second.i);
     }
@@ -154,16 +175,21 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
     double mod[kCols], own = 1.0;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const double x = (lane & 1u) ? -2.0 : 0.0;
-        const cpx c1 = {fmar(x, inner[4 * p], L.b1[p].r), fmar(x, inner[4 * p + 1], L.b1[p].i)};
-        const cpx c2 = {fmar(x, inner[4 * p + 2], L.b2[p].r), fmar(x, inner[4 * p + 3], L.b2[p].i)};
+        cpx c1 = L.b1[p], c2 = L.b2[p];
+#pragma unroll
+        for (int i = 0; i < DIGITS; ++i) {
+            const double x = (lane >> i & 1u) ? -2.0 : 0.0;
+            kptr<double> row = inner + -(int64_t)((size_t)i * ld);
+            c1 = {fmar(x, row[4 * p], c1.r), fmar(x, row[4 * p + 1], c1.i)};
+            c2 = {fmar(x, row[4 * p + 2], c2.r), fmar(x, row[4 * p + 3], c2.i)};
+        }
         mod[2 * p] = __builtin_sqrt(fmar(c1.r, c1.r, c1.i * c1.i));
         mod[2 * p + 1] = __builtin_sqrt(fmar(c2.r, c2.r, c2.i * c2.i));
         own *= mod[2 * p] * mod[2 * p + 1];
     }
     S.mag[wave][lane] = own;
     __syncthreads();
-    double lead = 2.0 * (double)(lin1 - lin0) * (double)reps * __builtin_fabs(w * tab[tl].s);
+    double lead = (double)(1 << DIGITS) * (double)(lin1 - lin0) * (double)reps * __builtin_fabs(w * tab[tl].s);
 #pragma unroll
     for (int v = 1; v < kMinorWaves; ++v) lead *= S.mag[(wave + v) % kMinorWaves][lane];
     // leave-one-out products: no division, so zero moduli are harmless
@@ -183,8 +209,15 @@ template <int NPMIN, int NPMAX>
 __device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S)
 {
     if constexpr (NPMIN <= NPMAX) {
-        if (minor_pairs_per_wave(d.n) == NPMIN) minor_pairs_unit<NPMIN>(A, d, u, S);
-        else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S);
+        if (minor_pairs_per_wave(d.n) == NPMIN) {
+            if constexpr (NPMIN == kMinorTwoDigits) {
+                if (d.col_pow == 2) {
+                    minor_pairs_unit<NPMIN, 2>(A, d, u, S);
+                    return;
+                }
+            }
+            minor_pairs_unit<NPMIN, 1>(A, d, u, S);
+        } else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S);
     }
 }
 

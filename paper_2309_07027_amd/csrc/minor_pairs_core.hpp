@@ -33,13 +33,24 @@ namespace bbfg {
 
 // acc + a b
 BBFG_FN void cmac(cpx& acc, cpx a, cpx b) { acc = cfma(a, b, acc); }
+BBFG_FN cpx csub(cpx a, cpx b) { return {a.r - b.r, a.i - b.i}; }
 BBFG_FN cpx cmul_uniform(cpx a, double s) { return {a.r * s, a.i * s}; }
 
-template <int NP>
+// DIGITS: inner binary digits, 1 or 2.  With a second digit x', taken as a second
+// half of the step, b_1 and b_2 serve four addends: y and D move to x' = 1 by
+// their differences (E, and the constant K of the two digits), and the sums over
+// both halves are accumulated at once.
+template <int NP, int DIGITS>
 struct MinorLane {
-    cpx b1[NP], b2[NP], D[NP];         // column sums at x = 0, difference of the product
-    cpx y[NP];                         // product at x = 0
-    cpx acc1[NP], acc2[NP], G[NP];     // sums of Z c_2, Z c_1 and -Z(1)
+    cpx b1[NP], b2[NP], D[NP];         // column sums, difference of the product in x, at x = x' = 0
+    cpx E[DIGITS > 1 ? NP : 1];        // its difference in x'
+    cpx y[NP], v[NP];                  // product at x = 0 and x = 1 of the current half
+    cpx acc1[NP], acc2[NP], G[NP];     // sums of Z c_2, Z c_1, and of the signed Z at x = 1
+    cpx F[DIGITS > 1 ? NP : 1];        // the same at x' = 1
+    cpx S[DIGITS > 1 ? NP : 1];        // the first half's sums
+
+    // doubles per pair of a step: the changes of b_1, b_2, D (and E)
+    static constexpr int kStep = 2 * (2 + DIGITS);
 
     // products over neighbouring pairs at one x
     static constexpr int H = (NP + 1) / 2;
@@ -51,13 +62,22 @@ struct MinorLane {
     BBFG_FN void clear()
     {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) acc1[p] = acc2[p] = G[p] = {0.0, 0.0};
+        for (int p = 0; p < NP; ++p) {
+            acc1[p] = acc2[p] = G[p] = {0.0, 0.0};
+            if constexpr (DIGITS > 1) F[p] = {0.0, 0.0};
+        }
+    }
+
+    static BBFG_FN void digit_step(kptr<double> row, int p, cpx& d1, cpx& d2)
+    {
+        d1 = {-2.0 * row[4 * p], -2.0 * row[4 * p + 1]};
+        d2 = {-2.0 * row[4 * p + 2], -2.0 * row[4 * p + 3]};
     }
 
     // Column sums at one position: coef(k) is kept row k's coefficient, a points
     // at this wavefront's columns of row 0 (rows `ld` doubles apart, columns past
     // the matrix zero; `cols` of the wavefront's 2 NP columns are real).  The last
-    // kept row is the inner digit's, at coefficient +1.
+    // kept row is x's, the one before it x' 's, at coefficient +1.
     template <typename Coef>
     BBFG_FN void seed(kptr<double> a, size_t ld, int r, int cols, Coef coef)
     {
@@ -78,30 +98,53 @@ struct MinorLane {
         }
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const cpx d1 = {-2.0 * row[4 * p], -2.0 * row[4 * p + 1]};
-            const cpx d2 = {-2.0 * row[4 * p + 2], -2.0 * row[4 * p + 3]};
+            cpx d1, d2;
+            digit_step(row, p, d1, d2);
             D[p] = cfma(d1, b2[p], cfma(d2, b1[p], cmul(d1, d2)));
+            if constexpr (DIGITS > 1) {
+                digit_step(row + -(int64_t)ld, p, d1, d2);
+                E[p] = cfma(d1, b2[p], cfma(d2, b1[p], cmul(d1, d2)));
+            }
         }
     }
 
-    // One step of the Gray walk: s holds per pair the change of b_1, b_2 and D.
+    // One step of the Gray walk: s holds per pair the changes.
     BBFG_FN void advance(const double* s)
     {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            b1[p] = cadd(b1[p], s + 6 * p);
-            b2[p] = cadd(b2[p], s + 6 * p + 2);
-            D[p] = cadd(D[p], s + 6 * p + 4);
+            b1[p] = cadd(b1[p], s + kStep * p);
+            b2[p] = cadd(b2[p], s + kStep * p + 2);
+            D[p] = cadd(D[p], s + kStep * p + 4);
+            if constexpr (DIGITS > 1) E[p] = cadd(E[p], s + kStep * p + 6);
         }
     }
 
-    BBFG_FN cpx value(int p, int x) const { return x ? cadd(y[p], D[p]) : y[p]; }
-
-    // This wavefront's product at both x.
+    // This wavefront's product at both x of the first half, or (after backward of
+    // the first) of the second; K: kStep doubles apart, K of the two digits.
     BBFG_FN void forward()
     {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) y[p] = cmul(b1[p], b2[p]);
+        for (int p = 0; p < NP; ++p) {
+            y[p] = cmul(b1[p], b2[p]);
+            v[p] = cadd(y[p], D[p]);
+        }
+        products();
+    }
+    BBFG_FN void forward_second(const double* K)
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            y[p] = cadd(y[p], E[p]);
+            v[p] = cadd(cadd(y[p], D[p]), K + 2 * p);
+        }
+        products();
+    }
+
+    BBFG_FN cpx value(int p, int x) const { return x ? v[p] : y[p]; }
+
+    BBFG_FN void products()
+    {
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
 #pragma unroll
@@ -141,8 +184,9 @@ struct MinorLane {
         }
     }
 
-    // Accumulates both addends; e0, e1: the weight times the other wavefronts'
-    // products (the digit x enters with sign (-1)^x).
+    // Accumulates a half's two addends; e0, e1: the weight (its sign turned in the
+    // second half) times the other wavefronts' products; x enters with (-1)^x.
+    template <bool LAST>
     BBFG_FN void backward(cpx e0, cpx e1)
     {
         cpx z0[NP], z1[NP];
@@ -150,21 +194,36 @@ struct MinorLane {
         others(1, e1, z1);
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const cpx s = {z0[p].r - z1[p].r, z0[p].i - z1[p].i};
-            G[p] = {G[p].r - z1[p].r, G[p].i - z1[p].i};
-            cmac(acc1[p], s, b2[p]);
-            cmac(acc2[p], s, b1[p]);
+            cpx s = csub(z0[p], z1[p]);
+            G[p] = csub(G[p], z1[p]);
+            if constexpr (DIGITS > 1) {
+                if constexpr (!LAST) {
+                    S[p] = s;
+                } else {
+                    F[p] = cadd(F[p], s);
+                    s = cadd(s, S[p]);
+                }
+            }
+            if constexpr (LAST) {
+                cmac(acc1[p], s, b2[p]);
+                cmac(acc2[p], s, b1[p]);
+            }
         }
     }
 
     // The sums over the walked addends of the minors without columns 2p, 2p + 1;
-    // inner points at the inner digit's row.
-    BBFG_FN void result(int p, kptr<double> inner, cpx& first, cpx& second) const
+    // inner points at x's row (x' 's lies ld doubles before).
+    BBFG_FN void result(int p, kptr<double> inner, size_t ld, cpx& first, cpx& second) const
     {
-        const cpx d1 = {-2.0 * inner[4 * p], -2.0 * inner[4 * p + 1]};
-        const cpx d2 = {-2.0 * inner[4 * p + 2], -2.0 * inner[4 * p + 3]};
+        cpx d1, d2;
+        digit_step(inner, p, d1, d2);
         first = cfma(d2, G[p], acc1[p]);
         second = cfma(d1, G[p], acc2[p]);
+        if constexpr (DIGITS > 1) {
+            digit_step(inner + -(int64_t)ld, p, d1, d2);
+            first = cfma(d2, F[p], first);
+            second = cfma(d1, F[p], second);
+        }
     }
 };
 

@@ -426,34 +426,40 @@ bool build_minor_pair_plan(const int32_t* mult, int n_rows, int n_cols, uint64_t
 {
     err.clear();
     if (n_cols + 1 < kMinorMinCols) return false;
-    // the pivot takes one row of multiplicity one, the inner digit another
-    int inner = -1, ones = 0;
+    // the pivot takes one row of multiplicity one, each inner digit another
+    std::vector<int> ones;
     double addends = 1.0;
     for (int i = 0; i < n_rows; ++i) {
-        if (mult[i] == 1) {
-            ++ones;
-            inner = i;
-        }
+        if (mult[i] == 1) ones.push_back(i);
         addends *= mult[i] + 1.0;
     }
     const uint64_t least = pp.l_batch > 0 ? kMinorMinAddendsBatch : kMinorMinAddends;
-    if (ones < 2 || addends / 2.0 <= (double)least) return false;
+    if (ones.size() < 2 || addends / 2.0 <= (double)least) return false;
+    const bool two = ones.size() > 2 && minor_pairs_per_wave(n_cols + 1) == kMinorTwoDigits &&
+                     addends / 2.0 > (double)kMinorTwoAddends;
+    const int digits = two ? 2 : 1;
     std::vector<int32_t> rest(mult, mult + n_rows);
-    rest[(size_t)inner] = 0;
-    if (build_plan(rest.data(), n_rows, n_cols - 1, slots, pp, P, err, cache) != BBFG_OK) return false;
+    for (int i = 0; i < digits; ++i) rest[(size_t)ones[ones.size() - 1 - (size_t)i]] = 0;
+    PlanParams q = pp;
+    q.l_batch = (pp.l_batch + (uint64_t)digits - 1) / (uint64_t)digits;
+    q.l_target = pp.l_target / (uint64_t)digits;  // as many rounds of units (30 columns: 4.0 ms with half of them)
+    if (build_plan(rest.data(), n_rows, n_cols - digits, slots, q, P, err, cache) != BBFG_OK) return false;
     P.n = n_cols;
-    P.n_addends *= 2;
+    P.n_addends <<= digits;
     P.scale_log2 = 1 - n_cols;
     P.err_coeff = (double)n_cols + std::sqrt((double)P.Q);
-    P.src_row.push_back(inner);
-    P.mult.push_back(1);
-    P.rows.push_back(RowInfo{1, ROW_FIXED, 1u, 1u, 1, 0});
-    P.r++;
-    P.minor_pairs = true;
+    for (int i = digits - 1; i >= 0; --i) {
+        P.src_row.push_back(ones[ones.size() - 1 - (size_t)i]);
+        P.mult.push_back(1);
+        P.rows.push_back(RowInfo{1, ROW_FIXED, 1u, 1u, 1, 0});
+        P.r++;
+    }
+    P.minor_digits = digits;
     if (pp.l_batch > 0) {
         // a step's few items should still fill the device
         const uint64_t total = (uint64_t)P.groups * P.span;
-        const uint64_t len = std::min<uint64_t>(pp.l_batch, std::max<uint64_t>(kMinorMinUnit, total / kMinorItemUnits));
+        const uint64_t len =
+            std::min<uint64_t>(q.l_batch, std::max<uint64_t>(kMinorMinUnit / (uint64_t)digits, total / kMinorItemUnits));
         P.units_per_group = std::min<uint64_t>(P.span, std::max<uint64_t>(1, (total + len - 1) / len / P.groups));
         P.units = P.units_per_group * P.groups;
     }

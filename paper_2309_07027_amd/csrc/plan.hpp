@@ -82,8 +82,9 @@ struct HostPlan {
     int scale_log2 = 0;            // the walk's sum times 2^scale_log2 is the permanent
     std::vector<uint32_t> low_radix;  // radices of the low digits (table key)
     TablePtr table;                // Q entries
-    bool minor_pairs = false;  // leave-one-column-out walk over pairs: the last kept row is its inner binary
-                               // digit (kind FIXED), the other fields split the sum over the other digits
+    int minor_digits = 0;      // > 0: leave-one-column-out walk over pairs; the last so many kept rows are its
+                               // inner binary digits (kind FIXED, the first one last), the other fields
+                               // split the sum over the other digits
     std::shared_ptr<const PairPlan> pair;  // set when the pair walk evaluates this permanent
     // scratch of one evaluation (run_perms, under the context's lock): the
     // evaluation that last placed this plan's row records, their offset and the

@@ -605,13 +605,13 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     int nmax = 0;
     // items that go over pairs of columns have a launch of their own: the pair
     // walk (plans that hold its split) or the leave-one-column-out walk over pairs
-    auto by_pairs = [&](const PermItem& it) { return minors ? it.plan->minor_pairs : !f32 && it.plan->pair != nullptr; };
+    auto by_pairs = [&](const PermItem& it) { return minors ? it.plan->minor_digits > 0 : !f32 && it.plan->pair != nullptr; };
     auto arena_of = [&](const PermItem& it, int nc) -> uint64_t {
         const uint64_t rows = (uint64_t)it.plan->r;
         if (!by_pairs(it)) return rows * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
         if (!minors) return rows * (uint64_t)nc;
         const uint64_t pairs = (uint64_t)minor_pairs_per_wave(nc) * kMinorWaves;
-        return rows * 2 * pairs + 2 * (rows - 1) * 3 * pairs;
+        return rows * 2 * pairs + 2 * (rows - 1) * (2 + (uint64_t)it.plan->minor_digits) * pairs;
     };
     size_t npair = 0;
     int np_max = 0;
@@ -778,7 +778,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         d.part_base = part_base[i];
         d.targets = (uint32_t)items[i].targets;
         d.res_base = res_base[i];
-        d.col_pow = items[i].col_pow >= 2 ? (uint32_t)items[i].col_pow : 1u;
+        d.col_pow = np ? (uint32_t)p.minor_digits : items[i].col_pow >= 2 ? (uint32_t)items[i].col_pow : 1u;
         d.mag_every = mag_every_for(p.units_per_group);
         for (uint64_t t = 0; t < stride_of(items[i]); ++t) hri[res_base[i] + t] = (uint32_t)i;
         PrepItem& q = hp[i];
@@ -794,6 +794,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.f32 = f32;
         q.rows_only = pair ? 1 : 0;
         q.np = np;
+        q.digits = p.minor_digits;
         for (int k = 0; k < p.r; ++k) {
             const int ur = p.src_row[(size_t)k];
             hs[s_cursor++] = (uint32_t)(items[i].row_map ? items[i].row_map[ur] : ur);

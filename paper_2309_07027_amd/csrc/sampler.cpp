@@ -248,7 +248,7 @@ void add_minor_items(const PermItem& proto, const int32_t* cols, std::deque<std:
                      std::vector<PermItem>& items, uint64_t res_first, uint32_t* slot)
 {
     const int K = proto.plan->n + 1;
-    if (proto.plan->minor_pairs) {  // one walk for every target
+    if (proto.plan->minor_digits > 0) {  // one walk for every target
         PermItem it = proto;
         keep.emplace_back(cols, cols + K);
         it.col_map = keep.back().data();

@@ -72,8 +72,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
     const double* A = it.src;
     if (it.np > 0) {
         // rows of all wavefronts' pairs (columns past the matrix zero), then per
-        // row but the last (the inner digit's) the two steps of its sign count:
-        // for each pair the changes of b_1, b_2 and D
+        // row but the last (the first inner digit's) the two steps of its sign
+        // count: for each pair the changes of b_1, b_2 and the differences
         const int pairs = it.np * kMinorWaves;
         auto at = [&](int k, int j, double& xr, double& xi) {
             xr = xi = 0.0;
@@ -94,15 +94,18 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
             row[2] = br;
             row[3] = bi;
             if (k + 1 == r) continue;
-            double cr, ci, dr, di;  // the inner row: D changes by 4 (c b + a d) when Delta_k grows
-            at(r - 1, 2 * p, cr, ci);
-            at(r - 1, 2 * p + 1, dr, di);
-            const double kr = 4.0 * (__builtin_fma(cr, br, -(ci * bi)) + __builtin_fma(ar, dr, -(ai * di)));
-            const double ki = 4.0 * (__builtin_fma(cr, bi, ci * br) + __builtin_fma(ar, di, ai * dr));
-            double* down = a2 + 2 * it.a2_off + 6 * ((size_t)(2 * k) * pairs + p);
-            double* up = down + 6 * (size_t)pairs;
-            const double v[6] = {2.0 * ar, 2.0 * ai, 2.0 * br, 2.0 * bi, -kr, -ki};
-            for (int q = 0; q < 6; ++q) {
+            const int step = 2 * (2 + it.digits);
+            double* down = a2 + 2 * it.a2_off + step * ((size_t)(2 * k) * pairs + p);
+            double* up = down + step * (size_t)pairs;
+            double v[8] = {2.0 * ar, 2.0 * ai, 2.0 * br, 2.0 * bi, 0.0, 0.0, 0.0, 0.0};
+            for (int i = 0; i < it.digits; ++i) {
+                double cr, ci, dr, di;  // inner row i: D_i changes by 4 (c b + a d) when Delta_k grows
+                at(r - 1 - i, 2 * p, cr, ci);
+                at(r - 1 - i, 2 * p + 1, dr, di);
+                v[4 + 2 * i] = -4.0 * (__builtin_fma(cr, br, -(ci * bi)) + __builtin_fma(ar, dr, -(ai * di)));
+                v[5 + 2 * i] = -4.0 * (__builtin_fma(cr, bi, ci * br) + __builtin_fma(ar, di, ai * dr));
+            }
+            for (int q = 0; q < step; ++q) {
                 down[q] = v[q];
                 up[q] = -v[q];
             }

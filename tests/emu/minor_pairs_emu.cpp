@@ -21,12 +21,13 @@ using namespace bbfg;
 
 namespace {
 
-template <int NP>
+template <int NP, int DIGITS>
 void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<double>& out)
 {
     const int r = P.r, pairs = NP * kMinorWaves;
+    constexpr int kStep = MinorLane<NP, DIGITS>::kStep;
     // the prep kernel's layout
-    std::vector<double> rows(4 * (size_t)r * pairs, 0.0), steps(6 * (size_t)(2 * (r - 1)) * pairs);
+    std::vector<double> rows(4 * (size_t)r * pairs, 0.0), steps(kStep * (size_t)(2 * (r - 1)) * pairs);
     for (int k = 0; k < r; ++k)
         for (int j = 0; j < K; ++j)
             for (int c = 0; c < 2; ++c)
@@ -34,13 +35,15 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
     for (int k = 0; k + 1 < r; ++k)
         for (int p = 0; p < pairs; ++p) {
             const double* x = &rows[4 * ((size_t)k * pairs + p)];
-            const double* c = &rows[4 * ((size_t)(r - 1) * pairs + p)];
-            const double kr = 4.0 * (c[0] * x[2] - c[1] * x[3] + x[0] * c[2] - x[1] * c[3]);
-            const double ki = 4.0 * (c[0] * x[3] + c[1] * x[2] + x[0] * c[3] + x[1] * c[2]);
-            const double v[6] = {2 * x[0], 2 * x[1], 2 * x[2], 2 * x[3], -kr, -ki};
-            for (int q = 0; q < 6; ++q) {
-                steps[6 * ((size_t)(2 * k) * pairs + p) + q] = v[q];
-                steps[6 * ((size_t)(2 * k + 1) * pairs + p) + q] = -v[q];
+            double v[kStep] = {2 * x[0], 2 * x[1], 2 * x[2], 2 * x[3]};
+            for (int i = 0; i < DIGITS; ++i) {
+                const double* c = &rows[4 * ((size_t)(r - 1 - i) * pairs + p)];
+                v[4 + 2 * i] = -4.0 * (c[0] * x[2] - c[1] * x[3] + x[0] * c[2] - x[1] * c[3]);
+                v[5 + 2 * i] = -4.0 * (c[0] * x[3] + c[1] * x[2] + x[0] * c[3] + x[1] * c[2]);
+            }
+            for (int q = 0; q < kStep; ++q) {
+                steps[kStep * ((size_t)(2 * k) * pairs + p) + q] = v[q];
+                steps[kStep * ((size_t)(2 * k + 1) * pairs + p) + q] = -v[q];
             }
         }
     emu_clear();
@@ -49,7 +52,7 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
     std::vector<double> binom((size_t)kBinomDim * kBinomDim, 0.0);
     for (int m = 0; m < kBinomDim; ++m)
         for (int k = 0; k <= m; ++k) binom[(size_t)m * kBinomDim + k] = (double)binom_u64(m, k);
-    const size_t ld = 4 * (size_t)pairs, step_ld = 6 * (size_t)pairs;
+    const size_t ld = 4 * (size_t)pairs, step_ld = kStep * (size_t)pairs;
     const uint32_t upg = (uint32_t)P.units_per_group;
     for (uint64_t u = 0; u < P.units; ++u) {
         const uint32_t g = (uint32_t)(u / upg), part = (uint32_t)(u % upg);
@@ -58,7 +61,7 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
         for (uint32_t lane = 0; lane < (uint32_t)kWave; ++lane) {
             const uint32_t lane_idx = g * kWave + lane;
             if (lane_idx >= P.lane_product) continue;
-            MinorLane<NP> L[kMinorWaves];
+            MinorLane<NP, DIGITS> L[kMinorWaves];
             for (auto& l : L) l.clear();
             for (uint64_t lin = lin0; lin < lin1;) {
                 const uint64_t h = lin / P.Q;
@@ -86,24 +89,40 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
                     const TabEntry e = (*P.table)[t];
                     if (t > t0)
                         for (int v = 0; v < kMinorWaves; ++v)
-                            L[v].advance(&steps[(size_t)e.row * step_ld + (size_t)v * 6 * NP]);
+                            L[v].advance(&steps[(size_t)e.row * step_ld + (size_t)v * kStep * NP]);
+                    auto exchange = [&](double ws, cpx (*o)[2]) {
+                        for (int v = 0; v < kMinorWaves; ++v)
+                            for (int x = 0; x < 2; ++x)
+                                o[v][x] = cmul_uniform(cmul(cmul(L[(v + 1) % kMinorWaves].half[x].all,
+                                                                 L[(v + 2) % kMinorWaves].half[x].all),
+                                                            L[(v + 3) % kMinorWaves].half[x].all),
+                                                       ws);
+                    };
+                    cpx o[kMinorWaves][2];
                     for (auto& l : L) l.forward();
-                    for (int v = 0; v < kMinorWaves; ++v) {
-                        cpx o[2];
-                        for (int x = 0; x < 2; ++x)
-                            o[x] = cmul_uniform(cmul(cmul(L[(v + 1) % kMinorWaves].half[x].all,
-                                                          L[(v + 2) % kMinorWaves].half[x].all),
-                                                     L[(v + 3) % kMinorWaves].half[x].all),
-                                                w * e.s);
-                        L[v].backward(o[0], o[1]);
+                    exchange(w * e.s, o);
+                    if constexpr (DIGITS > 1) {
+                        for (int v = 0; v < kMinorWaves; ++v) L[v].template backward<false>(o[v][0], o[v][1]);
+                        for (int v = 0; v < kMinorWaves; ++v) {
+                            double K[2 * NP];
+                            const double* row = &steps[(size_t)(2 * (r - 2) + 1) * step_ld + (size_t)v * kStep * NP];
+                            for (int p = 0; p < NP; ++p) {
+                                K[2 * p] = row[kStep * p + 4];
+                                K[2 * p + 1] = row[kStep * p + 5];
+                            }
+                            L[v].forward_second(K);
+                        }
+                        exchange(-w * e.s, o);
                     }
+                    for (int v = 0; v < kMinorWaves; ++v) L[v].template backward<true>(o[v][0], o[v][1]);
                 }
                 lin += t1 - t0;
             }
             for (int v = 0; v < kMinorWaves; ++v)
                 for (int p = 0; p < NP; ++p) {
                     cpx c[2];
-                    L[v].result(p, kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + (size_t)v * 4 * NP), c[0], c[1]);
+                    L[v].result(p, kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + (size_t)v * 4 * NP), ld, c[0],
+                                c[1]);
                     for (int q = 0; q < 2; ++q) {
                         const int j = v * 2 * NP + 2 * p + q;
                         if (j >= K) continue;
@@ -138,12 +157,13 @@ int main()
         return 0;
     }
     std::vector<double> out(2 * (size_t)K, 0.0);
+    const bool two = P.minor_digits == 2;
     switch (minor_pairs_per_wave(K)) {
-    case 2: run<2>(P, K, A, out); break;
-    case 3: run<3>(P, K, A, out); break;
-    case 4: run<4>(P, K, A, out); break;
-    case 5: run<5>(P, K, A, out); break;
-    case 6: run<6>(P, K, A, out); break;
+    case 2: run<2, 1>(P, K, A, out); break;
+    case 3: run<3, 1>(P, K, A, out); break;
+    case 4: two ? run<4, 2>(P, K, A, out) : run<4, 1>(P, K, A, out); break;
+    case 5: run<5, 1>(P, K, A, out); break;
+    case 6: run<6, 1>(P, K, A, out); break;
     default: return 4;
     }
     const double s = std::ldexp(1.0, P.scale_log2);

@@ -84,6 +84,15 @@ def test_planner_leaves_short_sums_and_bunched_rows_to_the_other_walk(exe):
     assert emulate(exe, A, np.array([2] * 8, dtype=np.int32), 64) is None               # no row of multiplicity one
 
 
+@pytest.mark.parametrize("K", [25, 32])
+def test_emulation_of_two_inner_digits(oracle, exe, K):
+    """25 to 32 columns and more than 2^18 addends: two inner digits.  A few
+    minors, those at both ends of a wavefront's columns among them."""
+    A, M = case(K, 2 ** 19)
+    got = emulate(exe, A, M, 512)
+    check(oracle, A, M, got, every=8)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("K", [20, 24, 25, 32, 33, 40, 41, 48])
 def test_gpu_matches_oracle(oracle, K):
