@@ -151,7 +151,8 @@ struct ShortArgs {
     const double* binom;
     double* partials;
     uint32_t* done;           // counters of finished work groups; zero between launches
-    double* out;              // value and diagnostics (pinned host memory)
+    unsigned long long* start;  // clock at the first work group's start
+    double* out;              // value, diagnostics, clock ticks of the launch (pinned host memory)
     uint32_t ld;
 };
 

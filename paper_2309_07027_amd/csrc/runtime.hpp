@@ -153,6 +153,7 @@ struct PlanIndex {
 struct Context {
     int device = -1;
     int n_cu = 0;
+    int clock_khz = 0;  // rate of the device's constant clock
     std::recursive_mutex mu;
     double* binom = nullptr;
     DevBuf staging;

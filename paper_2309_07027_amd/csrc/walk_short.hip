@@ -60,7 +60,8 @@ __device__ __forceinline__ void add_partial(const double* partials, uint64_t u, 
 // (at most 256 units; lane l stands for threads l, l + 64, l + 128, l + 192) or
 // four.  A single unit's record comes in registers.
 __device__ __forceinline__ void finalize_group(const PermDesc& d, const double* partials, uint32_t waves,
-                                               UnitSum* shared, ddv unit_r, ddv unit_i, double unit_a, double* out)
+                                               UnitSum* shared, ddv unit_r, ddv unit_i, double unit_a, unsigned long long start,
+                                               double* out)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     UnitSum v4[4];
@@ -117,6 +118,7 @@ __device__ __forceinline__ void finalize_group(const PermDesc& d, const double* 
         out[1] = im;
         out[2] = kappa * d.err_coeff;
         out[3] = kappa;
+        out[4] = (double)(wall_clock64() - start);
     }
 }
 
@@ -125,6 +127,7 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
 {
     extern __shared__ __align__(16) double rows[];
     __shared__ uint32_t last;
+    const unsigned long long began = wall_clock64();
     // the arguments where the launch put them: lanes index the row records
     const ShortArgs& S = *(const ShortArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     const PermDesc d = by_value.d;
@@ -172,13 +175,14 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
         }
     }
     if (d.units == 1) {
-        finalize_group(d, nullptr, 1, nullptr, sr, si, m, by_value.out);
+        finalize_group(d, nullptr, 1, nullptr, sr, si, m, began, by_value.out);
         return;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         // Work groups count themselves in kShortCounters counters, the last of each
         // of those in another: a thousand increments of one word take 20 us.
+        if (blockIdx.x == 0) __hip_atomic_store(by_value.start, began, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t mine = blockIdx.x % kShortCounters;
         const uint32_t members = (gridDim.x - mine + kShortCounters - 1) / kShortCounters;
         uint32_t* own = by_value.done + (1 + mine) * kCounterStride;
@@ -196,7 +200,8 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
     if (last) {
         // every unit's partial was stored before its work group's count
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        finalize_group(d, by_value.partials, waves, reinterpret_cast<UnitSum*>(rows), sr, si, m, by_value.out);
+        const unsigned long long start = __hip_atomic_load(by_value.start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        finalize_group(d, by_value.partials, waves, reinterpret_cast<UnitSum*>(rows), sr, si, m, start, by_value.out);
     }
 }
 
