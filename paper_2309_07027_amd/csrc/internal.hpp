@@ -206,15 +206,17 @@ constexpr int kMinorWaves = 4;                // wavefronts that share a walk's 
 constexpr int kMinorMinPairs = 2;             // pairs of a wavefront, at least
 constexpr int kMinorMinCols = 9;              // fewest columns it is used for
 // It takes sums of more addends than this in a sampler step (16 samples of 20
-// photons: 1.57, 1.59, 1.78, 2.02 ms with 2^6, 2^8, 2^10, 2^12; without it 2.9
-// ms) and in a lone call (where the walk of shorter sums stays the one whose
-// bits the CPU emulation of walk_core.hpp pins; 24 columns, 2^22 addends: 0.193
-// -> 0.089 ms).
+// photons: 0.79, 0.80, 1.05 ms with 2^6, 2^10, 2^12; 1024 samples of 16: 3.07,
+// 3.18, 3.22 ms) and in a lone call (where the walk of shorter sums stays the one
+// whose bits the CPU emulation of walk_core.hpp pins; 24 columns, 2^22 addends:
+// 0.193 -> 0.089 ms).
 constexpr uint64_t kMinorMinAddendsBatch = uint64_t(1) << 6;
 constexpr uint64_t kMinorMinAddends = uint64_t(1) << 17;
 // An item of a sampler step is split into about so many units, down to units of
-// so many steps of two addends (30 photons: 11.4 ms with 128 units, 12.0 with
-// 32, 12.5 with 16; 24 jobs on the server: 52.5, 51.4, 51.1 ms).
+// so many steps of two addends.  The split depends on the item alone, so that a
+// sample's bits do not depend on its neighbours; few samples want many units, a
+// full launch few (128, 64, 32 units: 16 samples of 24 photons 1.56, 1.52, 1.66
+// ms; 256 of them 10.6, 9.6, 9.1; 24 jobs on the server 47.1, 45.3, 44.4).
 constexpr uint64_t kMinorItemUnits = 64;
 constexpr uint64_t kMinorMinUnit = 16;
 // Two inner digits instead of one: at four pairs a wavefront (25-32 columns),
@@ -229,6 +231,17 @@ constexpr int minor_pairs_per_wave(int K)
 {
     const int np = ((K + 1) / 2 + kMinorWaves - 1) / kMinorWaves;
     return np > kMinorMinPairs ? np : kMinorMinPairs;
+}
+// Wavefronts that own so many pairs; the others own one less (two at least: with
+// one the chain of a step is all that is left).  Which SIMD has the smaller
+// shares changes from work group to work group by itself; turning them by hand in
+// every second one made no difference.  Equal shares padded with columns that are
+// 1 -> these: 25 columns, 2^24 addends, 0.160 -> 0.156 ms; 33 columns 16.8 ->
+// 15.4, 35 25.2 -> 24.1, 42 64.5 -> 60.2 ms (2^29 addends and more).
+constexpr int minor_full_waves(int K)
+{
+    const int np = minor_pairs_per_wave(K);
+    return np > kMinorMinPairs ? (K + 1) / 2 - kMinorWaves * (np - 1) : kMinorWaves;
 }
 
 // Kernel arguments of the pair walk (passed by value).

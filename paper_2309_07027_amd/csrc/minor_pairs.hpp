@@ -59,15 +59,16 @@ __device__ __forceinline__ double minor_coefs(const WalkArgs& A, const PermDesc&
     return w;
 }
 
-// One unit: the sums of this wavefront's 2 NP targets over the unit's addends,
-// then, for sampled units, the estimate of their magnitude sums (the modulus of
-// the addend at the unit's last position, the inner digits at the lane's lowest
-// bits, times the addends it stands for).
-template <int NP, int DIGITS>
-__device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S)
+// One unit: the sums of the targets of this wavefront's NP pairs, from pair
+// `first` on, over the unit's addends, then, for sampled units, the estimate of
+// their magnitude sums (the modulus of the addend at the unit's last position,
+// the inner digits at the lane's lowest bits, times the addends it stands for).
+// The item's rows hold ROWNP pairs for each wavefront.
+template <int NP, int DIGITS, int ROWNP>
+__device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S,
+                                                 uint32_t wave, uint32_t first)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t wave = uniform_u32(threadIdx.x / kWave);
     const uint32_t upg = (uint32_t)d.units_per_group;
     const uint32_t g = u_local / upg;
     const uint32_t part = u_local - g * upg;
@@ -80,13 +81,13 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
     if (!valid) lane_idx = 0;
 
     constexpr int kCols = 2 * NP;
-    const size_t ld = 4 * (size_t)NP * kMinorWaves;                 // doubles per kept row
+    const size_t ld = 4 * (size_t)ROWNP * kMinorWaves;              // doubles per kept row
     constexpr int kStep = MinorLane<NP, DIGITS>::kStep;
-    const size_t step_ld = kStep * (size_t)NP * kMinorWaves;        // doubles per step row
-    kptr<double> a = kconst(A.a + 2 * d.a_off + wave * (4 * NP));
-    kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + wave * (kStep * NP));
+    const size_t step_ld = kStep * (size_t)ROWNP * kMinorWaves;     // doubles per step row
+    kptr<double> a = kconst(A.a + 2 * d.a_off + first * 4);
+    kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + first * kStep);
     kptr<TabEntry> tab = kconst(d.tab);
-    const int cols = (int)d.n - (int)wave * kCols;                  // real columns of this wavefront (may be < 0)
+    const int cols = (int)d.n - 2 * (int)first;                     // real columns from there on (may be < 0)
     const uint32_t Q = d.Q;
     auto coef = [&](int k) { return (double)S.coef[k][lane]; };
 
@@ -151,13 +152,13 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         __syncthreads();  // the coefficients and weights may be overwritten
     }
     kptr<double> inner = a + (int64_t)((size_t)(d.r - 1) * ld);
-    const uint64_t slot = d.part_base + (uint64_t)u_local * d.targets + wave * kCols;
+    const uint64_t slot = d.part_base + (uint64_t)u_local * d.targets + 2 * first;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        cpx first, second;
-        L.result(p, inner, ld, first, second);
-        if (2 * p < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p, first.r, first.i);
-        if (2 * p + 1 < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p + 1, second.r, second.i);
+        cpx m1, m2;
+        L.result(p, inner, ld, m1, m2);
+        if (2 * p < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p, m1.r, m1.i);
+        if (2 * p + 1 < cols) store_partial_sums_all_lanes(A.partials, slot + 2 * p + 1, m2.r, m2.i);
     }
     const uint32_t every = d.mag_every;
     if (part % every != 0) {
@@ -205,19 +206,36 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
     }
 }
 
+// The wavefronts of a work group meet at the same barriers whether they own NP
+// pairs or NP - 1: all that is walked is the unit's.
+template <int NP, int DIGITS>
+__device__ __forceinline__ void minor_pairs_share(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
+                                                  uint32_t wave)
+{
+    const uint32_t full = (uint32_t)minor_full_waves(d.n);
+    if constexpr (NP > kMinorMinPairs) {
+        if (wave >= full) {
+            minor_pairs_unit<NP - 1, DIGITS, NP>(A, d, u, S, wave, wave * (NP - 1) + full);
+            return;
+        }
+    }
+    minor_pairs_unit<NP, DIGITS, NP>(A, d, u, S, wave, wave * NP);
+}
+
 template <int NPMIN, int NPMAX>
-__device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S)
+__device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
+                                                     uint32_t wave)
 {
     if constexpr (NPMIN <= NPMAX) {
         if (minor_pairs_per_wave(d.n) == NPMIN) {
             if constexpr (NPMIN == kMinorTwoDigits) {
                 if (d.col_pow == 2) {
-                    minor_pairs_unit<NPMIN, 2>(A, d, u, S);
+                    minor_pairs_share<NPMIN, 2>(A, d, u, S, wave);
                     return;
                 }
             }
-            minor_pairs_unit<NPMIN, 1>(A, d, u, S);
-        } else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S);
+            minor_pairs_share<NPMIN, 1>(A, d, u, S, wave);
+        } else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S, wave);
     }
 }
 
@@ -226,6 +244,7 @@ template <int NPMAX>
 __global__ __launch_bounds__(kMinorThreads) __attribute__((amdgpu_waves_per_eu(NPMAX <= 3 ? 3 : 2))) void minor_pairs_kernel(WalkArgs A)
 {
     __shared__ MinorShared S;
+    const uint32_t wave = uniform_u32(threadIdx.x / kWave);
     for (;;) {
         if (threadIdx.x == 0) S.next_unit = atomicAdd(A.counter, 1u);
         __syncthreads();
@@ -234,7 +253,7 @@ __global__ __launch_bounds__(kMinorThreads) __attribute__((amdgpu_waves_per_eu(N
         if (u >= A.total_units) break;
         const uint32_t item = item_of_unit(A, u);
         const PermDesc d = A.descs[item];
-        dispatch_minor_pairs<kMinorMinPairs, NPMAX>(A, d, u - (uint32_t)d.unit_base, S);
+        dispatch_minor_pairs<kMinorMinPairs, NPMAX>(A, d, u - (uint32_t)d.unit_base, S, wave);
     }
 }
 

@@ -15,14 +15,18 @@
 // the multiply-accumulates with the column sums are shared by the two addends,
 // and the d terms are added once at a unit's end.
 //
-// Bound by FP64 issue: 23.6 FP64 instructions per pair and addend (189 a step
-// of two addends and four pairs, 11 other vector ones) and about 40 registers
-// per pair, so up to 40 columns fit two wavefronts per SIMD without spills or
-// accumulation registers (up to 24 columns three).  One wavefront for all
-// columns, walk_minors_unit, issues 38 a pair and addend at 30 columns and 54
-// at 36, where half are register moves.  Measured (kernel): 24 columns, 2^22
-// addends, 0.193 -> 0.089 ms; 30 columns, 2^28, 4.96 -> 3.51 ms; 35 columns, 34
-// photons at random, 12.5 -> 7.2 ms.
+// A second binary digit, at four pairs a wavefront, makes a step of four addends
+// that shares the sums and the multiply-accumulates once more (MinorLane).
+//
+// Bound by FP64 issue: 23.6 FP64 instructions per pair and addend with one digit
+// (189 a step of two addends and four pairs, 11 other vector ones), 21.9 with
+// two (351 a step of four addends), and about 40 registers per pair, so up to 40
+// columns fit two wavefronts per SIMD without spills or accumulation registers
+// (up to 24 columns three).  One wavefront for all columns, walk_minors_unit,
+// issues 38 a pair and addend at 30 columns and 54 at 36, where half are register
+// moves.  Measured (kernel): 24 columns, 2^22 addends, 0.193 -> 0.089 ms; 30
+// columns, 2^28, 4.96 -> 3.51 ms with one digit, 3.11 with two; 35 columns, 34
+// photons at random, 12.5 -> 6.6 ms.
 //
 // Compiled by hipcc for the kernel and by a host compiler for the CPU emulation.
 #pragma once

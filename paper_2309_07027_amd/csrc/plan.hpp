@@ -17,7 +17,8 @@ struct PlanParams {
     // single launches: units fill every resident wavefront slot when the sum allows
     // shorter ones: units between l_least and l_floor positions, about u_short of
     // them in between (a unit's start costs as much as several positions: 20
-    // columns, 2^19 addends: 49.6, 46.7, 49.2 us a call with units of 16, 8, 4)
+    // columns, 2^19 addends, in three launches: 49.6, 46.7, 49.2 us a call with
+    // units of 16, 8, 4)
     uint64_t l_least = 4;
     uint64_t l_floor = 16;
     uint64_t u_short = 1024;

@@ -10,9 +10,9 @@
 // stores the last partial adds them all up.  The arithmetic and its order are
 // those of walk_single_kernel and finalize_kernel.
 //
-// Bound by latency.  perm_bbfg, a call: 8 columns (one unit) 37.5 -> 23.8 us, 16
-// columns, 2^15 addends, 57 -> 32 us, 20 columns, 2^19 addends (1024 units of 8
-// steps), 69 -> 40 us.  Above 32 columns, 2048 units or 40 KB of rows the
+// Bound by latency.  perm_bbfg, a call: 8 columns (one unit) 37.5 -> 21.2 us, 16
+// columns, 2^15 addends, 57 -> 30 us, 20 columns, 2^19 addends (1024 units of 8
+// steps), 69 -> 38 us (kernel: 6, 15, 23 us).  Above 32 columns, 2048 units or 40 KB of rows the
 // general sequence runs: there the rows no longer fit several times into a
 // compute unit's LDS and the walks are long enough to hide their loads.
 #include <hip/hip_runtime.h>

@@ -61,8 +61,20 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
         for (uint32_t lane = 0; lane < (uint32_t)kWave; ++lane) {
             const uint32_t lane_idx = g * kWave + lane;
             if (lane_idx >= P.lane_product) continue;
+            // wavefronts of NP pairs, and those of one less
+            constexpr int NL = NP > kMinorMinPairs ? NP - 1 : NP;
             MinorLane<NP, DIGITS> L[kMinorWaves];
-            for (auto& l : L) l.clear();
+            MinorLane<NL, DIGITS> less[kMinorWaves];
+            const int full = minor_full_waves(K);
+            auto wave = [&](int v, auto f) {
+                if (v < full) f(L[v], NP, (size_t)(v * NP));
+                else f(less[v], NL, (size_t)(v * NL + full));
+            };
+            auto waves = [&](auto f) {
+                for (int v = 0; v < kMinorWaves; ++v)
+                    wave(v, [&](auto& l, int pairs_of, size_t first) { f(v, l, pairs_of, first); });
+            };
+            waves([&](int, auto& l, int, size_t) { l.clear(); });
             for (uint64_t lin = lin0; lin < lin1;) {
                 const uint64_t h = lin / P.Q;
                 const uint32_t t0 = (uint32_t)(lin - h * P.Q);
@@ -82,54 +94,59 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
                     coef[(size_t)k] = x.base - 2 * (int)delta;
                     w *= pair_row_weight(x, binom.data(), coef[(size_t)k]);
                 }
-                for (int v = 0; v < kMinorWaves; ++v)
-                    L[v].seed(kconst(rows.data()) + v * 4 * NP, ld, r, K - v * 2 * NP,
-                              [&](int k) { return (double)coef[(size_t)k]; });
+                waves([&](int, auto& l, int, size_t first) {
+                    l.seed(kconst(rows.data()) + (int64_t)(4 * first), ld, r, K - 2 * (int)first,
+                           [&](int k) { return (double)coef[(size_t)k]; });
+                });
                 for (uint32_t t = t0; t < t1; ++t) {
                     const TabEntry e = (*P.table)[t];
                     if (t > t0)
-                        for (int v = 0; v < kMinorWaves; ++v)
-                            L[v].advance(&steps[(size_t)e.row * step_ld + (size_t)v * kStep * NP]);
-                    auto exchange = [&](double ws, cpx (*o)[2]) {
+                        waves([&](int, auto& l, int, size_t first) {
+                            l.advance(&steps[(size_t)e.row * step_ld + kStep * first]);
+                        });
+                    cpx all[kMinorWaves][2], o[kMinorWaves][2];
+                    auto exchange = [&](double ws) {
+                        waves([&](int v, auto& l, int, size_t) {
+                            for (int x = 0; x < 2; ++x) all[v][x] = l.half[x].all;
+                        });
                         for (int v = 0; v < kMinorWaves; ++v)
                             for (int x = 0; x < 2; ++x)
-                                o[v][x] = cmul_uniform(cmul(cmul(L[(v + 1) % kMinorWaves].half[x].all,
-                                                                 L[(v + 2) % kMinorWaves].half[x].all),
-                                                            L[(v + 3) % kMinorWaves].half[x].all),
+                                o[v][x] = cmul_uniform(cmul(cmul(all[(v + 1) % kMinorWaves][x],
+                                                                 all[(v + 2) % kMinorWaves][x]),
+                                                            all[(v + 3) % kMinorWaves][x]),
                                                        ws);
                     };
-                    cpx o[kMinorWaves][2];
-                    for (auto& l : L) l.forward();
-                    exchange(w * e.s, o);
+                    waves([&](int, auto& l, int, size_t) { l.forward(); });
+                    exchange(w * e.s);
                     if constexpr (DIGITS > 1) {
-                        for (int v = 0; v < kMinorWaves; ++v) L[v].template backward<false>(o[v][0], o[v][1]);
-                        for (int v = 0; v < kMinorWaves; ++v) {
+                        waves([&](int v, auto& l, int, size_t) { l.template backward<false>(o[v][0], o[v][1]); });
+                        waves([&](int, auto& l, int pairs_of, size_t first) {
                             double K[2 * NP];
-                            const double* row = &steps[(size_t)(2 * (r - 2) + 1) * step_ld + (size_t)v * kStep * NP];
-                            for (int p = 0; p < NP; ++p) {
+                            const double* row = &steps[(size_t)(2 * (r - 2) + 1) * step_ld + kStep * first];
+                            for (int p = 0; p < pairs_of; ++p) {
                                 K[2 * p] = row[kStep * p + 4];
                                 K[2 * p + 1] = row[kStep * p + 5];
                             }
-                            L[v].forward_second(K);
-                        }
-                        exchange(-w * e.s, o);
+                            l.forward_second(K);
+                        });
+                        exchange(-w * e.s);
                     }
-                    for (int v = 0; v < kMinorWaves; ++v) L[v].template backward<true>(o[v][0], o[v][1]);
+                    waves([&](int v, auto& l, int, size_t) { l.template backward<true>(o[v][0], o[v][1]); });
                 }
                 lin += t1 - t0;
             }
-            for (int v = 0; v < kMinorWaves; ++v)
-                for (int p = 0; p < NP; ++p) {
+            waves([&](int, auto& l, int pairs_of, size_t first) {
+                for (int p = 0; p < pairs_of; ++p) {
                     cpx c[2];
-                    L[v].result(p, kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + (size_t)v * 4 * NP), ld, c[0],
-                                c[1]);
+                    l.result(p, kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + 4 * first), ld, c[0], c[1]);
                     for (int q = 0; q < 2; ++q) {
-                        const int j = v * 2 * NP + 2 * p + q;
+                        const int j = 2 * (int)first + 2 * p + q;
                         if (j >= K) continue;
                         out[2 * (size_t)j] += c[q].r;
                         out[2 * (size_t)j + 1] += c[q].i;
                     }
                 }
+            });
         }
     }
 }

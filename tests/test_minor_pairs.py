@@ -1,8 +1,9 @@
 """The leave-one-column-out walk over pairs of columns against the oracle: on the
 CPU its per-lane code on the planner's split with bounds-checked reads
 (tests/emu/minor_pairs_emu.cpp), on the GPU through perm_minors.  Column counts
-on both sides of each step in the pairs per wavefront, odd and even, columns
-that leave a wavefront without any, rows of multiplicity above one.  The bound
+on both sides of each step in the pairs per wavefront, odd and even, equal and
+unequal shares, columns that leave a wavefront without any, rows of multiplicity
+above one.  The bound
 is the FP64 path's (1e-10 relative to the oracle where its kappa is at most 1e6,
 and always the reported estimate)."""
 import os
@@ -69,7 +70,7 @@ def check(oracle, A, M, got, est=None, every=1):
             assert e <= est[l], (l, e, est[l])
 
 
-@pytest.mark.parametrize("K", [15, 16, 17, 24, 25, 32, 33, 40, 41, 48])
+@pytest.mark.parametrize("K", [10, 15, 16, 17, 24, 25, 27, 30, 32, 33, 38, 40, 41, 48])
 def test_emulation_matches_oracle(oracle, exe, K):
     A, M = case(K, 2 ** 14)
     got = emulate(exe, A, M, 64)
@@ -84,7 +85,7 @@ def test_planner_leaves_short_sums_and_bunched_rows_to_the_other_walk(exe):
     assert emulate(exe, A, np.array([2] * 8, dtype=np.int32), 64) is None               # no row of multiplicity one
 
 
-@pytest.mark.parametrize("K", [25, 32])
+@pytest.mark.parametrize("K", [25, 27, 32])
 def test_emulation_of_two_inner_digits(oracle, exe, K):
     """25 to 32 columns and more than 2^18 addends: two inner digits.  A few
     minors, those at both ends of a wavefront's columns among them."""
@@ -94,7 +95,7 @@ def test_emulation_of_two_inner_digits(oracle, exe, K):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K", [20, 24, 25, 32, 33, 40, 41, 48])
+@pytest.mark.parametrize("K", [17, 20, 24, 25, 27, 29, 32, 33, 36, 40, 41, 48])
 def test_gpu_matches_oracle(oracle, K):
     A, M = case(K, 2 ** 19)
     print(f"case minors over pairs K={K} M={M.tolist()}", flush=True)
