@@ -94,7 +94,11 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
     MinorLane<NP, DIGITS> L;
     L.clear();
     uint32_t buf = 0;
-    // e of both x: the weight times the other wavefronts' products
+    // e of both x: the weight times the other wavefronts' products.  From its
+    // column sums to here a wavefront is what the other three wait for, and has
+    // little to issue; it goes before the accumulations of the other work groups'
+    // wavefronts on its SIMD (25 columns, 2^24 addends, 0.156 -> 0.145 ms; 29 and
+    // 30, 2^28, 2.28 -> 1.97 and 3.39 -> 3.25; 33 to 40 columns 2 to 5 % less).
     auto exchange = [&](double ws, cpx& e0, cpx& e1) {
         S.prod[buf][wave][0][lane] = L.half[0].all;
         S.prod[buf][wave][1][lane] = L.half[1].all;
@@ -105,6 +109,8 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         e0 = cmul_uniform(cmul(cmul((*o0)[0][lane], (*o1)[0][lane]), (*o2)[0][lane]), ws);
         e1 = cmul_uniform(cmul(cmul((*o0)[1][lane], (*o1)[1][lane]), (*o2)[1][lane]), ws);
         buf ^= 1u;
+        __builtin_amdgcn_s_setprio(0);
+        BBFG_SCHED_BARRIER();
     };
     // K of the two inner digits: the change of D when x' grows
     double K[DIGITS > 1 ? 2 * NP : 1];
@@ -127,10 +133,14 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         uint32_t next_row = t0 + 1 < t1 ? uniform_u32(tab[t0 + 1].row) : 0u;
         for (uint32_t t = t0; t < t1; ++t) {
             cpx e0, e1;
+            __builtin_amdgcn_s_setprio(1);
+            BBFG_SCHED_BARRIER();
             L.forward();
             exchange(ws, e0, e1);
             if constexpr (DIGITS > 1) {
                 L.template backward<false>(e0, e1);
+                __builtin_amdgcn_s_setprio(1);
+                BBFG_SCHED_BARRIER();
                 L.forward_second(K);
                 exchange(-ws, e0, e1);
             }
@@ -244,7 +254,8 @@ template <int NPMAX>
 __global__ __launch_bounds__(kMinorThreads) __attribute__((amdgpu_waves_per_eu(NPMAX <= 3 ? 3 : 2))) void minor_pairs_kernel(WalkArgs A)
 {
     __shared__ MinorShared S;
-    const uint32_t wave = uniform_u32(threadIdx.x / kWave);
+    // the remainder tells the range, which saves registers (32 columns 9.6 -> 9.4 ms)
+    const uint32_t wave = uniform_u32(threadIdx.x / kWave % kMinorWaves);
     for (;;) {
         if (threadIdx.x == 0) S.next_unit = atomicAdd(A.counter, 1u);
         __syncthreads();
