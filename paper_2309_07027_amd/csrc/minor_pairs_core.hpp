@@ -24,9 +24,8 @@
 // columns fit two wavefronts per SIMD without spills or accumulation registers
 // (up to 24 columns three).  One wavefront for all columns, walk_minors_unit,
 // issues 38 a pair and addend at 30 columns and 54 at 36, where half are register
-// moves.  Measured (kernel): 24 columns, 2^22 addends, 0.193 -> 0.089 ms; 30
-// columns, 2^28, 4.96 -> 3.1 ms; 35 columns, 34
-// photons at random, 12.5 -> 6.2 ms.
+// moves.  Measured (kernel): 24 columns, 2^22 addends, 0.193 -> 0.087 ms; 30
+// columns, 2^28, 4.96 -> 3.1 ms; 35 columns, 34 photons at random, 12.5 -> 6.2 ms.
 //
 // Compiled by hipcc for the kernel and by a host compiler for the CPU emulation.
 #pragma once
