@@ -69,10 +69,10 @@ std::vector<int> choose_lane_digits(const std::vector<int>& digits, const std::v
     mask[1] = 0;
     for (size_t i = 0; i < digits.size() && i < 62; ++i) {
         const uint32_t R = rows[(size_t)digits[i]].radix;
-        for (int p = (int)kCap; p >= 1; --p) {
+        for (int p = (int)(kCap / R); p >= 1; --p) {
             if (mask[(size_t)p] < 0 || mask[(size_t)p] >> i & 1) continue;
             const uint64_t q = (uint64_t)p * R;
-            if (q <= kCap && mask[(size_t)q] < 0) mask[(size_t)q] = mask[(size_t)p] | ((int64_t)1 << i);
+            if (mask[(size_t)q] < 0) mask[(size_t)q] = mask[(size_t)p] | ((int64_t)1 << i);
         }
     }
     int best = 1;
