@@ -172,6 +172,9 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
 #pragma unroll
             for (int q = 0; q < kPartialDoubles; ++q)
                 __hip_atomic_store(p + q, x[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // Each wavefront waits for its own stores: the work group's barrier does
+            // not, and the release before its count covers wavefront 0 alone.
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         }
     }
     if (d.units == 1) {
@@ -198,7 +201,7 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
     }
     __syncthreads();
     if (last) {
-        // every unit's partial was stored before its work group's count
+        // every unit's partial had left its wavefront before its work group's count
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const unsigned long long start = __hip_atomic_load(by_value.start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         finalize_group(d, by_value.partials, waves, reinterpret_cast<UnitSum*>(rows), sr, si, m, start, by_value.out);
