@@ -132,6 +132,8 @@ struct PrepItem {
     int32_t rows_only;  // no +-2a rows
     int32_t digits;     // inner digits of that walk
     int32_t np;         // > 0: the layout of the leave-one-column-out walk over pairs, np pairs a wavefront
+    uint64_t inner_rows;  // walks over pairs: the kept rows of the inner digits, a bit each (0: other walks)
+    uint64_t direct_off;  // their flag in a (complex elements): not zero where products are formed from the sums
 };
 
 // ---------------------------------------------------------------------------
@@ -179,7 +181,8 @@ constexpr int kPairMinCols = 4;
 // Device descriptor of one permanent evaluated by the pair walk.  Its units are
 // (lane group, high position) in that order; a unit covers every mid position.
 struct PairDesc {
-    uint64_t a_off;        // element offset of the r x n kept rows (complex)
+    uint64_t a_off;        // element offset of the r x n kept rows (complex) and, behind them, the flag that
+                           //   prep_rows_kernel sets where products are to be formed from the column sums
     uint64_t mid_off;      // double offsets into the tables: mid x np x kPairSlots complex uniform parts,
     uint64_t weight_off;   //   the mid positions' signed weights,
     uint64_t const_off;    //   np x 6 complex constants

@@ -36,7 +36,6 @@ namespace bbfg {
 
 // acc + a b
 BBFG_FN void cmac(cpx& acc, cpx a, cpx b) { acc = cfma(a, b, acc); }
-BBFG_FN cpx csub(cpx a, cpx b) { return {a.r - b.r, a.i - b.i}; }
 BBFG_FN cpx cmul_uniform(cpx a, double s) { return {a.r * s, a.i * s}; }
 
 // DIGITS: inner binary digits, 1 or 2.  With a second digit x', taken as a second

@@ -226,6 +226,10 @@ try {
     q.n = n;
     q.r = r;
     q.rows_only = P.pair ? 1 : 0;
+    if (P.pair) {
+        q.inner_rows = pair_inner_rows(*P.pair);
+        q.direct_off = d.a2_off;  // behind the rows
+    }
     uint32_t* hs = reinterpret_cast<uint32_t*>(H + o_src);
     for (int k = 0; k < r; ++k) hs[k] = (uint32_t)P.src_row[(size_t)k];
     std::memcpy(g_host_meta + kMetaBytes, P.table->data(), tab_bytes);

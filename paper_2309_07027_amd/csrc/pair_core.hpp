@@ -27,6 +27,19 @@
 // 14 columns of multiplicity 2, 2^27 addends, 0.50 -> 0.32 ms; 4096 items of
 // 23-24 photons 37.6 -> 29.1 ms.
 //
+// A value formed from differences carries an error of about 2^-53 of the largest
+// of its pair's 16 products, where a product of two column sums has one relative
+// to the sums.  The two are alike while the inner rows' entries are of the size
+// of the others.  Where they dominate a column their signs can cancel there, and
+// other columns can make up for the small product: with two rows of 1e4 that
+// cancel in two columns and add up in two others the differences lose four
+// digits, and the estimate, which is made of the addends, does not show it.  Such
+// a permanent (differences_serve) has its products formed from the column sums
+// (pair_block_direct), at the plain walk's 12 instructions an addend and pair:
+// 30 columns, 2^29 addends, 3.13 ms a call instead of 2.24 (the plain walk 3.04-
+// 3.12); 512 items of 23 photons 10.9 instead of 7.7 ms (10.0).  Fetching a pair's
+// scalars a pair ahead made no difference there.
+//
 // Compiled by hipcc for the kernels and by a host compiler for the CPU
 // emulation used in tests, as walk_core.hpp.
 #pragma once
@@ -61,6 +74,7 @@ BBFG_FN double fmar_sub(double a, double b, double c)
 }
 
 BBFG_FN cpx cadd(cpx a, cpx b) { return {a.r + b.r, a.i + b.i}; }
+BBFG_FN cpx csub(cpx a, cpx b) { return {a.r - b.r, a.i - b.i}; }
 BBFG_FN cpx cadd(cpx a, const double* k) { return {a.r + k[0], a.i + k[1]}; }
 BBFG_FN cpx cmul(cpx a, cpx b)
 {
@@ -81,6 +95,31 @@ BBFG_FN void cmul_into(cpx& p, cpx v)
     p.i = p.i * v.r;
     p.i = fmar(p.r, v.i, p.i);
     p.r = fmar_sub(p.r, v.r, t);
+}
+
+// Whether the inner rows (inner_rows: a bit each) leave a column of r kept rows
+// to differences; mag(k) is the modulus |re| + |im| of row k's entry.  At least
+// half of the other entries have to reach 1/16 of the largest inner one: with
+// rows 16 times the others that cancel as above the differences are off by as
+// much as the plain walk, with 64 times by ten times as much.  Entries of like
+// distribution (Gaussian, Haar) fail it in fewer than one column of a million.
+constexpr double kInnerRange = 16.0;
+template <typename Mag>
+BBFG_FN bool differences_serve(int r, uint64_t inner_rows, Mag mag)
+{
+    double top = 0.0;
+    int others = 0, near = 0;
+    for (int k = 0; k < r; ++k)
+        if (inner_rows >> k & 1u) {
+            const double m = mag(k);
+            top = m > top ? m : top;
+        }
+    for (int k = 0; k < r; ++k)
+        if (!(inner_rows >> k & 1u)) {
+            ++others;
+            near += kInnerRange * mag(k) >= top ? 1 : 0;
+        }
+    return 2 * near >= others;
 }
 
 // The pair's column sums and differences: slot 0, 1: b_1, b_2; slot 2 + k: D_k.
@@ -227,6 +266,27 @@ BBFG_FN void pair_block(const PairSums& q, const double* K, cpx* P)
     }
 }
 
+// The same values as products of the column sums c1, c2, walked over the inner
+// digits in Gray order; a1, a2: the inner rows' entries.
+template <bool FIRST>
+BBFG_FN void pair_block_direct(cpx c1, cpx c2, const cpx* a1, const cpx* a2, cpx* P)
+{
+    int x = 0;
+#pragma unroll
+    for (int g = 0; g < kPairBlock; ++g) {
+        if (g > 0) {
+            const int k = __builtin_ctz((unsigned)g);
+            x ^= 1 << k;
+            const double f = x >> k & 1 ? -2.0 : 2.0;
+            c1 = {fmar(f, a1[k].r, c1.r), fmar(f, a1[k].i, c1.i)};
+            c2 = {fmar(f, a2[k].r, c2.r), fmar(f, a2[k].i, c2.i)};
+        }
+        const cpx v = cmul(c1, c2);
+        if constexpr (FIRST) P[x] = v;
+        else cmul_into(P[x], v);
+    }
+}
+
 // Sum of the 16 products with the inner digits' signs, and of their moduli |re| + |im|.
 BBFG_FN void pair_block_sum(const cpx* P, double& sr, double& si, double& sa)
 {
@@ -266,6 +326,21 @@ BBFG_FN void pair_fetch(kptr<double> U, kptr<double> K, PairInputs& in)
     for (int i = 0; i < 2 * kPairConsts; ++i) in.k[i] = K[i];
 }
 
+// A block's products, raised and added: the sums grow by the weighted ones.
+template <bool POW>
+BBFG_FN void pair_close(const PairDesc& d, cpx* P, double w, double& accr, double& acci, double& acca)
+{
+    if constexpr (POW) {
+#pragma unroll
+        for (int x = 0; x < kPairBlock; ++x) cpow_uint<double>(P[x].r, P[x].i, d.col_pow);
+    }
+    double sr, si, sa;
+    pair_block_sum(P, sr, si, sa);
+    accr = fmar(w, sr, accr);
+    acci = fmar(w, si, acci);
+    acca = fmar(__builtin_fabs(w), sa, acca);
+}
+
 // One lane's walk over mid positions [h0, h1): sum of the weighted addends and
 // of their magnitudes.  lane(p, out) reads the lane part of pair p.  POW: every
 // column has multiplicity d.col_pow, the product is (prod_j c_j)^col_pow.
@@ -299,15 +374,42 @@ BBFG_FN void pair_walk(const PairDesc& d, kptr<double> mid, kptr<double> weight,
         };
         step(std::true_type{}, 0u, np > 1 ? 1u : 0u);
         for (uint32_t p = 1; p < np; ++p) step(std::false_type{}, p, p + 1 < np ? p + 1 : 0u);
-        if constexpr (POW) {
+        pair_close<POW>(d, P, w, accr, acci, acca);
+    }
+    out_r = accr;
+    out_i = acci;
+    out_a = acca;
+}
+
+// The same walk with the products formed from the column sums; a: the kept rows.
+template <bool POW, typename Lane>
+BBFG_FN void pair_walk_direct(const PairDesc& d, kptr<double> a, kptr<double> mid, kptr<double> weight, uint32_t h0,
+                              uint32_t h1, Lane lane, double& out_r, double& out_i, double& out_a)
+{
+    const uint32_t np = (uint32_t)d.np;
+    double accr = 0.0, acci = 0.0, acca = 0.0;
+    kptr<double> U = mid + (size_t)h0 * np * (2 * kPairSlots);
+    for (uint32_t h = h0; h < h1; ++h) {
+        cpx P[kPairBlock];
+        const double w = weight[h];
+        auto step = [&](auto first, uint32_t p) {
+            cpx a1[kPairBits], a2[kPairBits], c[2];
 #pragma unroll
-            for (int x = 0; x < kPairBlock; ++x) cpow_uint<double>(P[x].r, P[x].i, d.col_pow);
-        }
-        double sr, si, sa;
-        pair_block_sum(P, sr, si, sa);
-        accr = fmar(w, sr, accr);
-        acci = fmar(w, si, acci);
-        acca = fmar(__builtin_fabs(w), sa, acca);
+            for (int k = 0; k < kPairBits; ++k) {
+                kptr<double> row = a + 2 * ((size_t)d.inner[k] * d.n + 2 * p);
+                a1[k] = {row[0], row[1]};
+                a2[k] = {0.0, 0.0};
+                if (2 * p + 1 < (uint32_t)d.n) a2[k] = {row[2], row[3]};
+            }
+            lane(p, c);
+            c[0] = {c[0].r + U[0], c[0].i + U[1]};
+            c[1] = {c[1].r + U[2], c[1].i + U[3]};
+            U = U + 2 * kPairSlots;
+            pair_block_direct<decltype(first)::value>(c[0], c[1], a1, a2, P);
+        };
+        step(std::true_type{}, 0u);
+        for (uint32_t p = 1; p < np; ++p) step(std::false_type{}, p);
+        pair_close<POW>(d, P, w, accr, acci, acca);
     }
     out_r = accr;
     out_i = acci;

@@ -487,6 +487,13 @@ void fill_walk_desc(PermDesc& d, const HostPlan& p, int n_cols, bool f32)
 
 }  // namespace
 
+uint64_t pair_inner_rows(const PairPlan& p)
+{
+    uint64_t rows = 0;
+    for (int k : p.inner) rows |= uint64_t(1) << k;
+    return rows;
+}
+
 uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles)
 {
     const PairPlan& pp = *p.pair;
@@ -608,7 +615,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     auto arena_of = [&](const PermItem& it, int nc) -> uint64_t {
         const uint64_t rows = (uint64_t)it.plan->r;
         if (!by_pairs(it)) return rows * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
-        if (!minors) return rows * (uint64_t)nc;
+        if (!minors) return rows * (uint64_t)nc + 1;  // a, the flag
         const uint64_t pairs = (uint64_t)minor_pairs_per_wave(nc) * kMinorWaves;
         return rows * 2 * pairs + 2 * (rows - 1) * (2 + (uint64_t)it.plan->minor_digits) * pairs;
     };
@@ -794,6 +801,10 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.rows_only = pair ? 1 : 0;
         q.np = np;
         q.digits = p.minor_digits;
+        if (pair && !minors) {
+            q.inner_rows = pair_inner_rows(*p.pair);
+            q.direct_off = d.a2_off;
+        }
         for (int k = 0; k < p.r; ++k) {
             const int ur = p.src_row[(size_t)k];
             hs[s_cursor++] = (uint32_t)(items[i].row_map ? items[i].row_map[ur] : ur);

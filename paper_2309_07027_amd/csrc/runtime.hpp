@@ -280,6 +280,9 @@ struct RunResult {
 // doubles.  Returns its mid positions.
 uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles);
 
+// The kept rows of the pair walk's inner digits, a bit each.
+uint64_t pair_inner_rows(const PairPlan& p);
+
 // Evaluates items (all n >= 1).  The (re, im) results stay in c.results (item
 // order; an item with targets = G has G consecutive results) and, when out_host
 // is not null, are copied to out_host[2*i]; the diagnostics (err_est, kappa) to

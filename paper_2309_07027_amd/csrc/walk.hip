@@ -23,6 +23,7 @@
 
 #include "internal.hpp"
 #include "kernels.hpp"
+#include "pair_core.hpp"
 #include "walk_core.hpp"
 #include "walk_batch.hpp"
 #include "walk_device.hpp"
@@ -52,6 +53,8 @@ __global__ void init_binom_kernel(double* tab)
 // before: the first blocks read their items from the pinned host image, the
 // others copy it for the kernels that follow (one launch instead of three).
 // ---------------------------------------------------------------------------
+// For a walk over pairs of columns it also tells whether differences serve every
+// column (pair_core.hpp), from the moduli of the entries in LDS.
 constexpr int kPrepThreads = 256;
 constexpr size_t kImageBlockBytes = kPrepThreads * sizeof(uint4);
 
@@ -70,6 +73,14 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
     const PrepItem it = items[blockIdx.x];
     const int n = it.n, r = it.r;
     const double* A = it.src;
+    __shared__ double mag[kMaxN * kMaxN];
+    auto set_direct = [&]() {
+        __syncthreads();
+        const int j = (int)threadIdx.x;
+        const bool off = j < n && !differences_serve(r, it.inner_rows, [&](int k) { return mag[k * n + j]; });
+        const int any = __syncthreads_or(off ? 1 : 0);
+        if (threadIdx.x == 0) a[2 * it.direct_off] = any ? 1.0 : 0.0;
+    };
     if (it.np > 0) {
         // rows of all wavefronts' pairs (columns past the matrix zero), then per
         // row but the last (the first inner digit's) the two steps of its sign
@@ -131,13 +142,17 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
         } else {
             a[2 * da] = xr;
             a[2 * da + 1] = xi;
-            if (it.rows_only) continue;
+            if (it.rows_only) {
+                mag[e] = __builtin_fabs(xr) + __builtin_fabs(xi);
+                continue;
+            }
             a2[2 * dp] = 2.0 * xr;
             a2[2 * dp + 1] = 2.0 * xi;
             a2[2 * dm] = -2.0 * xr;
             a2[2 * dm + 1] = -2.0 * xi;
         }
     }
+    if (it.rows_only) set_direct();
 }
 
 // ---------------------------------------------------------------------------

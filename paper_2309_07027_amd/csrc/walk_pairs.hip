@@ -122,13 +122,23 @@ __global__ __launch_bounds__(kPairThreads) void pair_walk_kernel(PairArgs A)
         __syncthreads();
         const uint32_t h0 = d.mid * wave / kPairWaves, h1 = d.mid * (wave + 1) / kPairWaves;
         double r, i, m;
-        pair_walk<POW>(d, kconst(A.tables + d.mid_off), kconst(A.tables + d.weight_off),
-                       kconst(A.tables + d.const_off), h0, h1,
-                       [&](uint32_t p, PairSums& q) {
+        const bool direct = a[2 * (size_t)d.r * d.n] != 0.0;  // set by the gather (walk.hip)
+        if (direct) {
+            pair_walk_direct<POW>(d, a, kconst(A.tables + d.mid_off), kconst(A.tables + d.weight_off), h0, h1,
+                                  [&](uint32_t p, cpx* c) {
+                                      c[0] = parts[p * kPairSlots * kWave + lane];
+                                      c[1] = parts[(p * kPairSlots + 1) * kWave + lane];
+                                  },
+                                  r, i, m);
+        } else {
+            pair_walk<POW>(d, kconst(A.tables + d.mid_off), kconst(A.tables + d.weight_off),
+                           kconst(A.tables + d.const_off), h0, h1,
+                           [&](uint32_t p, PairSums& q) {
 #pragma unroll
-                           for (int s = 0; s < kPairSlots; ++s) q.s[s] = parts[(p * kPairSlots + s) * kWave + lane];
-                       },
-                       r, i, m);
+                               for (int s = 0; s < kPairSlots; ++s) q.s[s] = parts[(p * kPairSlots + s) * kWave + lane];
+                           },
+                           r, i, m);
+        }
         __syncthreads();  // the lane parts are no longer read
         red[threadIdx.x] = r;
         red[kPairThreads + threadIdx.x] = i;

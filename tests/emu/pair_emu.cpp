@@ -79,6 +79,15 @@ int main()
         weight[h] = pair_mid_weight(d, ri, binom.data(), h);
     }
     for (uint32_t p = 0; p < np; ++p) pair_constants(d, a.data(), p, consts + (size_t)p * 2 * kPairConsts);
+    // the gather's choice between differences and products of column sums
+    uint64_t inner_rows = 0;
+    for (int k : pair->inner) inner_rows |= uint64_t(1) << k;
+    bool direct = false;
+    for (int j = 0; j < n; ++j)
+        direct = direct || !differences_serve(r, inner_rows, [&](int k) {
+                     const double* x = &a[2 * ((size_t)k * n + j)];
+                     return std::fabs(x[0]) + std::fabs(x[1]);
+                 });
     double sr = 0.0, si = 0.0, sa = 0.0;
     for (uint32_t u = 0; u < d.units; ++u) {
         const uint32_t g = u / d.high, high = u % d.high;
@@ -99,7 +108,15 @@ int main()
                 const uint32_t h0 = d.mid * wave / kPairWaves, h1 = d.mid * (wave + 1) / kPairWaves;
                 double x, y, z;
                 auto get = [&](uint32_t p, PairSums& q) { q = parts[p]; };
-                if (pow >= 2)
+                auto sums = [&](uint32_t p, cpx* c) {
+                    c[0] = parts[p].s[0];
+                    c[1] = parts[p].s[1];
+                };
+                if (direct && pow >= 2)
+                    pair_walk_direct<true>(d, kconst(a.data()), kconst(tab.data()), kconst(weight), h0, h1, sums, x, y, z);
+                else if (direct)
+                    pair_walk_direct<false>(d, kconst(a.data()), kconst(tab.data()), kconst(weight), h0, h1, sums, x, y, z);
+                else if (pow >= 2)
                     pair_walk<true>(d, kconst(tab.data()), kconst(weight), kconst(consts), h0, h1, get, x, y, z);
                 else
                     pair_walk<false>(d, kconst(tab.data()), kconst(weight), kconst(consts), h0, h1, get, x, y, z);
