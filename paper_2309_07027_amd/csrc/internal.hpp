@@ -235,6 +235,12 @@ constexpr int minor_pairs_per_wave(int K)
     const int np = ((K + 1) / 2 + kMinorWaves - 1) / kMinorWaves;
     return np > kMinorMinPairs ? np : kMinorMinPairs;
 }
+// Complex elements of a walk's steps: per kept row but the last two rows with the
+// changes of b_1, b_2 and the digits' differences for each pair.
+constexpr uint64_t minor_step_elems(int r, int digits, int np)
+{
+    return 2 * (uint64_t)(r - 1) * (uint64_t)(2 + digits) * (uint64_t)np * kMinorWaves;
+}
 // Wavefronts that own so many pairs; the others own one less (two at least: with
 // one the chain of a step is all that is left).  Which SIMD has the smaller
 // shares changes from work group to work group by itself; turning them by hand in

@@ -64,7 +64,7 @@ __device__ __forceinline__ double minor_coefs(const WalkArgs& A, const PermDesc&
 // their magnitude sums (the modulus of the addend at the unit's last position,
 // the inner digits at the lane's lowest bits, times the addends it stands for).
 // The item's rows hold ROWNP pairs for each wavefront.
-template <int NP, int DIGITS, int ROWNP>
+template <int NP, int DIGITS, int ROWNP, bool DIRECT>
 __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S,
                                                  uint32_t wave, uint32_t first)
 {
@@ -82,16 +82,17 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
 
     constexpr int kCols = 2 * NP;
     const size_t ld = 4 * (size_t)ROWNP * kMinorWaves;              // doubles per kept row
-    constexpr int kStep = MinorLane<NP, DIGITS>::kStep;
+    constexpr int kStep = MinorLane<NP, DIGITS, DIRECT>::kStep;
     const size_t step_ld = kStep * (size_t)ROWNP * kMinorWaves;     // doubles per step row
     kptr<double> a = kconst(A.a + 2 * d.a_off + first * 4);
+    kptr<double> inner = a + (int64_t)((size_t)(d.r - 1) * ld);     // x's row
     kptr<double> steps = kconst(A.a2 + 2 * d.a2_off + first * kStep);
     kptr<TabEntry> tab = kconst(d.tab);
     const int cols = (int)d.n - 2 * (int)first;                     // real columns from there on (may be < 0)
     const uint32_t Q = d.Q;
     auto coef = [&](int k) { return (double)S.coef[k][lane]; };
 
-    MinorLane<NP, DIGITS> L;
+    MinorLane<NP, DIGITS, DIRECT> L;
     L.clear();
     uint32_t buf = 0;
     // e of both x: the weight times the other wavefronts' products.  From its
@@ -114,7 +115,7 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
     };
     // K of the two inner digits: the change of D when x' grows
     double K[DIGITS > 1 ? 2 * NP : 1];
-    if constexpr (DIGITS > 1) {
+    if constexpr (DIGITS > 1 && !DIRECT) {
         kptr<double> row = steps + (2 * (size_t)(d.r - 2) + 1) * step_ld;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
@@ -133,15 +134,23 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         uint32_t next_row = t0 + 1 < t1 ? uniform_u32(tab[t0 + 1].row) : 0u;
         for (uint32_t t = t0; t < t1; ++t) {
             cpx e0, e1;
+            kptr<double> here = inner;
+            if constexpr (DIRECT) {
+                // read the inner rows anew each step: held over the loop they take
+                // registers that then spill
+                int32_t zero = 0;
+                asm volatile("" : "+s"(zero));
+                here = inner + zero;
+            }
             __builtin_amdgcn_s_setprio(1);
             BBFG_SCHED_BARRIER();
-            L.forward();
+            L.forward(here, ld);
             exchange(ws, e0, e1);
             if constexpr (DIGITS > 1) {
-                L.template backward<false>(e0, e1);
+                L.template backward<false>(e0, e1, here, ld);
                 __builtin_amdgcn_s_setprio(1);
                 BBFG_SCHED_BARRIER();
-                L.forward_second(K);
+                L.forward_second(K, here, ld);
                 exchange(-ws, e0, e1);
             }
             // the next step's changes are fetched under the rest of this step (not
@@ -155,13 +164,12 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
             ws = w * tab[t + 1 < t1 ? t + 1 : t].s;
             next_row = uniform_u32(tab[t + 2 < t1 ? t + 2 : t].row);
             BBFG_SCHED_BARRIER();
-            L.template backward<true>(e0, e1);
+            L.template backward<true>(e0, e1, here, ld);
             L.advance(s);
         }
         lin += (uint64_t)(t1 - t0);
         __syncthreads();  // the coefficients and weights may be overwritten
     }
-    kptr<double> inner = a + (int64_t)((size_t)(d.r - 1) * ld);
     const uint64_t slot = d.part_base + (uint64_t)u_local * d.targets + 2 * first;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -189,7 +197,7 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
         cpx c1 = L.b1[p], c2 = L.b2[p];
 #pragma unroll
         for (int i = 0; i < DIGITS; ++i) {
-            const double x = (lane >> i & 1u) ? -2.0 : 0.0;
+            const double x = (lane >> i & 1u) ? (DIRECT ? -1.0 : -2.0) : (DIRECT ? 1.0 : 0.0);
             kptr<double> row = inner + -(int64_t)((size_t)i * ld);
             c1 = {fmar(x, row[4 * p], c1.r), fmar(x, row[4 * p + 1], c1.i)};
             c2 = {fmar(x, row[4 * p + 2], c2.r), fmar(x, row[4 * p + 3], c2.i)};
@@ -218,18 +226,28 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
 
 // The wavefronts of a work group meet at the same barriers whether they own NP
 // pairs or NP - 1: all that is walked is the unit's.
-template <int NP, int DIGITS>
+template <int NP, int DIGITS, bool DIRECT>
 __device__ __forceinline__ void minor_pairs_share(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
                                                   uint32_t wave)
 {
     const uint32_t full = (uint32_t)minor_full_waves(d.n);
     if constexpr (NP > kMinorMinPairs) {
         if (wave >= full) {
-            minor_pairs_unit<NP - 1, DIGITS, NP>(A, d, u, S, wave, wave * (NP - 1) + full);
+            minor_pairs_unit<NP - 1, DIGITS, NP, DIRECT>(A, d, u, S, wave, wave * (NP - 1) + full);
             return;
         }
     }
-    minor_pairs_unit<NP, DIGITS, NP>(A, d, u, S, wave, wave * NP);
+    minor_pairs_unit<NP, DIGITS, NP, DIRECT>(A, d, u, S, wave, wave * NP);
+}
+
+// With differences, or as the gather's flag says (behind the steps), without.
+template <int NP, int DIGITS>
+__device__ __forceinline__ void minor_pairs_way(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
+                                                uint32_t wave)
+{
+    const bool direct = kconst(A.a2 + 2 * (d.a2_off + minor_step_elems(d.r, DIGITS, NP)))[0] != 0.0;
+    if (direct) minor_pairs_share<NP, DIGITS, true>(A, d, u, S, wave);
+    else minor_pairs_share<NP, DIGITS, false>(A, d, u, S, wave);
 }
 
 template <int NPMIN, int NPMAX>
@@ -240,11 +258,11 @@ __device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const Pe
         if (minor_pairs_per_wave(d.n) == NPMIN) {
             if constexpr (NPMIN == kMinorTwoDigits) {
                 if (d.col_pow == 2) {
-                    minor_pairs_share<NPMIN, 2>(A, d, u, S, wave);
+                    minor_pairs_way<NPMIN, 2>(A, d, u, S, wave);
                     return;
                 }
             }
-            minor_pairs_share<NPMIN, 1>(A, d, u, S, wave);
+            minor_pairs_way<NPMIN, 1>(A, d, u, S, wave);
         } else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S, wave);
     }
 }

@@ -27,6 +27,12 @@
 // moves.  Measured (kernel): 24 columns, 2^22 addends, 0.193 -> 0.087 ms; 30
 // columns, 2^28, 4.96 -> 3.1 ms; 35 columns, 34 photons at random, 12.5 -> 6.2 ms.
 //
+// Where an inner row dominates a column the products at x = 1 and x' = 1 are formed
+// from the column sums there, not from differences, and each addend's Z is
+// accumulated with its own column sums (DIRECT; the reason is pair_core.hpp's).
+// The inner rows are then added to the sums of the others at each step, so that
+// they leave no rounding of their size in a sum where they cancel.
+//
 // Compiled by hipcc for the kernel and by a host compiler for the CPU emulation.
 #pragma once
 
@@ -41,15 +47,18 @@ BBFG_FN cpx cmul_uniform(cpx a, double s) { return {a.r * s, a.i * s}; }
 // DIGITS: inner binary digits, 1 or 2.  With a second digit x', taken as a second
 // half of the step, b_1 and b_2 serve four addends: y and D move to x' = 1 by
 // their differences (E, and the constant K of the two digits), and the sums over
-// both halves are accumulated at once.
-template <int NP, int DIGITS>
+// both halves are accumulated at once.  DIRECT: no differences, and the column sums
+// held are those without the inner rows.
+template <int NP, int DIGITS, bool DIRECT>
 struct MinorLane {
-    cpx b1[NP], b2[NP], D[NP];         // column sums, difference of the product in x, at x = x' = 0
-    cpx E[DIGITS > 1 ? NP : 1];        // its difference in x'
+    cpx b1[NP], b2[NP];                // column sums at x = x' = 0
+    cpx D[DIRECT ? 1 : NP];            // difference of the product in x
+    cpx E[DIGITS > 1 && !DIRECT ? NP : 1];  // its difference in x'
     cpx y[NP], v[NP];                  // product at x = 0 and x = 1 of the current half
-    cpx acc1[NP], acc2[NP], G[NP];     // sums of Z c_2, Z c_1, and of the signed Z at x = 1
-    cpx F[DIGITS > 1 ? NP : 1];        // the same at x' = 1
-    cpx S[DIGITS > 1 ? NP : 1];        // the first half's sums
+    cpx acc1[NP], acc2[NP];            // sums of Z c_2, Z c_1
+    cpx G[DIRECT ? 1 : NP];            // sum of the signed Z at x = 1
+    cpx F[DIGITS > 1 && !DIRECT ? NP : 1];  // the same at x' = 1
+    cpx S[DIGITS > 1 && !DIRECT ? NP : 1];  // the first half's sums
 
     // doubles per pair of a step: the changes of b_1, b_2, D (and E)
     static constexpr int kStep = 2 * (2 + DIGITS);
@@ -65,8 +74,9 @@ struct MinorLane {
     {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            acc1[p] = acc2[p] = G[p] = {0.0, 0.0};
-            if constexpr (DIGITS > 1) F[p] = {0.0, 0.0};
+            acc1[p] = acc2[p] = {0.0, 0.0};
+            if constexpr (!DIRECT) G[p] = {0.0, 0.0};
+            if constexpr (DIGITS > 1 && !DIRECT) F[p] = {0.0, 0.0};
         }
     }
 
@@ -89,7 +99,7 @@ struct MinorLane {
             b2[p] = {2 * p + 1 < cols ? 0.0 : 1.0, 0.0};
         }
         kptr<double> row = a;
-        for (int k = 0; k < r; ++k) {
+        for (int k = 0; k < (DIRECT ? r - DIGITS : r); ++k) {
             const double c = coef(k);
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
@@ -98,8 +108,9 @@ struct MinorLane {
             }
             if (k + 1 < r) row = row + (int64_t)ld;
         }
+        if constexpr (DIRECT) return;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int p = 0; p < (DIRECT ? 0 : NP); ++p) {
             cpx d1, d2;
             digit_step(row, p, d1, d2);
             D[p] = cfma(d1, b2[p], cfma(d2, b1[p], cmul(d1, d2)));
@@ -117,28 +128,63 @@ struct MinorLane {
         for (int p = 0; p < NP; ++p) {
             b1[p] = cadd(b1[p], s + kStep * p);
             b2[p] = cadd(b2[p], s + kStep * p + 2);
+            if constexpr (DIRECT) continue;
             D[p] = cadd(D[p], s + kStep * p + 4);
             if constexpr (DIGITS > 1) E[p] = cadd(E[p], s + kStep * p + 6);
         }
     }
 
+    // b and f times a row's entry at e
+    static BBFG_FN cpx joined(cpx b, double f, kptr<double> row, int e)
+    {
+        return {fmar(f, row[e], b.r), fmar(f, row[e + 1], b.i)};
+    }
+    // DIRECT: pair p's column sums at x' = 0 or 1 but for x's row
+    template <bool SECOND>
+    BBFG_FN void without_x(int p, kptr<double> inner, size_t ld, cpx& c1, cpx& c2) const
+    {
+        c1 = b1[p];
+        c2 = b2[p];
+        if constexpr (DIGITS > 1) {
+            kptr<double> row = inner + -(int64_t)ld;
+            c1 = joined(c1, SECOND ? -1.0 : 1.0, row, 4 * p);
+            c2 = joined(c2, SECOND ? -1.0 : 1.0, row, 4 * p + 2);
+        }
+    }
+    template <bool SECOND>
+    BBFG_FN void direct_products(int p, kptr<double> inner, size_t ld)
+    {
+        cpx c1, c2;
+        without_x<SECOND>(p, inner, ld, c1, c2);
+        y[p] = cmul(joined(c1, 1.0, inner, 4 * p), joined(c2, 1.0, inner, 4 * p + 2));
+        v[p] = cmul(joined(c1, -1.0, inner, 4 * p), joined(c2, -1.0, inner, 4 * p + 2));
+    }
+
     // This wavefront's product at both x of the first half, or (after backward of
-    // the first) of the second; K: kStep doubles apart, K of the two digits.
-    BBFG_FN void forward()
+    // the first) of the second; K: K of the two digits; inner points at x's row.
+    BBFG_FN void forward(kptr<double> inner, size_t ld)
     {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            y[p] = cmul(b1[p], b2[p]);
-            v[p] = cadd(y[p], D[p]);
+            if constexpr (DIRECT) {
+                direct_products<false>(p, inner, ld);
+            } else {
+                y[p] = cmul(b1[p], b2[p]);
+                v[p] = cadd(y[p], D[p]);
+            }
         }
         products();
     }
-    BBFG_FN void forward_second(const double* K)
+    BBFG_FN void forward_second(const double* K, kptr<double> inner, size_t ld)
     {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            y[p] = cadd(y[p], E[p]);
-            v[p] = cadd(cadd(y[p], D[p]), K + 2 * p);
+            if constexpr (DIRECT) {
+                direct_products<true>(p, inner, ld);
+            } else {
+                y[p] = cadd(y[p], E[p]);
+                v[p] = cadd(cadd(y[p], D[p]), K + 2 * p);
+            }
         }
         products();
     }
@@ -189,13 +235,23 @@ struct MinorLane {
     // Accumulates a half's two addends; e0, e1: the weight (its sign turned in the
     // second half) times the other wavefronts' products; x enters with (-1)^x.
     template <bool LAST>
-    BBFG_FN void backward(cpx e0, cpx e1)
+    BBFG_FN void backward(cpx e0, cpx e1, kptr<double> inner, size_t ld)
     {
         cpx z0[NP], z1[NP];
         others(0, e0, z0);
         others(1, e1, z1);
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
+            if constexpr (DIRECT) {
+                cpx c1, c2;
+                without_x<(DIGITS > 1 && LAST)>(p, inner, ld, c1, c2);
+                cmac(acc1[p], joined(c2, 1.0, inner, 4 * p + 2), z0[p]);
+                cmac(acc2[p], joined(c1, 1.0, inner, 4 * p), z0[p]);
+                const cpx less = {-z1[p].r, -z1[p].i};
+                cmac(acc1[p], joined(c2, -1.0, inner, 4 * p + 2), less);
+                cmac(acc2[p], joined(c1, -1.0, inner, 4 * p), less);
+                continue;
+            }
             cpx s = csub(z0[p], z1[p]);
             G[p] = csub(G[p], z1[p]);
             if constexpr (DIGITS > 1) {
@@ -217,6 +273,9 @@ struct MinorLane {
     // inner points at x's row (x' 's lies ld doubles before).
     BBFG_FN void result(int p, kptr<double> inner, size_t ld, cpx& first, cpx& second) const
     {
+        first = acc1[p];
+        second = acc2[p];
+        if constexpr (DIRECT) return;
         cpx d1, d2;
         digit_step(inner, p, d1, d2);
         first = cfma(d2, G[p], acc1[p]);

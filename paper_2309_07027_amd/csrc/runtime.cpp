@@ -616,8 +616,8 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         const uint64_t rows = (uint64_t)it.plan->r;
         if (!by_pairs(it)) return rows * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
         if (!minors) return rows * (uint64_t)nc + 1;  // a, the flag
-        const uint64_t pairs = (uint64_t)minor_pairs_per_wave(nc) * kMinorWaves;
-        return rows * 2 * pairs + 2 * (rows - 1) * (2 + (uint64_t)it.plan->minor_digits) * pairs;
+        const int np = minor_pairs_per_wave(nc);  // rows, steps, the flag
+        return rows * 2 * (uint64_t)np * kMinorWaves + minor_step_elems(it.plan->r, it.plan->minor_digits, np) + 1;
     };
     size_t npair = 0;
     int np_max = 0;
@@ -801,7 +801,10 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.rows_only = pair ? 1 : 0;
         q.np = np;
         q.digits = p.minor_digits;
-        if (pair && !minors) {
+        if (np) {
+            q.inner_rows = ((uint64_t(1) << p.minor_digits) - 1) << (p.r - p.minor_digits);
+            q.direct_off = d.a2_off + minor_step_elems(p.r, p.minor_digits, np);
+        } else if (pair) {
             q.inner_rows = pair_inner_rows(*p.pair);
             q.direct_off = d.a2_off;
         }

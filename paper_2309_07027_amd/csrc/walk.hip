@@ -104,6 +104,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
             row[1] = ai;
             row[2] = br;
             row[3] = bi;
+            if (2 * p < n) mag[k * n + 2 * p] = __builtin_fabs(ar) + __builtin_fabs(ai);
+            if (2 * p + 1 < n) mag[k * n + 2 * p + 1] = __builtin_fabs(br) + __builtin_fabs(bi);
             if (k + 1 == r) continue;
             const int step = 2 * (2 + it.digits);
             double* down = a2 + 2 * it.a2_off + step * ((size_t)(2 * k) * pairs + p);
@@ -121,6 +123,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_rows_kernel(
                 up[q] = -v[q];
             }
         }
+        set_direct();
         return;
     }
     for (int e = threadIdx.x; e < r * n; e += blockDim.x) {

@@ -21,11 +21,11 @@ using namespace bbfg;
 
 namespace {
 
-template <int NP, int DIGITS>
-void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<double>& out)
+template <int NP, int DIGITS, bool DIRECT>
+void run_way(const HostPlan& P, int K, const std::vector<double>& A, std::vector<double>& out)
 {
     const int r = P.r, pairs = NP * kMinorWaves;
-    constexpr int kStep = MinorLane<NP, DIGITS>::kStep;
+    constexpr int kStep = MinorLane<NP, DIGITS, DIRECT>::kStep;
     // the prep kernel's layout
     std::vector<double> rows(4 * (size_t)r * pairs, 0.0), steps(kStep * (size_t)(2 * (r - 1)) * pairs);
     for (int k = 0; k < r; ++k)
@@ -63,8 +63,8 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
             if (lane_idx >= P.lane_product) continue;
             // wavefronts of NP pairs, and those of one less
             constexpr int NL = NP > kMinorMinPairs ? NP - 1 : NP;
-            MinorLane<NP, DIGITS> L[kMinorWaves];
-            MinorLane<NL, DIGITS> less[kMinorWaves];
+            MinorLane<NP, DIGITS, DIRECT> L[kMinorWaves];
+            MinorLane<NL, DIGITS, DIRECT> less[kMinorWaves];
             const int full = minor_full_waves(K);
             auto wave = [&](int v, auto f) {
                 if (v < full) f(L[v], NP, (size_t)(v * NP));
@@ -116,10 +116,15 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
                                                             all[(v + 3) % kMinorWaves][x]),
                                                        ws);
                     };
-                    waves([&](int, auto& l, int, size_t) { l.forward(); });
+                    auto inner = [&](size_t first) {
+                        return kconst(rows.data()) + (int64_t)((size_t)(r - 1) * ld + 4 * first);
+                    };
+                    waves([&](int, auto& l, int, size_t first) { l.forward(inner(first), ld); });
                     exchange(w * e.s);
                     if constexpr (DIGITS > 1) {
-                        waves([&](int v, auto& l, int, size_t) { l.template backward<false>(o[v][0], o[v][1]); });
+                        waves([&](int v, auto& l, int, size_t first) {
+                            l.template backward<false>(o[v][0], o[v][1], inner(first), ld);
+                        });
                         waves([&](int, auto& l, int pairs_of, size_t first) {
                             double K[2 * NP];
                             const double* row = &steps[(size_t)(2 * (r - 2) + 1) * step_ld + kStep * first];
@@ -127,11 +132,13 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
                                 K[2 * p] = row[kStep * p + 4];
                                 K[2 * p + 1] = row[kStep * p + 5];
                             }
-                            l.forward_second(K);
+                            l.forward_second(K, inner(first), ld);
                         });
                         exchange(-w * e.s);
                     }
-                    waves([&](int v, auto& l, int, size_t) { l.template backward<true>(o[v][0], o[v][1]); });
+                    waves([&](int v, auto& l, int, size_t first) {
+                        l.template backward<true>(o[v][0], o[v][1], inner(first), ld);
+                    });
                 }
                 lin += t1 - t0;
             }
@@ -149,6 +156,21 @@ void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<dou
             });
         }
     }
+}
+
+// With differences or without, as the gather chooses.
+template <int NP, int DIGITS>
+void run(const HostPlan& P, int K, const std::vector<double>& A, std::vector<double>& out)
+{
+    const uint64_t inner_rows = ((uint64_t(1) << DIGITS) - 1) << (P.r - DIGITS);
+    bool direct = false;
+    for (int j = 0; j < K; ++j)
+        direct = direct || !differences_serve(P.r, inner_rows, [&](int k) {
+                     const double* x = &A[2 * ((size_t)P.src_row[(size_t)k] * K + j)];
+                     return std::fabs(x[0]) + std::fabs(x[1]);
+                 });
+    if (direct) run_way<NP, DIGITS, true>(P, K, A, out);
+    else run_way<NP, DIGITS, false>(P, K, A, out);
 }
 
 }  // namespace

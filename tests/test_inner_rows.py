@@ -10,12 +10,16 @@ more rows do so in columns of their own.
 
 A column sum holding entries of size S is rounded at 2^-53 S, beside sums of order
 one: four such columns, each a few roundings, make the bound 16 * 2^-53 S on top
-of the reported estimate, with the oracle in double-double as the reference."""
+of the reported estimate, with the oracle in double-double as the reference.  In
+the leave-one-column-out walk an inner row is added to a sum and taken off it
+twice, so its sums hold 2 S and its bound is twice as wide."""
 import numpy as np
 import pytest
 
 from paper_2309_07027_amd import binding as B
 from paper_2309_07027_amd import inputs as I
+from tests import test_minor_pairs
+from tests.test_minor_pairs import exe as minors_exe  # noqa: F401  (a fixture)
 from tests.test_pair_walk import emulate, exe, rel  # noqa: F401  (exe is a fixture)
 
 U = 2.0 ** -53
@@ -95,3 +99,39 @@ def test_gpu_column_powers(oracle):
     print("case inner rows, column powers", flush=True)
     v, info = B.perm_bbfg_cols(A, M, [2] * 12, with_info=True)
     assert rel(v, oracle.perm_generalized(np.repeat(A, 2, axis=1), M)) <= info["rel_err_est"]
+
+
+def minors_case(K, M, S, kind, seed=0):
+    """Rows of multiplicity one first: the scaled rows are among them."""
+    ones = sum(1 for x in M if x == 1)
+    A = matrix(K, S, kind, seed, rows=ones)
+    rng = np.random.default_rng(seed + 1000)
+    more = rng.standard_normal((len(M) - ones, K)) + 1j * rng.standard_normal((len(M) - ones, K))
+    return np.concatenate([A, more]), np.array(M, dtype=np.int32)
+
+
+def check_minors(oracle, A, M, got, S, est=None):
+    K = A.shape[1]
+    for l in (2, K - 1):
+        ref, absum = oracle.perm_generalized(np.delete(A, l, axis=1), M, with_abs=True)
+        e = est[l] if est is not None else absum / abs(ref) * U * K
+        assert rel(got[l], ref) <= 2 * bound(S, e), (l, S)
+
+
+# 20 columns with one inner row; 27 with two (more than 2^18 addends)
+@pytest.mark.parametrize("K,M,S", [(20, [1] * 19, 1e4), (20, [1] * 19, 1e6), (27, [1] * 18 + [4, 4], 1e6)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_emulated_minors(oracle, minors_exe, K, M, S, kind):  # noqa: F811
+    A, M = minors_case(K, M, S, kind)
+    check_minors(oracle, A, M, test_minor_pairs.emulate(minors_exe, A, M, 0), S)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,M", [(20, [1] * 19), (24, [1] * 14 + [4, 5]), (27, [1] * 14 + [6, 6]),
+                                 (30, [1] * 14 + [7, 8]), (35, [1] * 14 + [10, 10]), (41, [1] * 14 + [13, 13])])
+@pytest.mark.parametrize("kind", KINDS)
+def test_gpu_minors(oracle, K, M, kind):
+    A, M = minors_case(K, M, 1e5, kind, seed=K)
+    print(f"case inner rows, minors K={K} {kind}", flush=True)
+    got, est = B.perm_minors(A, M, with_err=True)
+    check_minors(oracle, A, M, got, 1e5, est)
