@@ -5,9 +5,9 @@
 // loads, each of which depends on the one before (row record -> row, Gray entry
 // -> row) and misses the first time; around it stood a gather launch before and
 // a finalize launch after.  Here everything that describes the permanent comes
-// with the kernel's arguments, each wavefront gathers the rows itself, all at
-// once, into LDS, its Gray entries to one lane each, and the wavefront that
-// stores the last partial adds them all up.  The arithmetic and its order are
+// with the kernel's arguments, each work group gathers the rows itself, all at
+// once, into LDS, each wavefront its Gray entries to one lane each, and the work
+// group that stores the last partial adds them all up.  The arithmetic and its order are
 // those of walk_single_kernel and finalize_kernel.
 //
 // Bound by latency.  perm_bbfg, a call: 8 columns (one unit) 37.5 -> 21.2 us, 16
@@ -136,11 +136,12 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
     // the kept rows, and behind them +2a and -2a of each
     double2* const a = reinterpret_cast<double2*>(rows);
     double2* const a2 = a + d.r * N;
-    const double2* const src = reinterpret_cast<const double2*>(by_value.src);
+    const double* const src = by_value.src;  // a caller's matrix: aligned to its doubles only
 #pragma unroll 4
     for (uint32_t e = threadIdx.x; e < (uint32_t)d.r * N; e += blockDim.x) {
         const uint32_t k = e / N, j = e - k * N;
-        const double2 x = src[(uint64_t)S.src_row[k] * by_value.ld + j];
+        const double* const at = src + 2 * ((uint64_t)S.src_row[k] * by_value.ld + j);
+        const double2 x = {at[0], at[1]};
         a[e] = x;
         a2[2 * k * N + j] = {2.0 * x.x, 2.0 * x.y};
         a2[(2 * k + 1) * N + j] = {-2.0 * x.x, -2.0 * x.y};
