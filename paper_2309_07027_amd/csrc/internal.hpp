@@ -181,13 +181,13 @@ constexpr int kPairMinCols = 4;
 // Device descriptor of one permanent evaluated by the pair walk.  Its units are
 // (lane group, high position) in that order; a unit covers every mid position.
 struct PairDesc {
-    uint64_t a_off;        // element offset of the r x n kept rows (complex) and, behind them, the flag that
-                           //   prep_rows_kernel sets where products are to be formed from the column sums
+    uint64_t a_off;        // element offset of the r x n kept rows (complex)
     uint64_t mid_off;      // double offsets into the tables: mid x np x kPairSlots complex uniform parts,
     uint64_t weight_off;   //   the mid positions' signed weights,
     uint64_t const_off;    //   np x 6 complex constants
     uint64_t part_base;    // first partial slot (one per unit)
     uint32_t unit_base;    // first unit of the item in the launch
+    uint32_t direct_off;   // PrepItem's
     uint32_t units;        // groups * high
     uint32_t rowinfo_off;  // entry offset of the r RowInfo records
     uint32_t lane_product;

@@ -68,7 +68,11 @@ template <int NP, int DIGITS, int ROWNP, bool DIRECT>
 __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDesc& d, uint32_t u_local, MinorShared& S,
                                                  uint32_t wave, uint32_t first)
 {
-    const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t lane = threadIdx.x & (kWave - 1);
+    // What is made of it is not held from unit to unit: for that the bucket of up to
+    // 24 columns spilled, and a kernel that uses scratch memory costs a sampling step
+    // 10 us (16 samples of 24 photons 1.51 -> 1.61 ms).
+    asm volatile("" : "+v"(lane));
     const uint32_t upg = (uint32_t)d.units_per_group;
     const uint32_t g = u_local / upg;
     const uint32_t part = u_local - g * upg;
@@ -156,7 +160,12 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
             // the next step's changes are fetched under the rest of this step (not
             // earlier: a wait for LDS data waits for scalar loads as well); after
             // the last step they are row 0's, and go into sums that are seeded anew
+            // (without differences registers are short, and the fetch follows that rest)
             BBFG_SCHED_BARRIER();
+            if constexpr (DIRECT) {
+                L.template backward<true>(e0, e1, here, ld);
+                BBFG_SCHED_BARRIER();
+            }
             double s[kStep * NP];
             kptr<double> row = steps + (size_t)next_row * step_ld;
 #pragma unroll
@@ -164,7 +173,7 @@ __device__ __forceinline__ void minor_pairs_unit(const WalkArgs& A, const PermDe
             ws = w * tab[t + 1 < t1 ? t + 1 : t].s;
             next_row = uniform_u32(tab[t + 2 < t1 ? t + 2 : t].row);
             BBFG_SCHED_BARRIER();
-            L.template backward<true>(e0, e1, here, ld);
+            if constexpr (!DIRECT) L.template backward<true>(e0, e1, here, ld);
             L.advance(s);
         }
         lin += (uint64_t)(t1 - t0);
@@ -240,17 +249,7 @@ __device__ __forceinline__ void minor_pairs_share(const WalkArgs& A, const PermD
     minor_pairs_unit<NP, DIGITS, NP, DIRECT>(A, d, u, S, wave, wave * NP);
 }
 
-// With differences, or as the gather's flag says (behind the steps), without.
-template <int NP, int DIGITS>
-__device__ __forceinline__ void minor_pairs_way(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
-                                                uint32_t wave)
-{
-    const bool direct = kconst(A.a2 + 2 * (d.a2_off + minor_step_elems(d.r, DIGITS, NP)))[0] != 0.0;
-    if (direct) minor_pairs_share<NP, DIGITS, true>(A, d, u, S, wave);
-    else minor_pairs_share<NP, DIGITS, false>(A, d, u, S, wave);
-}
-
-template <int NPMIN, int NPMAX>
+template <int NPMIN, int NPMAX, bool DIRECT>
 __device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const PermDesc& d, uint32_t u, MinorShared& S,
                                                      uint32_t wave)
 {
@@ -258,12 +257,12 @@ __device__ __forceinline__ void dispatch_minor_pairs(const WalkArgs& A, const Pe
         if (minor_pairs_per_wave(d.n) == NPMIN) {
             if constexpr (NPMIN == kMinorTwoDigits) {
                 if (d.col_pow == 2) {
-                    minor_pairs_way<NPMIN, 2>(A, d, u, S, wave);
+                    minor_pairs_share<NPMIN, 2, DIRECT>(A, d, u, S, wave);
                     return;
                 }
             }
-            minor_pairs_way<NPMIN, 1>(A, d, u, S, wave);
-        } else dispatch_minor_pairs<NPMIN + 1, NPMAX>(A, d, u, S, wave);
+            minor_pairs_share<NPMIN, 1, DIRECT>(A, d, u, S, wave);
+        } else dispatch_minor_pairs<NPMIN + 1, NPMAX, DIRECT>(A, d, u, S, wave);
     }
 }
 
@@ -281,8 +280,13 @@ __global__ __launch_bounds__(kMinorThreads) __attribute__((amdgpu_waves_per_eu(N
         __syncthreads();
         if (u >= A.total_units) break;
         const uint32_t item = item_of_unit(A, u);
+        // the gather's flag, at an address that does not wait for the descriptor (a unit
+        // of a sampling step is a few us long)
+        const double direct = kconst(A.a + 2 * (size_t)item)[0];
         const PermDesc d = A.descs[item];
-        dispatch_minor_pairs<kMinorMinPairs, NPMAX>(A, d, u - (uint32_t)d.unit_base, S, wave);
+        if (direct != 0.0)
+            dispatch_minor_pairs<kMinorMinPairs, NPMAX, true>(A, d, u - (uint32_t)d.unit_base, S, wave);
+        else dispatch_minor_pairs<kMinorMinPairs, NPMAX, false>(A, d, u - (uint32_t)d.unit_base, S, wave);
     }
 }
 

@@ -201,8 +201,8 @@ try {
         src = Astage;
     }
     PermDesc& d = *reinterpret_cast<PermDesc*>(H + o_desc);
-    d.a_off = 0;
-    d.a2_off = (uint64_t)r * n;
+    d.a_off = P.pair ? 1 : 0;  // behind the flag
+    d.a2_off = d.a_off + (uint64_t)r * n;
     d.tab = tab;
     d.units = P.pair ? P.pair->units : P.units;
     d.units_per_group = P.units_per_group;
@@ -220,6 +220,7 @@ try {
     PrepItem& q = *reinterpret_cast<PrepItem*>(H + o_prep);
     q.src = src;
     q.ld = (uint32_t)n_cols;
+    q.a_off = d.a_off;
     q.a2_off = d.a2_off;
     q.srcrow_off = 0;
     q.srccol_off = kIdentityCols;
@@ -228,7 +229,7 @@ try {
     q.rows_only = P.pair ? 1 : 0;
     if (P.pair) {
         q.inner_rows = pair_inner_rows(*P.pair);
-        q.direct_off = d.a2_off;  // behind the rows
+        q.direct_off = 0;
     }
     uint32_t* hs = reinterpret_cast<uint32_t*>(H + o_src);
     for (int k = 0; k < r; ++k) hs[k] = (uint32_t)P.src_row[(size_t)k];
@@ -236,7 +237,7 @@ try {
 
     uint64_t pair_doubles = 0, pair_positions = 0;
     if (P.pair)
-        pair_positions = fill_pair_desc(*reinterpret_cast<PairDesc*>(H + o_pair), d, P, 0, &pair_doubles);
+        pair_positions = fill_pair_desc(*reinterpret_cast<PairDesc*>(H + o_pair), d, P, 0, 0, &pair_doubles);
 
     WalkArgs W;
     std::memset(&W, 0, sizeof W);

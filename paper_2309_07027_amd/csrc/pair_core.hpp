@@ -108,17 +108,17 @@ template <typename Mag>
 BBFG_FN bool differences_serve(int r, uint64_t inner_rows, Mag mag)
 {
     double top = 0.0;
-    int others = 0, near = 0;
-    for (int k = 0; k < r; ++k)
-        if (inner_rows >> k & 1u) {
-            const double m = mag(k);
-            top = m > top ? m : top;
-        }
-    for (int k = 0; k < r; ++k)
-        if (!(inner_rows >> k & 1u)) {
-            ++others;
-            near += kInnerRange * mag(k) >= top ? 1 : 0;
-        }
+    int inner = 0, near = 0;
+    for (uint64_t rows = inner_rows; rows; rows &= rows - 1, ++inner) {
+        const double m = mag(__builtin_ctzll(rows));
+        top = m > top ? m : top;
+    }
+#pragma unroll 8
+    for (int k = 0; k < r; ++k) {  // loads first: nothing here depends on the row before
+        const double m = kInnerRange * mag(k);
+        near += (int)((inner_rows >> k & 1u) == 0) & (int)(m >= top);
+    }
+    const int others = r - inner;
     return 2 * near >= others;
 }
 

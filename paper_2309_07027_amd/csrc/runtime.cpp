@@ -494,12 +494,14 @@ uint64_t pair_inner_rows(const PairPlan& p)
     return rows;
 }
 
-uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles)
+uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t direct_off,
+                        uint64_t* table_doubles)
 {
     const PairPlan& pp = *p.pair;
     std::memset(&q, 0, sizeof q);
     q.a_off = d.a_off;
     q.part_base = d.part_base;
+    q.direct_off = (uint32_t)direct_off;
     q.unit_base = (uint32_t)unit_base;
     q.units = (uint32_t)pp.units;
     q.rowinfo_off = d.rowinfo_off;
@@ -615,9 +617,9 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     auto arena_of = [&](const PermItem& it, int nc) -> uint64_t {
         const uint64_t rows = (uint64_t)it.plan->r;
         if (!by_pairs(it)) return rows * (uint64_t)nc * 3u;  // a (r x n) + a2 (2r x n)
-        if (!minors) return rows * (uint64_t)nc + 1;  // a, the flag
-        const int np = minor_pairs_per_wave(nc);  // rows, steps, the flag
-        return rows * 2 * (uint64_t)np * kMinorWaves + minor_step_elems(it.plan->r, it.plan->minor_digits, np) + 1;
+        if (!minors) return rows * (uint64_t)nc;
+        const int np = minor_pairs_per_wave(nc);  // rows, steps
+        return rows * 2 * (uint64_t)np * kMinorWaves + minor_step_elems(it.plan->r, it.plan->minor_digits, np);
     };
     size_t npair = 0;
     int np_max = 0;
@@ -677,6 +679,10 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         a_elems += arena_of(it, nc);
         if (!by_pairs(it)) nmax = std::max(nmax, nc);
     }
+
+    // the arena starts with a flag per item, for the walks over pairs
+    const uint64_t n_flags = npair ? nitem : 0;
+    a_elems += n_flags;
 
     // unit numbering of each launch: longest units first (items ordered by
     // per-unit cost)
@@ -764,7 +770,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         std::memcpy(hr + p->slot_rowinfo, (p->pair && !f32 ? p->pair->rows : p->rows).data(),
                     sizeof(RowInfo) * (size_t)p->r);
     for (const Upload& u : uploads) std::memcpy(H + off_tabs + u.off, u.plan->table->data(), u.bytes);
-    uint64_t a_cursor = 0;
+    uint64_t a_cursor = n_flags;
     size_t s_cursor = 0, c_cursor = 0;
     for (size_t i = 0; i < nitem; ++i) {
         const HostPlan& p = *items[i].plan;
@@ -801,13 +807,9 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         q.rows_only = pair ? 1 : 0;
         q.np = np;
         q.digits = p.minor_digits;
-        if (np) {
-            q.inner_rows = ((uint64_t(1) << p.minor_digits) - 1) << (p.r - p.minor_digits);
-            q.direct_off = d.a2_off + minor_step_elems(p.r, p.minor_digits, np);
-        } else if (pair) {
-            q.inner_rows = pair_inner_rows(*p.pair);
-            q.direct_off = d.a2_off;
-        }
+        q.direct_off = i;
+        if (np) q.inner_rows = ((uint64_t(1) << p.minor_digits) - 1) << (p.r - p.minor_digits);
+        else if (pair) q.inner_rows = pair_inner_rows(*p.pair);
         for (int k = 0; k < p.r; ++k) {
             const int ur = p.src_row[(size_t)k];
             hs[s_cursor++] = (uint32_t)(items[i].row_map ? items[i].row_map[ur] : ur);
@@ -841,7 +843,7 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         PairDesc* hpd = reinterpret_cast<PairDesc*>(H + off_pair);
         for (size_t oi = 0; oi < npair; ++oi)
             mid_max = std::max(mid_max, fill_pair_desc(hpd[oi], hd[order_pair[oi]], *items[order_pair[oi]].plan,
-                                                       unit_base[order_pair[oi]], &table_doubles));
+                                                       unit_base[order_pair[oi]], order_pair[oi], &table_doubles));
         unit_map = table_doubles;  // the units' items follow the tables
         if (npair > 1) table_doubles += (pair_units + 1) / 2;
         BBFG_TRY(w.pair_tables.ensure(sizeof(double) * table_doubles));

@@ -278,7 +278,8 @@ struct RunResult {
 // Fills q from its permanent's descriptor d (complete but for its walk fields)
 // and plan, and places its tables at the end of a buffer of *table_doubles
 // doubles.  Returns its mid positions.
-uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t* table_doubles);
+uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint64_t unit_base, uint64_t direct_off,
+                        uint64_t* table_doubles);
 
 // The kept rows of the pair walk's inner digits, a bit each.
 uint64_t pair_inner_rows(const PairPlan& p);

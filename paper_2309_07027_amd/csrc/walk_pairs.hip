@@ -94,6 +94,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_walk_kernel(PairArgs A)
         const uint32_t high = u_local - g * d.high;
         kptr<RowInfo> ri = kconst(A.rowinfo + d.rowinfo_off);
         kptr<double> a = kconst(A.a + 2 * d.a_off);
+        const double direct = kconst(A.a + 2 * (size_t)d.direct_off)[0];  // set by the gather (walk.hip)
         uint32_t lane_idx = g * kWave + lane;
         const bool valid = lane_idx < d.lane_product;
         if (!valid) lane_idx = 0;
@@ -122,8 +123,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_walk_kernel(PairArgs A)
         __syncthreads();
         const uint32_t h0 = d.mid * wave / kPairWaves, h1 = d.mid * (wave + 1) / kPairWaves;
         double r, i, m;
-        const bool direct = a[2 * (size_t)d.r * d.n] != 0.0;  // set by the gather (walk.hip)
-        if (direct) {
+        if (direct != 0.0) {
             pair_walk_direct<POW>(d, a, kconst(A.tables + d.mid_off), kconst(A.tables + d.weight_off), h0, h1,
                                   [&](uint32_t p, cpx* c) {
                                       c[0] = parts[p * kPairSlots * kWave + lane];

@@ -126,10 +126,11 @@ def test_emulated_minors(oracle, minors_exe, K, M, S, kind):  # noqa: F811
     check_minors(oracle, A, M, test_minor_pairs.emulate(minors_exe, A, M, 0), S)
 
 
+# two to six pairs a wavefront; the longer ones once (the oracle takes seconds)
 @pytest.mark.gpu
-@pytest.mark.parametrize("K,M", [(20, [1] * 19), (24, [1] * 14 + [4, 5]), (27, [1] * 14 + [6, 6]),
-                                 (30, [1] * 14 + [7, 8]), (35, [1] * 14 + [10, 10]), (41, [1] * 14 + [13, 13])])
-@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("K,M,kind", [(K, M, kind) for K, M in ((20, [1] * 19), (24, [1] * 16 + [3, 4])) for kind in KINDS] +
+                         [(27, [1] * 18 + [4, 4], "both"), (30, [1] * 18 + [5, 6], "one"),
+                          (35, [1] * 18 + [8, 8], "both"), (41, [1] * 18 + [11, 11], "one")])
 def test_gpu_minors(oracle, K, M, kind):
     A, M = minors_case(K, M, 1e5, kind, seed=K)
     print(f"case inner rows, minors K={K} {kind}", flush=True)
