@@ -312,6 +312,29 @@ BBFG_FN void pair_block_sum(const cpx* P, double& sr, double& si, double& sa)
     sa = a[0];
 }
 
+// A lane's sums over the unit's wavefronts, in double-double as those over lanes
+// and units are (a wavefront's own cover at most 512 addends): (r, i, m, w) starts
+// as the first wavefront's, get(v, r, i, m, w) reads another's; each wavefront has
+// a share w of the lane's weight.
+template <typename Get>
+BBFG_FN void pair_join(Get get, double r, double i, double m, double w, ddv& sr, ddv& si, double& sa)
+{
+    sr = {r, 0.0};
+    si = {i, 0.0};
+#pragma unroll
+    for (int v = 1; v < kPairWaves; ++v) {
+        double vr, vi, vm, vw;
+        get(v, vr, vi, vm, vw);
+        sr = dd_add(sr, vr);
+        si = dd_add(si, vi);
+        m += vm;
+        w *= vw;
+    }
+    sr = dd_mul(sr, w);
+    si = dd_mul(si, w);
+    sa = __builtin_fabs(w) * m;
+}
+
 // What one pair of a block reads by scalar loads: its uniform part and constants.
 struct PairInputs {
     double u[2 * kPairSlots];

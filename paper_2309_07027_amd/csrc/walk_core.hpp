@@ -67,9 +67,33 @@ BBFG_FN ddv dd_add(ddv a, ddv b)
     return dd_fast(s.hi, s.lo);
 }
 
+// a + b for a plain b
+BBFG_FN ddv dd_add(ddv a, double b)
+{
+    ddv s = dd_two_sum(a.hi, b);
+    s.lo += a.lo;
+    return dd_fast(s.hi, s.lo);
+}
+
+// x added to s, not normalised: the rounding errors are summed apart, so that only
+// the additions to s.hi wait for each other
+BBFG_FN void dd_gather(ddv& s, double x)
+{
+    const ddv t = dd_two_sum(s.hi, x);
+    s.hi = t.hi;
+    s.lo += t.lo;
+}
+
 // fused multiply-add in the precision of the operands
 BBFG_FN float fmar(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 BBFG_FN double fmar(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// a b for a plain b
+BBFG_FN ddv dd_mul(ddv a, double b)
+{
+    const double p = a.hi * b;
+    return dd_fast(p, fmar(a.lo, b, fmar(a.hi, b, -p)));
+}
 
 // complex product (a_r + i a_i)(b_r + i b_i): two products, two fused
 template <typename Real>

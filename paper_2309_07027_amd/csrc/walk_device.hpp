@@ -27,12 +27,10 @@ __device__ __forceinline__ uint32_t item_of_unit(const WalkArgs& A, uint32_t u)
     return uniform_u32(kconst(A.uorder)[lo]);
 }
 
-// Wavefront sums of the per-lane results, (r, i) in double-double; the butterfly
+// Wavefront sums of the per-lane results, (sr, si) in double-double; the butterfly
 // leaves the same bits in every lane.
-__device__ __forceinline__ void wave_sum(double r, double i, double& a, ddv& sr, ddv& si)
+__device__ __forceinline__ void wave_sum(ddv& sr, ddv& si, double& a)
 {
-    sr = {r, 0.0};
-    si = {i, 0.0};
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         ddv orr = {__shfl_xor(sr.hi, off), __shfl_xor(sr.lo, off)};
@@ -44,11 +42,17 @@ __device__ __forceinline__ void wave_sum(double r, double i, double& a, ddv& sr,
     }
 }
 
-// The wavefront's sums, stored by lane 0 as the unit's partial record.
-__device__ __forceinline__ void store_partial(double* partials, uint64_t slot, double r, double i, double a)
+__device__ __forceinline__ void wave_sum(double r, double i, double& a, ddv& sr, ddv& si)
 {
-    ddv sr, si;
-    wave_sum(r, i, a, sr, si);
+    sr = {r, 0.0};
+    si = {i, 0.0};
+    wave_sum(sr, si, a);
+}
+
+// The wavefront's sums, stored by lane 0 as the unit's partial record.
+__device__ __forceinline__ void store_partial(double* partials, uint64_t slot, ddv sr, ddv si, double a)
+{
+    wave_sum(sr, si, a);
     if ((threadIdx.x & (kWave - 1)) == 0) {
         double* p = partials + slot * kPartialDoubles;
         p[0] = sr.hi;
@@ -57,6 +61,11 @@ __device__ __forceinline__ void store_partial(double* partials, uint64_t slot, d
         p[3] = si.lo;
         p[4] = a;
     }
+}
+
+__device__ __forceinline__ void store_partial(double* partials, uint64_t slot, double r, double i, double a)
+{
+    store_partial(partials, slot, ddv{r, 0.0}, ddv{i, 0.0}, a);
 }
 
 // Every lane of the wavefront stores the same partial record (the butterfly

@@ -146,14 +146,18 @@ __global__ __launch_bounds__(kPairThreads) void pair_walk_kernel(PairArgs A)
         red[3 * kPairThreads + threadIdx.x] = w;
         __syncthreads();
         if (wave == 0) {
-#pragma unroll
-            for (int v = 1; v < kPairWaves; ++v) {
-                r += red[v * kWave + lane];
-                i += red[kPairThreads + v * kWave + lane];
-                m += red[2 * kPairThreads + v * kWave + lane];
-                w *= red[3 * kPairThreads + v * kWave + lane];
-            }
-            store_partial(A.partials, d.part_base + u_local, w * r, w * i, __builtin_fabs(w) * m);
+            ddv sr, si;
+            double sa;
+            pair_join(
+                [&](int v, double& vr, double& vi, double& vm, double& vw) {
+                    const int at = v * kWave + (int)lane;
+                    vr = red[at];
+                    vi = red[kPairThreads + at];
+                    vm = red[2 * kPairThreads + at];
+                    vw = red[3 * kPairThreads + at];
+                },
+                r, i, m, w, sr, si, sa);
+            store_partial(A.partials, d.part_base + u_local, sr, si, sa);
         }
     }
 }
