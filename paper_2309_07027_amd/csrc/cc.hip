@@ -14,6 +14,7 @@
 
 #include "cc_kernels.hpp"
 #include "internal.hpp"
+#include "walk_core.hpp"
 
 namespace bbfg {
 
@@ -160,7 +161,7 @@ struct EarlyShared {
     CCShared draw;
     double row[kEarlySteps][kEarlySteps][2];           // drawn rows at the sample's columns
     double acc[3 * kEarlySteps][kCCThreads + 1];       // per target: re, im, |re| + |im| of every thread
-    double part[3 * kEarlySteps][4];
+    double sum[3 * kEarlySteps];
 };
 
 template <int K>
@@ -228,28 +229,34 @@ __device__ __forceinline__ void early_minors(EarlyShared& S)
         S.acc[3 * j + 2][t] = acca[j];
     }
     __syncthreads();
-    if (t < 3 * K * 4) {
-        const double* a = S.acc[t >> 2];
-        const uint32_t first = (t & 3u) * (kCCThreads / 4);
-        double s = 0.0;
+    // the threads' sums are added in double-double, as a wavefront's lanes are in the
+    // walks: kParts threads a sum, neighbours starting in different banks
+    constexpr uint32_t kParts = 3 * K * 8 <= kCCThreads ? 8 : 4;
+    constexpr uint32_t kShare = kCCThreads / kParts;
+    if (t < 3 * K * kParts) {
+        const double* a = S.acc[t / kParts] + t % kParts * kShare;
+        const uint32_t turn = t % kParts * (32 / kParts);
+        ddv s = {0.0, 0.0};
 #pragma unroll 8
-        for (uint32_t i = 0; i < kCCThreads / 4; ++i) s += a[first + ((i + 16 * (t & 3u)) & (kCCThreads / 4 - 1))];
-        S.part[t >> 2][t & 3u] = s;
+        for (uint32_t i = 0; i < kShare; ++i) dd_gather(s, a[(i + turn) & (kShare - 1)]);
+        s = dd_fast(s.hi, s.lo);
+#pragma unroll
+        for (uint32_t off = 1; off < kParts; off <<= 1)
+            s = dd_add(s, {__shfl_xor(s.hi, (int)off), __shfl_xor(s.lo, (int)off)});
+        if (t % kParts == 0) S.sum[t / kParts] = s.hi + s.lo;
     }
     __syncthreads();
     if (t < K) {
         const double scale = 1.0 / (double)(1u << (K - 2));
         double v[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double* q = S.part[3 * t + c];
-            v[c] = ((q[0] + q[1]) + (q[2] + q[3])) * scale;
-        }
+        for (int c = 0; c < 3; ++c) v[c] = S.sum[3 * t + c] * scale;
         S.draw.mr[t] = v[0];
         S.draw.mi[t] = v[1];
         S.draw.ma[t] = __builtin_sqrt(v[0] * v[0] + v[1] * v[1]);
-        // kappa u (n + sqrt(Q)) of the K - 1 columns, Q = 1
-        S.draw.me[t] = S.draw.ma[t] > 0.0 ? v[2] / S.draw.ma[t] * (double)K * 0x1.0p-53 : __builtin_inf();
+        // kappa u (n + sqrt(Q)): K - 1 columns, Q Gray positions without a new seed
+        const double coeff = (double)(K - 1) + __builtin_sqrt((double)(1u << (kSigns - kHeld)));
+        S.draw.me[t] = S.draw.ma[t] > 0.0 ? v[2] / S.draw.ma[t] * coeff * 0x1.0p-53 : __builtin_inf();
     }
     __syncthreads();
 }

@@ -45,3 +45,38 @@ def test_a_units_sum_over_its_wavefronts(tmp_path):
     assert hi_r == -15 * sum(x for v, x in enumerate(value) if v not in (1, 6))
     assert hi_i == 15 * sum(x for v, x in enumerate(value) if v not in (2, 15))
     assert sa == 15 * 16
+
+
+def test_a_running_sum(tmp_path):
+    """What the first steps of a sample add their threads' sums with."""
+    total, = run(tmp_path, """
+    ddv s = {0.0, 0.0};
+    for (int i = 0; i < 64; ++i) dd_gather(s, i == 5 ? 0x1p60 : i == 50 ? -0x1p60 : 1.0 + i / 4096.0);
+    std::printf("%a\\n", s.hi + s.lo);
+    return 0;""")
+    assert total == sum(1 + i / 4096 for i in range(64) if i not in (5, 50))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [2, 9, 10, 11, 12, 14])
+def test_estimate_of_the_first_steps_of_a_sample(n):
+    """n photons in one mode: step k's minors are all (k - 1)!, whatever the order, so
+    the estimate is the sum over the steps of dw / w with dw = e (2 sqrt(w) + e),
+    sqrt(w) = k!, e = k! kappa u (k - 1 + sqrt(Q)), Q the Gray positions a thread
+    walks from one seed: one up to ten columns, doubling with each further one."""
+    from math import comb, factorial
+
+    import numpy as np
+
+    from paper_2309_07027_amd import binding as B
+    u = 2.0 ** -53
+    want = 0.0
+    for k in range(2, n + 1):
+        q = k - 1  # photons of a minor
+        kappa = sum(comb(q - 1, d) * abs(q - 2 * d) ** q for d in range(q)) / 2 ** (q - 1) / factorial(q)
+        e = kappa * u * (q + 2.0 ** (max(0, k - 10) / 2))
+        want += e * (2 + e)
+    print(f"case early estimate n={n}", flush=True)
+    got, info = B.bs_sample(np.ones((1, 1), dtype=complex), [n], 3, 0.0, 1, with_info=True)
+    assert (got == n).all()
+    assert abs(info["rel_err_est"] / want - 1) < 1e-9
