@@ -838,15 +838,36 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     };
     fill_index(ix_walk, order, total_units);
     fill_index(ix_pair, order_pair, pair_units);
-    uint64_t table_doubles = 0, unit_map = 0, mid_max = 0;
+    // the pair walk's items in launches whose tables stay within their bound
+    struct PairLaunch {
+        size_t first = 0, items = 0;  // in order_pair
+        uint64_t units = 0, doubles = 0, unit_map = 0, mid_max = 0, grid = 0;
+        uint32_t table_blocks = 0;
+        PairArgs args;
+    };
+    std::vector<PairLaunch> pair_launches;
     if (npair && !minors) {
         PairDesc* hpd = reinterpret_cast<PairDesc*>(H + off_pair);
-        for (size_t oi = 0; oi < npair; ++oi)
-            mid_max = std::max(mid_max, fill_pair_desc(hpd[oi], hd[order_pair[oi]], *items[order_pair[oi]].plan,
-                                                       unit_base[order_pair[oi]], order_pair[oi], &table_doubles));
-        unit_map = table_doubles;  // the units' items follow the tables
-        if (npair > 1) table_doubles += (pair_units + 1) / 2;
-        BBFG_TRY(w.pair_tables.ensure(sizeof(double) * table_doubles));
+        uint64_t most = 0, unit_first = 0;
+        for (size_t oi = 0; oi < npair;) {
+            PairLaunch l;
+            l.first = oi;
+            for (; oi < npair; ++oi, ++l.items) {
+                const size_t i = order_pair[oi];
+                uint64_t doubles = l.doubles;
+                const uint64_t mid = fill_pair_desc(hpd[oi], hd[i], *items[i].plan, unit_base[i] - unit_first, i, &doubles);
+                if (l.items && sizeof(double) * doubles > kPairTableBytes) break;
+                l.doubles = doubles;
+                l.mid_max = std::max(l.mid_max, mid);
+                l.units += units_of(items[i]);
+            }
+            unit_first += l.units;
+            l.unit_map = l.doubles;  // the units' items follow the tables
+            if (l.items > 1) l.doubles += (l.units + 1) / 2;
+            most = std::max(most, l.doubles);
+            pair_launches.push_back(l);
+        }
+        BBFG_TRY(w.pair_tables.ensure(sizeof(double) * most));
     }
 
     // device buffers
@@ -877,8 +898,6 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
     W.counter = w.counter.as<uint32_t>();
     W.total_units = (uint32_t)total_units;
 
-    PairArgs PA;
-    std::memset(&PA, 0, sizeof PA);
     WalkArgs WP = W;  // the leave-one-column-out walk over pairs
     uint64_t pair_grid = 0;
     if (npair && minors) {
@@ -888,22 +907,25 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
         int groups = 1;
         BBFG_TRY(minor_groups(c, np_max, &groups));
         pair_grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, pair_units);
-    } else if (npair) {
-        PA.descs = reinterpret_cast<const PairDesc*>(D + off_pair);
+    }
+    for (PairLaunch& l : pair_launches) {
+        PairArgs& PA = l.args;
+        std::memset(&PA, 0, sizeof PA);
+        PA.descs = reinterpret_cast<const PairDesc*>(D + off_pair) + l.first;
         PA.rowinfo = W.rowinfo;
         PA.a = W.a;
         PA.tables = w.pair_tables.as<double>();
         PA.binom = c.binom;
         PA.partials = W.partials;
-        PA.unit_item = npair > 1 ? reinterpret_cast<uint32_t*>(PA.tables + unit_map) : nullptr;
+        PA.unit_item = l.items > 1 ? reinterpret_cast<uint32_t*>(PA.tables + l.unit_map) : nullptr;
         PA.counter = W.counter + kCounterStride;
-        PA.total_units = (uint32_t)pair_units;
+        PA.total_units = (uint32_t)l.units;
         PA.np_max = (uint32_t)np_max;
         int groups = 1;
         BBFG_TRY(pair_groups(c, np_max, powcols, &groups));
-        pair_grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, pair_units);
+        l.grid = std::min<uint64_t>((uint64_t)groups * (uint64_t)c.n_cu, l.units);
+        l.table_blocks = pair_table_blocks(l.items, l.mid_max, (uint64_t)np_max);
     }
-    const uint32_t table_blocks = npair && !minors ? pair_table_blocks(npair, mid_max, (uint64_t)np_max) : 0;
     int bucket = 0;
     uint64_t grid = total_units;
     if (!single && nwalk) {
@@ -933,10 +955,13 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
                              reinterpret_cast<const uint32_t*>(M + off_col), w.arena_d.as<double>(),
                              w.arena_d.as<double>(), w.arena_f.as<float>(), w.arena_f.as<float>(), W.counter,
                              H, D, short_image ? off_tabs : 0));
-        if (npair && !minors) BBFG_HIP(launch_pair_tables((uint32_t)npair, table_blocks, q, PA));
-        if (timed) BBFG_HIP(hipEventRecord(w.ev0, q));
+        if (timed && pair_launches.empty()) BBFG_HIP(hipEventRecord(w.ev0, q));
         if (npair && minors) BBFG_HIP(launch_minor_pairs(np_max, (uint32_t)pair_grid, q, WP));
-        else if (npair) BBFG_HIP(launch_pair_walk(powcols, (uint32_t)pair_grid, q, PA));
+        for (const PairLaunch& l : pair_launches) {
+            BBFG_HIP(launch_pair_tables((uint32_t)l.items, l.table_blocks, q, l.args));
+            if (timed && l.first == 0) BBFG_HIP(hipEventRecord(w.ev0, q));
+            BBFG_HIP(launch_pair_walk(powcols, (uint32_t)l.grid, q, l.args));
+        }
         if (!nwalk) {
         } else if (single) BBFG_HIP(launch_walk_single(items[0].plan->n, f32, (uint32_t)total_units, q, W, 0u));
         else if (minors) BBFG_HIP(launch_walk_minors(bucket, (uint32_t)grid, q, W));
@@ -984,13 +1009,17 @@ int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, b
             for (size_t i = 0; i < n; ++i) key = (key ^ b[i]) * 1099511628211ull;
         };
         mix(&W, sizeof W);
-        mix(&PA, sizeof PA);
         mix(&WP, sizeof WP);
+        for (const PairLaunch& l : pair_launches) {
+            mix(&l.args, sizeof l.args);
+            const uint64_t shape[] = {l.items, l.grid, l.table_blocks};
+            mix(shape, sizeof shape);
+        }
         const uint64_t extra[] = {nitem, nres, (uint64_t)single, (uint64_t)minors, (uint64_t)powcols, (uint64_t)f32,
                                   (uint64_t)bucket,
                                   grid, L.size, off_desc, off_row, off_prep, off_src, off_col, ix_walk.base, ix_walk.order, ix_walk.chunk,
                                   ix_pair.base, ix_pair.order, ix_pair.chunk, off_pair, off_ritem, off_tabs,
-                                  npair, pair_grid, (uint64_t)table_blocks,
+                                  npair, pair_grid,
                                   (uint64_t)(uintptr_t)H, (uint64_t)(uintptr_t)D, (uint64_t)(uintptr_t)R,
                                   (uint64_t)(uintptr_t)HR, (uint64_t)(uintptr_t)w.arena_d.p,
                                   (uint64_t)(uintptr_t)w.arena_f.p};

@@ -90,6 +90,12 @@ constexpr size_t kShortImageBytes = 64 << 10;
 // At most so many results are written to pinned host memory by finalize itself.
 constexpr uint64_t kDirectResults = 256;
 
+// Most bytes of pair-walk tables held at once.  An item above the pair walk's line
+// has 134 to 363 KB of them, so this is a launch of 3000 to 8000 items, 7 us each
+// or more; a longer batch takes several, whose tables follow each other in one
+// buffer.  (The buffer's growth steps may take half as much again.)
+constexpr uint64_t kPairTableBytes = uint64_t(1) << 30;
+
 // Byte layout helper for one upload of several arrays.
 struct Layout {
     size_t size = 0;

@@ -55,6 +55,7 @@ __global__ __launch_bounds__(kTabThreads) void pair_tables_kernel(PairArgs A)
         }
         __syncthreads();
     }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *A.counter = 0u;  // of the walk that follows
     if (A.unit_item)
         for (uint32_t u = blockIdx.y * blockDim.x + threadIdx.x; u < d.units; u += step) A.unit_item[d.unit_base + u] = blockIdx.x;
     if (blockIdx.y == 0) {
