@@ -438,7 +438,8 @@ typedef struct {
     double host_s; /* part of busy_s spent preparing steps on the host (plans, metadata, launches) */
     double wait_s; /* part of busy_s spent waiting for the device to finish a step */
     double flops;   /* algorithmic FP64 flops of the finished steps' walks (as bbfg_info.flops) */
-    double walk_ms; /* device time of those walks (HIP events around each step's walk kernel) */
+    double walk_ms; /* device time of those walks (HIP events around each step's walk kernels and
+                       around the launch of samples' first steps) */
 } bbfg_server_stats;
 int bs_server_stats(bbfg_server *srv, bbfg_server_stats *out);
 

@@ -115,12 +115,16 @@ Workspace::~Workspace()
     if (ev0) (void)hipEventDestroy(ev0);
     if (ev1) (void)hipEventDestroy(ev1);
     if (done) (void)hipEventDestroy(done);
+    if (early0) (void)hipEventDestroy(early0);
+    if (early1) (void)hipEventDestroy(early1);
 }
 
 int Workspace::init()
 {
     if (!ev0) BBFG_HIP(hipEventCreate(&ev0));
     if (!ev1) BBFG_HIP(hipEventCreate(&ev1));
+    if (!early0) BBFG_HIP(hipEventCreate(&early0));
+    if (!early1) BBFG_HIP(hipEventCreate(&early1));
     if (!done) BBFG_HIP(hipEventCreateWithFlags(&done, hipEventDisableTiming));
     BBFG_TRY(counter.ensure(256));
     if (!short_done.p) {

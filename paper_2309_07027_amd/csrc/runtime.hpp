@@ -118,6 +118,7 @@ struct Workspace {
     DevBuf arena_d, arena_f, meta, partials, results, counter, cc_meta, pair_tables, short_done;
     PinnedBuf hmeta, hres, cc_hmeta;
     hipEvent_t ev0 = nullptr, ev1 = nullptr, done = nullptr;
+    hipEvent_t early0 = nullptr, early1 = nullptr;  // around the first steps of samples
     Workspace() = default;
     Workspace(const Workspace&) = delete;
     Workspace& operator=(const Workspace&) = delete;

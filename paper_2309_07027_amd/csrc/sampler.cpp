@@ -397,16 +397,16 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
         M = D;
     }
     const int32_t* pi_dev = reinterpret_cast<const int32_t*>(M + o_pi);
-    // the walks are timed; the early launch is where there are none
-    const bool time_early = items.empty() && !early.empty();
-    if (time_early) BBFG_HIP(hipEventRecord(w.ev0, s));
+    // timed as the walks are (run_perms), whose flops its own are counted with
+    p.has_early = !early.empty();
+    if (p.has_early) BBFG_HIP(hipEventRecord(w.early0, s));
     BBFG_HIP(launch_cc_early((uint32_t)early.size(), reinterpret_cast<const CCEarly*>(M + o_first), pi_dev,
                              reinterpret_cast<const double*>(M + o_us), reinterpret_cast<int32_t*>(H + p.o_early),
                              reinterpret_cast<double*>(H + p.o_early_tv), s));
-    if (time_early) BBFG_HIP(hipEventRecord(w.ev1, s));
+    if (p.has_early) BBFG_HIP(hipEventRecord(w.early1, s));
     RunResult rr;
     if (!items.empty()) BBFG_TRY(run_perms(c, w, items, 0, false, nullptr, nullptr, &rr, false));
-    p.has_items = !items.empty() || time_early;
+    p.has_items = !items.empty();
     // the minors' diagnostics follow their nres results (run_perms)
     BBFG_HIP(launch_cc_weights((uint32_t)steps.size(), reinterpret_cast<const CCStep*>(M + o_steps), pi_dev,
                                reinterpret_cast<const uint32_t*>(M + o_slot), w.results.as<double>(),
@@ -448,11 +448,14 @@ int cc_step_end(Workspace& w, std::vector<ActiveSample>& act, CCPending& p, doub
     if (!p.queued) return BBFG_OK;
     p.queued = false;
     BBFG_HIP(hipEventSynchronize(w.done));
-    if (p.has_items && kernel_ms) {
+    auto add_time = [kernel_ms](hipEvent_t from, hipEvent_t to) -> int {
         float ms = 0.f;
-        BBFG_HIP(hipEventElapsedTime(&ms, w.ev0, w.ev1));
+        BBFG_HIP(hipEventElapsedTime(&ms, from, to));
         *kernel_ms += ms;
-    }
+        return BBFG_OK;
+    };
+    if (p.has_early && kernel_ms) BBFG_TRY(add_time(w.early0, w.early1));
+    if (p.has_items && kernel_ms) BBFG_TRY(add_time(w.ev0, w.ev1));
     const int32_t* first = reinterpret_cast<const int32_t*>(w.cc_hmeta.as<char>() + p.o_early);
     const double* first_tv = reinterpret_cast<const double*>(w.cc_hmeta.as<char>() + p.o_early_tv);
     for (size_t i = 0; i < p.act_of_early.size(); ++i) {

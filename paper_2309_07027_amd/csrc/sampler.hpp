@@ -118,6 +118,7 @@ struct CCPending {
     size_t o_drawn = 0;               // offset of the draws in w.cc_hmeta
     size_t o_tv = 0;                  // offset of the steps' error estimates in w.cc_hmeta
     bool has_items = false;           // a minors launch was queued (timed by w.ev0/ev1)
+    bool has_early = false;           // an early launch was queued (timed by w.early0/early1)
     double flops = 0.0;               // algorithmic flops of the queued minors walks
     bool queued = false;
 };
