@@ -275,7 +275,9 @@ int perm_batch_last_was_graph(void);
  * other items of the batch.  L is chosen by an autotuner that times synthetic
  * batches of n-photon permanents (photons at random on 60 modes) for
  * L in {64, ..., 4096} on the current device and keeps the longest L within 2 %
- * of the best rate (the shortest for BBFG_MINORS); untuned n use L = 512.  The
+ * of the best rate (the shortest for BBFG_MINORS); untuned n use L = 512, and so
+ * do n whose FP64 items all go over pairs of columns, a walk with a split of its
+ * own.  The
  * leave-one-column-out walks of the sampler (precision BBFG_MINORS; n = the
  * size of the minors, n + 1 columns) are tuned separately: a unit of theirs
  * ends with one reduction per target column.

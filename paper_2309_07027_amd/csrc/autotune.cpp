@@ -16,6 +16,11 @@
 // from the median of three launches after a warm-up launch.
 // The leave-one-column-out walks of the sampler (kind BBFG_MINORS) end every
 // unit with one reduction per target column, so they are tuned on their own.
+// Only what a unit length sets is timed: items that go over the pair walk, which
+// splits itself, stay out of an FP64 batch (an n all of whose items do keeps the
+// length of the n before, or the default), and candidates that split every item
+// alike, as short walks over pairs are cut into 64 units or units of 16 steps
+// anyway, share one measurement.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -94,22 +99,33 @@ try {
             (int)std::max<int64_t>(2, std::min<int64_t>(minors ? 256 : 1024, (int64_t(1) << 31) >> (n - 1)));
         const int cols = minors ? n + 1 : n;
         synthetic_batch(n, cols, distinct, 0x5eedULL * (uint64_t)n + (minors ? 7 : 0), A, aoff, rows, mult, moff);
-        int count = distinct;
+        std::vector<int> tuned;  // the items that the length splits
+        uint64_t per = 0;
+        for (int i = 0; i < distinct; ++i) {
+            std::shared_ptr<const HostPlan> pl;
+            BBFG_TRY(get_plan(*c, mult.data() + moff[(size_t)i], rows[(size_t)i], n, kind, PLAN_BATCH, &pl));
+            if (pl->pair) continue;
+            tuned.push_back(i);
+            per += pl->n_addends;
+        }
+        if (tuned.empty()) {
+            const auto before = c->batch_L.find(std::make_pair(n - 1, kind));
+            c->batch_L[std::make_pair(n, kind)] =
+                n > n_lo && before != c->batch_L.end() ? before->second : kDefaultBatchUnit;
+            ++c->plan_epoch;
+            continue;
+        }
+        int count = (int)tuned.size();
         if (!minors) {
-            uint64_t per = 0;
-            for (int i = 0; i < distinct; ++i) {
-                std::shared_ptr<const HostPlan> pl;
-                BBFG_TRY(get_plan(*c, mult.data() + moff[(size_t)i], rows[(size_t)i], n, kind, PLAN_BATCH, &pl));
-                per += pl->n_addends;
-            }
-            const double want = std::ldexp(1.0, 28) / (double)std::max<uint64_t>(1, per) * distinct;
-            count = (int)std::min(16384.0, std::max((double)distinct, std::ceil(want)));
+            const double want = std::ldexp(1.0, 28) / (double)std::max<uint64_t>(1, per) * count;
+            count = (int)std::min(16384.0, std::max((double)count, std::ceil(want)));
         }
         DevBuf dA;
         BBFG_TRY(dA.ensure(sizeof(double) * A.size()));
         BBFG_HIP(hipMemcpyAsync(dA.p, A.data(), sizeof(double) * A.size(), hipMemcpyHostToDevice, s));
         BBFG_HIP(hipStreamSynchronize(s));
         std::vector<std::pair<uint64_t, double>> rates;  // (L, addends per ms)
+        std::vector<std::vector<uint64_t>> splits;       // units of every item at each of them
         for (uint64_t L : kCandidates) {
             c->batch_L[std::make_pair(n, kind)] = L;
             ++c->plan_epoch;
@@ -117,8 +133,9 @@ try {
             std::deque<std::vector<int32_t>> keep;
             std::vector<uint32_t> slot((size_t)cols);
             uint64_t addends = 0, nres = 0;
+            std::vector<uint64_t> split;
             for (int rep_item = 0; rep_item < count; ++rep_item) {
-                const int i = rep_item % distinct;
+                const int i = tuned[(size_t)rep_item % tuned.size()];
                 PermItem it;
                 it.src = dA.as<double>();
                 it.src_off = (uint64_t)aoff[(size_t)i];
@@ -128,6 +145,7 @@ try {
                 it.mult = mult.data() + moff[(size_t)i];
                 BBFG_TRY(get_plan(*c, it.mult, it.n_rows, n, kind, PLAN_BATCH, &it.plan));
                 addends += it.plan->n_addends;
+                if ((size_t)rep_item < tuned.size()) split.push_back(it.plan->units);
                 if (minors) {
                     keep.emplace_back((size_t)cols);
                     for (int j = 0; j < cols; ++j) keep.back()[(size_t)j] = j;
@@ -138,6 +156,12 @@ try {
                 } else {
                     items.push_back(std::move(it));
                 }
+            }
+            const size_t like = (size_t)(std::find(splits.begin(), splits.end(), split) - splits.begin());
+            splits.push_back(split);
+            if (like < rates.size()) {
+                rates.push_back({L, rates[like].second});
+                continue;
             }
             std::vector<double> ms;
             for (int rep = 0; rep < 4; ++rep) {
