@@ -29,6 +29,7 @@ namespace bbfg {
 namespace {
 
 constexpr uint32_t kShortWaves = 4;
+constexpr int kWaitVector = 0x0F70;  // s_waitcnt vmcnt(0)
 
 __device__ __forceinline__ double readlane_f64(double x, int k)
 {
@@ -174,8 +175,13 @@ __global__ __launch_bounds__(kWave * kShortWaves) void walk_short_kernel(ShortAr
             for (int q = 0; q < kPartialDoubles; ++q)
                 __hip_atomic_store(p + q, x[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // Each wavefront waits for its own stores: the work group's barrier does
-            // not, and the release before its count covers wavefront 0 alone.
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            // not, and the release before its count waits for wavefront 0's alone (what
+            // it writes back covers the compute unit's stores that have arrived).  A
+            // release fence here would write back the cache once a wavefront: 20 columns
+            // 45 us a call instead of 39.
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(kWaitVector);
+            asm volatile("" ::: "memory");
         }
     }
     if (d.units == 1) {
