@@ -326,43 +326,41 @@ int cc_step_begin(Context& c, Workspace& w, std::vector<ActiveSample>& act, CCPe
         for (int l = 0; l < k; ++l) pis.push_back(S.pi[(size_t)l]);
         const uint64_t x = splitmix64_draw(S.key, (uint64_t)(J.n - 1 + (k - 1)));
         st.u = (double)(x >> 11) * 0x1.0p-53;
-        if (k >= 2) {
-            // the k minors share the prefix rows: one joint walk over k columns.
-            // Rows are listed by multiplicity (then mode), so the plan depends on
-            // the multiset of multiplicities only and is shared by many steps.
-            std::map<int32_t, int32_t> cnt;
-            for (int32_t r : S.prefix) cnt[r]++;
-            std::vector<std::pair<int32_t, int32_t>> rm(cnt.begin(), cnt.end());  // (mode, count)
-            std::sort(rm.begin(), rm.end(), [](const std::pair<int32_t, int32_t>& a, const std::pair<int32_t, int32_t>& b) {
-                return a.second != b.second ? a.second < b.second : a.first < b.first;
-            });
-            keep.emplace_back();
-            std::vector<int32_t>& rowmap = keep.back();
-            keep.emplace_back();
-            std::vector<int32_t>& mult = keep.back();
-            for (auto& kv : rm) {
-                rowmap.push_back(kv.first);
-                mult.push_back(kv.second);
-            }
-            PermItem proto;
-            BBFG_TRY(get_plan(c, mult.data(), (int)mult.size(), k - 1, BBFG_MINORS, PLAN_BATCH, &proto.plan));
-            proto.src = J.A.as<double>();
-            proto.src_off = 0;
-            proto.ld = (uint32_t)J.n;
-            proto.n_rows = (int)mult.size();
-            proto.n = k - 1;
-            proto.mult = mult.data();
-            proto.row_map = rowmap.data();
-            st.minor_off = (uint32_t)slots.size();
-            slots.resize(slots.size() + (size_t)k);
-            const size_t first = items.size();
-            add_minor_items(proto, S.pi.data(), keep, items, nres, slots.data() + st.minor_off);
-            for (size_t i = first; i < items.size(); ++i) nres += (uint64_t)items[i].targets;
-            if (addends) *addends += (uint64_t)k * proto.plan->n_addends;
-            bool bunched = false;
-            for (int32_t x : mult) bunched = bunched || x > 1;
-            p.flops += (double)proto.plan->n_addends * minors_flops(k, bunched);
+        // the k minors share the prefix rows: one joint walk over k columns.
+        // Rows are listed by multiplicity (then mode), so the plan depends on
+        // the multiset of multiplicities only and is shared by many steps.
+        std::map<int32_t, int32_t> cnt;
+        for (int32_t r : S.prefix) cnt[r]++;
+        std::vector<std::pair<int32_t, int32_t>> rm(cnt.begin(), cnt.end());  // (mode, count)
+        std::sort(rm.begin(), rm.end(), [](const std::pair<int32_t, int32_t>& a, const std::pair<int32_t, int32_t>& b) {
+            return a.second != b.second ? a.second < b.second : a.first < b.first;
+        });
+        keep.emplace_back();
+        std::vector<int32_t>& rowmap = keep.back();
+        keep.emplace_back();
+        std::vector<int32_t>& mult = keep.back();
+        for (auto& kv : rm) {
+            rowmap.push_back(kv.first);
+            mult.push_back(kv.second);
         }
+        PermItem proto;
+        BBFG_TRY(get_plan(c, mult.data(), (int)mult.size(), k - 1, BBFG_MINORS, PLAN_BATCH, &proto.plan));
+        proto.src = J.A.as<double>();
+        proto.src_off = 0;
+        proto.ld = (uint32_t)J.n;
+        proto.n_rows = (int)mult.size();
+        proto.n = k - 1;
+        proto.mult = mult.data();
+        proto.row_map = rowmap.data();
+        st.minor_off = (uint32_t)slots.size();
+        slots.resize(slots.size() + (size_t)k);
+        const size_t first = items.size();
+        add_minor_items(proto, S.pi.data(), keep, items, nres, slots.data() + st.minor_off);
+        for (size_t i = first; i < items.size(); ++i) nres += (uint64_t)items[i].targets;
+        if (addends) *addends += (uint64_t)k * proto.plan->n_addends;
+        bool bunched = false;
+        for (int32_t x : mult) bunched = bunched || x > 1;
+        p.flops += (double)proto.plan->n_addends * minors_flops(k, bunched);
         steps.push_back(st);
         act_of_step.push_back(ai);
     }
