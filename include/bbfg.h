@@ -78,8 +78,10 @@ typedef struct {
     double rel_err_est;  /* estimated relative error of the result: kappa * u * (n + sqrt(Q)) */
     double kappa;        /* (sum |addend|) / |sum of addends|: conditioning of the sum */
     uint64_t n_addends;  /* number of distinct addends C' = prod_k (M'_k + 1) (Sec. 2.2) */
-    uint64_t n_units;    /* independent work units (one wavefront each) */
-    double kernel_ms;    /* device time of the walk kernel, from HIP events on the library stream */
+    uint64_t n_units;    /* independent work units: a wavefront each, 16 wavefronts in the walk over pairs
+                          * of columns (long sums), 4 in the leave-one-column-out walk over pairs */
+    double kernel_ms;    /* device time of the walk kernels, from HIP events on the library stream; of a
+                          * short permanent, which is one launch, from the device's own clock */
     double flops;        /* algorithmic FP64 flops of the call's walks (an FMA counts 2): C' F per
                           * permanent with F = 8n - 4 (all M = 1) or 8n - 2; per leave-one-column-out
                           * addend over K columns F = 22K - 36 (all M = 1) or 22K - 32 */
@@ -129,7 +131,10 @@ int bbfg_set_stream(void *hip_stream);
  *
  * Result: column sums and products in FP64, re-seeded at every work-unit and
  * Gray-block start; per-unit partials reduced across the wavefront and across
- * units in double-double, then scaled by 2^{1-n} exactly.
+ * units in double-double, then scaled by 2^{1-n} exactly.  Sums of more than
+ * 2^19 addends (perm_ryser 2^20, perm_bbfg_cols 2^22) with four rows of
+ * multiplicity one form the products of pairs of column sums from differences
+ * over those rows, or, where their entries dominate a column, from the sums.
  * Errors: BBFG_EINVAL (null A/out with n > 0, negative multiplicity, sum
  * mismatch), BBFG_ERANGE (n_cols > BBFG_MAX_N), BBFG_ENOMEM, BBFG_EDEVICE.
  */
@@ -160,7 +165,9 @@ int perm_ryser(const bbfg_c128 *A, int32_t n_rows, const int32_t *row_mult, int3
 /*
  * perm_bbfg_noalloc -- perm_bbfg for callers that cannot allocate device
  * memory (tight serving loops, code that must not call hipMalloc).  Same
- * arguments, plan, kernels and result bits as perm_bbfg; every device buffer
+ * arguments and result bits as perm_bbfg within the limits below (a short sum
+ * takes a launch sequence here where perm_bbfg takes one launch, with the same
+ * arithmetic in the same order); every device buffer
  * it uses (binomial table, metadata, Gray table, staged host A, gathered rows,
  * unit partials, results) lives in one file-scope device array of 3 MiB per
  * device, which stays allocated until the process ends.  It calls no
@@ -169,8 +176,11 @@ int perm_ryser(const bbfg_c128 *A, int32_t n_rows, const int32_t *row_mult, int3
  * device; a first call on a device without it does so itself.
  *
  * Limits: n_cols <= BBFG_MAX_N (else BBFG_ERANGE); a host A has at most 256
- * rows (BBFG_ERANGE beyond); the walk is split into at most 32768 units
- * (longer units for the largest sums).  info->kernel_ms is not measured (0).
+ * rows (BBFG_ERANGE beyond); the walk is split into at most 32768 units.  A
+ * long sum that perm_bbfg splits into more (on 256 compute units from 2^35
+ * addends on: 36 rows of multiplicity one) is walked addend by addend here, in
+ * longer units: other last bits, within the same error estimate, and about 1.4
+ * times the time.  info->kernel_ms is not measured (0).
  * Calls are serialised inside the process (they share the array); the call is
  * synchronous, so nothing of it overlaps the next call.
  * Errors: as perm_bbfg.

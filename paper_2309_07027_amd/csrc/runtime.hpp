@@ -291,18 +291,17 @@ uint64_t fill_pair_desc(PairDesc& q, const PermDesc& d, const HostPlan& p, uint6
 // The kept rows of the pair walk's inner digits, a bit each.
 uint64_t pair_inner_rows(const PairPlan& p);
 
-// Evaluates items (all n >= 1).  The (re, im) results stay in c.results (item
-// order; an item with targets = G has G consecutive results) and, when out_host
-// is not null, are copied to out_host[2*i]; the diagnostics (err_est, kappa) to
-// diag_host[2*i] (for minor items from the sampled magnitude sums, see
-// walk_minors_unit).  The device copy of the diagnostics follows the results:
-// w.results + 2 * (number of results).  With sync = false nothing is
-// copied back and the stream is not synchronised (the caller queues more work
-// that reads c.results).  single = true uses the one-permanent launch.
+// Evaluates items (all n >= 1) in workspace w.  The (re, im) results (item order;
+// an item with targets = G has G consecutive ones) go to out_host[2*i] and the
+// diagnostics (err_est, kappa) to diag_host[2*i], each when not null (for minor
+// items from the sampled magnitude sums, see walk_minors_unit).  With sync = false
+// nothing is copied back and the stream is not synchronised: the results are left
+// in w.results and the diagnostics behind them (w.results + 2 * number of
+// results) for work that the caller queues.  (A synchronous call of at most
+// kDirectResults leaves nothing there.)  single = true uses the one-permanent launch.
 // use_graph = true captures a layout into a hipGraph the second time it is
-// seen and replays the graph from then on.
-// Runs in workspace w (the context's own by default); the results stay in
-// w.results.
+// seen and replays the graph from then on.  The overload below runs in the
+// context's own workspace.
 int run_perms(Context& c, Workspace& w, std::vector<PermItem>& items, int f32, bool single, double* out_host,
               double* diag_host, RunResult* rr, bool sync = true, bool use_graph = false);
 // Evaluates one plain FP64 permanent (no maps, no column multiplicities) in one
