@@ -20,7 +20,7 @@
 // the results, so no column sum drifts.
 //
 // Bound by FP64 issue: 133 VALU instructions a pair and block, 132 of them FP64,
-// 91 % of the issue slots used at 30 columns.  16 wavefronts of at most 128
+// 89 % of the issue slots used at 30 columns.  16 wavefronts of at most 128
 // registers share one unit's lane parts (6 KB a pair); 12 of 160 registers, with
 // the lane parts fetched a pair ahead, measured 3 % slower.  Measured against
 // the walk of walk_core.hpp: 30 columns, 2^29 addends, 2.98 -> 2.09 ms (kernel);
@@ -102,7 +102,8 @@ BBFG_FN void cmul_into(cpx& p, cpx v)
 // half of the other entries have to reach 1/16 of the largest inner one: with
 // rows 16 times the others that cancel as above the differences are off by as
 // much as the plain walk, with 64 times by ten times as much.  Entries of like
-// distribution (Gaussian, Haar) fail it in fewer than one column of a million.
+// distribution (Gaussian, Haar) fail it in fewer than one column of a million
+// beside ten other rows, in 2e-5 of the columns beside five, 3e-4 beside three.
 constexpr double kInnerRange = 16.0;
 template <typename Mag>
 BBFG_FN bool differences_serve(int r, uint64_t inner_rows, Mag mag)
